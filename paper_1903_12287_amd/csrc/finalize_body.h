@@ -6,6 +6,39 @@
 #include "kernels.h"
 #include "device_common.h"
 
+// ---- row scales of the ranking backward --------------------------------------
+// Every row's fp16 scale relative to the largest row of its (chunk, side) of
+// nn and of qk, 2^(e - e_max + 15), 0 for rows more than 29 binades below it.
+// Each of the chunk's nblk workgroups finds the four largest exponents again
+// (a few thousand floats that the L2 holds; one atomic maximum a row in the
+// gather cost it twenty times its own time) and writes its share of the scales.
+__device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b, int c, int Cc, int blk, int nblk) {
+  __shared__ int tops[FIN_THREADS / PBG_WAVE];
+  const int Nc = Cc + g.U;
+  for (int k = 0; k < 4; ++k) {
+    const bool nn = k < 2;
+    const int z = c * 2 + (k & 1), rows = nn ? Nc : Cc;
+    const float* is = nn ? b.pn_is + (int64_t)z * g.N : b.pq_is + (int64_t)z * g.C;
+    float m = 0.0f;
+#pragma unroll 4
+    for (int t = threadIdx.x; t < rows; t += FIN_THREADS) m = fmaxf(m, is[t]);
+    m = group16_max(m);
+    m = fmaxf(m, __shfl_xor(m, 16, PBG_WAVE));
+    m = fmaxf(m, __shfl_xor(m, 32, PBG_WAVE));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) tops[threadIdx.x >> 6] = (int)(__float_as_uint(m) >> 23) + 14;
+    __syncthreads();
+    int top = tops[0];
+    for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) top = max(top, tops[w]);
+    if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_max : b.pq_max)[z] = top;
+    uint16_t* ks = nn ? b.nks + (int64_t)z * g.ks_n : b.qks + (int64_t)z * g.ks_q;
+    for (int t = blk * FIN_THREADS + threadIdx.x; t < rows; t += nblk * FIN_THREADS) {
+      const int ex = 30 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top;
+      ks[t] = (uint16_t)(ex > 0 ? ex << 10 : 0);
+    }
+  }
+}
+
 // ---- per-edge dL/dp, translation bias gradient, losses ------------------------
 // Workgroup blk of chunk c (FIN_THREADS rows): writes its share of the chunk
 // loss to parts[c * nblk + blk].
@@ -14,6 +47,7 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
   const int Cc = chunk_edges(g, c);
   double acc = 0.0;
   const int e = blk * FIN_THREADS + threadIdx.x;
+  if (g.pieces == PIECES_SCALED && g.loss == LOSS_RANKING) row_scales(g, b, c, Cc, blk, nblk);
   if (e < Cc) {
     const int64_t ce = (int64_t)c * g.C + e;
     const float p = b.pos[pos_index(g, c, 0, e)];
@@ -22,11 +56,20 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
     if (g.loss != LOSS_SOFTMAX) {
       const float* r0 = b.rowpart + ((int64_t)(c * 2 + 0) * g.C + e) * g.nct * 2;
       const float* r1 = b.rowpart + ((int64_t)(c * 2 + 1) * g.C + e) * g.nct * 2;
+      // column tiles with candidates of this chunk (merged: side 1's in-chunk
+      // tiles, then its uniform ones)
+      const int bn = g.pieces != PIECES_NONE ? PBG_PART_BN : PBG_SCORE_BN;
+      const int n0 = (Cc + g.U + bn - 1) / bn;
+      const int n1 = g.dq_has_dn ? (Cc + bn - 1) / bn + (g.U + bn - 1) / bn : n0;
 #pragma unroll 8
-      for (int ct = 0; ct < g.nct; ++ct) {
-        const float2 a0 = *(const float2*)(r0 + 2 * ct), a1 = *(const float2*)(r1 + 2 * ct);
+      for (int ct = 0; ct < n0; ++ct) {
+        const float2 a0 = *(const float2*)(r0 + 2 * ct);
         l0 += a0.x;
         d0 += a0.y;
+      }
+#pragma unroll 8
+      for (int ct = 0; ct < n1; ++ct) {
+        const float2 a1 = *(const float2*)(r1 + 2 * ct);
         l1 += a1.x;
         d1 += a1.y;
       }

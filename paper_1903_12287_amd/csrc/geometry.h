@@ -36,6 +36,13 @@ enum { LOSS_RANKING = 0, LOSS_LOGISTIC = 1, LOSS_SOFTMAX = 2 };
 #define PBG_EPS_NORM 1e-12f
 #define PBG_EPS_ADAGRAD 1e-10f
 #define PBG_SCORE_BN 128  // column tile of the score contraction
+#define PBG_PART_BN 64    // columns of a row partial of the score contraction on row pieces
+// row tile of the score contraction on row pieces: 256, or 128 where a chunk
+// holds no more edges
+__host__ __device__ inline int score_rows(int C) { return C <= 128 ? 128 : 256; }
+
+// Row pieces of the packed rows (pieces.h) that the gather writes beside them
+enum { PIECES_NONE = 0, PIECES_UNIT = 1, PIECES_SCALED = 2 };
 
 struct StepGeom {
   int C, U, N;      // chunk capacity, uniform draws per side, N = C + U
@@ -59,6 +66,9 @@ struct StepGeom {
   int relsum;       // one relation operator for every edge (not linear): the operator backward adds the
                     // parameter-gradient rows of each block and relc holds one row per block
   const float* cweight;   // relation weight of each chunk of the step (device), NULL: all 1
+  int pieces;       // PIECES_*
+  int dh, pld;      // elements of a row of pieces (dim rounded up to 8), 16-bit words a row
+  int ks_n, ks_q;   // row strides of nks / qks (candidates and edges rounded up to 32)
   int dq_has_dn;    // with QK_IN_NN: dq of side s, row e < Cc, already holds dn of side 1 - s, row e (the
                     // ranking backward merged them), and those dn rows are not written
 };
@@ -117,11 +127,25 @@ struct StepBufs {
   float* qk;
   float* nn;
   float* nrm;           // [S][2][N] norms of the raw vectors behind nn (cos)
+  // pieces of nn and qk ([S][2][N or C][pld]); PIECES_SCALED: their rows' inverse scales, the scale exponent of
+  // each (chunk, side)'s largest row, and every row's fp16 scale relative to it
+  uint16_t* pn;
+  uint16_t* pq;
+  float* pn_is;         // [S][2][N]
+  float* pq_is;         // [S][2][C]
+  int* pn_max;          // [S][2]
+  int* pq_max;          // [S][2]
+  uint16_t* nks;        // [S][2][ks_n]
+  uint16_t* qks;        // [S][2][ks_q]
   float* pos;           // [S][C] positive scores ([S][2][C] with reciprocal predicates)
   float* bias;          // [S][C] <theta_r, x_d> (translation + dot)
   int32_t* neg;         // [S][2][U] uniform draws (side 0 from partition j, side 1 from i)
   float* ds;            // [S][2][C][Np] dL/dS (logistic, softmax)
-  uint16_t* dsb;        // [S][2][ceil(Np/16)][C] dL/dS bits (ranking, float32 path)
+  uint16_t* dsb;        // [S][2][ceil(Np/16)][C] dL/dS bits (ranking, bf16 inputs)
+  uint32_t* bits0;      // dL/dS bits (ranking, float32 path; BitsView in kernels.h)
+  uint32_t* bits1;
+  int64_t bits_cs, bits_ss, bits1_cs;
+  int bits_rb, bits_cb, bits_cb1;
   float* rowpart;       // [S][2][C][nct][2]  per score tile: (loss, dS sum) or, for
                         // softmax, (tile max, sum exp(s - tile max))
   float* rowscale;      // [S][2][nct][C]  softmax on split pieces: exp(tile max - lse)

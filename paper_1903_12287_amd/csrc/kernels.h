@@ -44,7 +44,7 @@ enum {
 struct GemmArgsH {
   const uint16_t* A;
   const uint16_t* B;     // planes pieces of B, b_ps elements apart
-  int planes;            // 1, or 3: the exact bf16 pieces of a float32 operand (A = bit matrix only)
+  int planes;            // 1, or 3: the exact bf16 pieces of a float32 operand (launch_gemm_split_pair)
   int64_t b_ps;
   const float* Af;       // launch_score_split: float32 operands [m][k] and [n][k]
   const float* Bf;
@@ -74,10 +74,6 @@ struct GemmArgsH {
   int share_cc;          // launch_score_split with Q of each side the first C candidate rows of the
                          // other: the in-chunk block of side 1 is the transpose of side 0's, and side 0's
                          // full tiles inside it produce side 1's too
-  int merge_cc;          // ranking backward with the same Q / candidate rows (launch_gemm_bf16_pair, three
-                         // planes): a0's dQ rows e < Cc of side s also take dN of candidate e of side 1 - s
-                         // (the same vector; a0.A's other side read by columns over k < Cc), and a1's dN rows
-                         // start at Cc rounded down to 16 (the rows below are left unwritten)
 };
 
 // bf16-input score contraction with a loss epilogue (EPI_LOSS, EPI_LOSS_BITS or
@@ -116,6 +112,81 @@ void launch_finalize_split3_t(const StepGeom& g, const StepBufs& b, double* part
 void launch_split3_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qT, int64_t qT_bs, int64_t q_ps,
                      int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nT, int64_t nT_bs,
                      int64_t n_ps, int n_ldT, int ld_src, int kp, int batches, hipStream_t s);
+
+// ---- contractions on row pieces (pieces.h) ---------------------------------------
+// The ranking loss keeps dS (0 or 1) as bits, in 16 x 16 blocks of eight
+// 32-bit words [half][r], r = 0..3: the low and high 16 bits of word (half, r)
+// are rows 8 half + r and 8 half + 4 + r of the block, bit k its column k.
+// Block (row block rb, column block cb) of a (chunk, side) sits at word
+// (cb * RB + rb) * 8.  Rows past the chunk's edges and columns past its
+// candidates are 0 in every block of a 128 x 128 tile that holds any score.
+// StepGeom::dq_has_dn (merged): side 0 holds all its candidates; the second
+// plane holds, at (edge e, edge i), side 1's bit of edge i and in-chunk
+// candidate e; side 1's own bits start at the first uniform candidate.
+struct BitsView {
+  uint32_t* b0;           // [S][2][CB][RB][8]
+  uint32_t* b1;           // [S][CB1][RB][8], merged only
+  int RB, CB, CB1;
+};
+inline BitsView bits_view(int C, int U) {
+  BitsView v{nullptr, nullptr, (C + 255) / 256 * 16, (C + U + 127) / 128 * 8, (C + 127) / 128 * 8};
+  return v;
+}
+
+struct ScoreArgs {
+  const uint16_t *A, *B;        // pieces of the queries and of the candidates: dh elements, ld words a row
+  int64_t a_cs, a_ss, b_cs, b_ss;
+  int dh, ld;
+  const float *ia, *ib;         // inverse row scales (NULL: unit rows, factor unscale for the product)
+  int64_t ia_cs, ia_ss, ib_cs, ib_ss;
+  float unscale, iunscale;      // 2^-30 and 2^30 (unit rows in two fp16 planes), or 1
+  int C, U, m_step;
+  const int32_t* cstart;
+  int Mfix, Nfix;               // Mfix > 0: one plain product of that size, no chunks
+  int nsides;
+  int share;                    // queries are the other side's candidates: side 0's in-chunk tiles
+                                // also give side 1's, side 1 computes its uniform candidates only
+  const float* pos;
+  int pos_sides;
+  const float* bias;
+  float margin;
+  int loss;
+  float* rowpart;               // [c][2][C][nct][2], column blocks of 64 (share: side 1's in-chunk
+  int nct;                      // blocks first, then its uniform ones)
+  uint32_t *bits0, *bits1;
+  int64_t bits_cs, bits_ss, bits1_cs;   // words
+  int RB;
+  float* Cm;                    // float32 scores (EPI_STORE)
+  int64_t c_cs, c_ss;
+  int ldc;
+};
+void launch_score(const ScoreArgs& a, int epi, int nchunks, hipStream_t s);
+
+// dQ = dS . N and dN = dS^T . Q of the ranking loss from the bits and the
+// planes of N and Q
+struct BitsArgs {
+  const uint16_t *N, *Q;
+  int64_t n_cs, n_ss, q_cs, q_ss;
+  int dh, ld, dp;
+  const uint32_t *bits0, *bits1;
+  int64_t bits_cs, bits_ss, bits1_cs;
+  int RB, CB, CB1;
+  int C, U, m_step;
+  const int32_t* cstart;
+  int merged;                   // dQ of side s, edge e also takes dN of side 1 - s; dN: uniform rows only
+  const uint16_t *nks, *qks;    // fp16 scale of each row relative to the largest (NULL: unit rows)
+  int64_t nks_cs, nks_ss, qks_cs, qks_ss;
+  const int *nmax, *qmax;       // [c][2] scale exponent of the largest row
+  float unscale;                // factor of the sums (unit rows)
+  const float* cscale;          // relation weight of each chunk
+  float *dq, *dn;
+  int64_t dq_cs, dq_ss, dn_cs, dn_ss;
+};
+void launch_bits_backward(const BitsArgs& a, int nchunks, hipStream_t s);
+// planes of the queries (qk) of both sides, or of side 1's candidates (nn):
+// the rows that the linear operator's products leave behind the gather
+void launch_query_pieces(const StepGeom& g, const StepBufs& b, hipStream_t s);
+void launch_candidate_pieces(const StepGeom& g, const StepBufs& b, hipStream_t s);
 
 // ---- gather / operator / negatives --------------------------------------------
 void launch_gather(const StepGeom& g, const StepBufs& b, hipStream_t s);
@@ -300,4 +371,6 @@ void launch_add_side_bias(const StepGeom& g, const float* bias, float* out, hipS
 // dL/dS as float32 [c][2][C][N] from the layout `mode` (DS_*) the loss left it in
 void launch_expand_ds(const StepGeom& g, int mode, const uint16_t* bits, int nw, int ldw, const float* f32,
                       const float* scale, const uint16_t* h, int ld, float* out, hipStream_t s);
+// the same from the ranking bits of BitsView
+void launch_expand_bits(const StepGeom& g, const StepBufs& b, float* out, hipStream_t s);
 void launch_copy_pos(const StepGeom& g, const float* pos, float* out, hipStream_t s);

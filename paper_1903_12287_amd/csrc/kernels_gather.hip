@@ -15,7 +15,7 @@
 // and every candidate row is the entity itself (a unit vector for cos).
 #include <algorithm>
 #include "kernels.h"
-#include "row_ops.h"
+#include "row_pieces.h"
 
 namespace {
 
@@ -67,6 +67,8 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
       // Q and K are these candidate rows (QK_IN_NN)
       row_store(gq, b.nn + ((int64_t)(c * 2 + 1) * g.N + e) * dp, d, dp, cplx, lane);
       row_store(y, b.nn + ((int64_t)(c * 2 + 0) * g.N + e) * dp, d, dp, cplx, lane);
+      candidate_pieces(g, b, c, 1, e, gq, cplx, lane);
+      candidate_pieces(g, b, c, 0, e, y, cplx, lane);
       if (lane == 0) {
         b.pos[(int64_t)c * g.C + e] = p;
         b.bias[(int64_t)c * g.C + e] = 0.0f;
@@ -108,6 +110,8 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
         }
         row_store(y, n0row, d, dp, cplx, lane);
         row_store(x, n1row, d, dp, cplx, lane);
+        candidate_pieces(g, b, c, 0, e, y, cplx, lane);
+        candidate_pieces(g, b, c, 1, e, x, cplx, lane);
         return;
       }
       Row tr;
@@ -128,6 +132,10 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
       row_store(gk, krow, d, dp, cplx, lane);
       row_store(y, n0row, d, dp, cplx, lane);
       row_store(x, n1row, d, dp, cplx, lane);
+      query_pieces(g, b, c, 0, e, gq, cplx, lane);
+      query_pieces(g, b, c, 1, e, gk, cplx, lane);
+      candidate_pieces(g, b, c, 0, e, y, cplx, lane);
+      candidate_pieces(g, b, c, 1, e, x, cplx, lane);
       if (lane == 0) {
         b.pos[(int64_t)(c * 2 + 0) * g.C + e] = p0;
         b.pos[(int64_t)(c * 2 + 1) * g.C + e] = p1;
@@ -148,6 +156,7 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
         const float ny = row_normalize(y);
         row_store(y, n0row, d, dp, cplx, lane);
         row_store(x, b.lin_x + ((int64_t)c * g.N + e) * dp, d, dp, cplx, lane);
+        candidate_pieces(g, b, c, 0, e, y, cplx, lane);
         if (lane == 0) {
           b.bias[(int64_t)c * g.C + e] = 0.0f;
           b.nrm[(int64_t)(c * 2 + 0) * g.N + e] = ny;
@@ -158,6 +167,8 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
       // (one relation: as contractions over the whole step; several: per edge)
       row_store(y, n0row, d, dp, cplx, lane);
       row_store(x, n1row, d, dp, cplx, lane);
+      candidate_pieces(g, b, c, 0, e, y, cplx, lane);
+      candidate_pieces(g, b, c, 1, e, x, cplx, lane);
       if (lane == 0) b.bias[(int64_t)c * g.C + e] = 0.0f;
       return;
     }
@@ -172,6 +183,10 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
       row_store(k, krow, d, dp, cplx, lane);
       row_store(y, n0row, d, dp, cplx, lane);
       row_store(x, n1row, d, dp, cplx, lane);
+      query_pieces(g, b, c, 0, e, gq, cplx, lane);
+      query_pieces(g, b, c, 1, e, k, cplx, lane);
+      candidate_pieces(g, b, c, 0, e, y, cplx, lane);
+      candidate_pieces(g, b, c, 1, e, x, cplx, lane);
       if (lane == 0) {
         b.pos[(int64_t)c * g.C + e] = p;
         b.bias[(int64_t)c * g.C + e] = bs;
@@ -183,6 +198,8 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
       // Q and K are these candidate rows (QK_IN_NN)
       row_store(gq, n1row, d, dp, cplx, lane);
       row_store(y, n0row, d, dp, cplx, lane);
+      candidate_pieces(g, b, c, 1, e, gq, cplx, lane);
+      candidate_pieces(g, b, c, 0, e, y, cplx, lane);
       if (lane == 0) {
         b.pos[(int64_t)c * g.C + e] = p;
         b.bias[(int64_t)c * g.C + e] = 0.0f;
@@ -235,6 +252,7 @@ __global__ __launch_bounds__(256) void gather_op_kernel(StepGeom g, StepBufs b) 
     float* dstrow = raw_linear ? b.lin_x + ((int64_t)c * g.N + t) * dp
                                : b.nn + ((int64_t)(c * 2 + side) * g.N + t) * dp;
     row_store(v[q], dstrow, d, dp, cplx, lane);
+    if (!raw_linear) candidate_pieces(g, b, c, side, t, v[q], cplx, lane);
     if (lane == 0) {
       b.neg[(int64_t)(c * 2 + side) * g.U + k] = u[q];
       if (unit) b.nrm[(int64_t)(c * 2 + side) * g.N + t] = nv[q];
@@ -359,6 +377,26 @@ __global__ __launch_bounds__(256) void positive_scores_kernel(StepGeom g, StepBu
   if (lane == 0) b.pos[(int64_t)c * g.C + e] = p;
 }
 
+// pieces of rows already in the workspace: blockIdx.z 0 and 1 the queries of
+// side 0 and 1, 2 the candidates of side 1
+template <int RQ>
+__global__ __launch_bounds__(256) void row_pieces_kernel(StepGeom g, StepBufs b, int z0) {
+  const int lane = threadIdx.x & 63;
+  const int c = blockIdx.y, z = z0 + blockIdx.z;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int Cc = chunk_edges(g, c);
+  RowT<RQ> r;
+  if (z < 2) {
+    if (row >= Cc) return;
+    row_load(r, b.qk + ((int64_t)(c * 2 + z) * g.C + row) * g.dp, g.d, false, lane);
+    query_pieces(g, b, c, z, row, r, false, lane);
+  } else {
+    if (row >= Cc + g.U) return;
+    row_load(r, b.nn + ((int64_t)(c * 2 + 1) * g.N + row) * g.dp, g.d, false, lane);
+    candidate_pieces(g, b, c, 1, row, r, false, lane);
+  }
+}
+
 // row-major d x d matrices -> transposed copies (linear operator)
 __global__ void transpose_rel_kernel(const float* A, float* AT, int R, int d) {
   const int64_t n = (int64_t)R * d * d;
@@ -420,6 +458,23 @@ void launch_pad_linear(const float* A, int d, int dp, float* Ap, float* ATp, hip
   int blocks = (n + 255) / 256;
   if (blocks > 1024) blocks = 1024;
   pad_linear_kernel<<<blocks, 256, 0, s>>>(A, d, dp, Ap, ATp);
+}
+
+static void launch_row_pieces(const StepGeom& g, const StepBufs& b, int rows, int z0, int nz, hipStream_t s) {
+  if (g.pieces == PIECES_NONE) return;
+  const dim3 grid((rows + 3) / 4, g.nchunks, nz);
+  const int rq = row_width_for(g.d);
+  if (rq == 2) row_pieces_kernel<2><<<grid, 256, 0, s>>>(g, b, z0);
+  else if (rq == 4) row_pieces_kernel<4><<<grid, 256, 0, s>>>(g, b, z0);
+  else row_pieces_kernel<8><<<grid, 256, 0, s>>>(g, b, z0);
+}
+
+void launch_query_pieces(const StepGeom& g, const StepBufs& b, hipStream_t s) {
+  launch_row_pieces(g, b, g.C, 0, 2, s);
+}
+
+void launch_candidate_pieces(const StepGeom& g, const StepBufs& b, hipStream_t s) {
+  launch_row_pieces(g, b, g.N, 2, 1, s);
 }
 
 void launch_positive_scores(const StepGeom& g, const StepBufs& b, hipStream_t s) {

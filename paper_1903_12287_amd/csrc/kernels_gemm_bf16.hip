@@ -10,14 +10,6 @@
 // from its bit matrix (rows for dQ, columns for dN), otherwise from bf16 dS
 // rows (transposed on the way into LDS for dN), so no copy of dS^T exists.
 //
-// Float32 backward of the ranking loss on the same instruction: there dS is
-// 0 or 1, and a float32 operand x splits exactly into three bf16 pieces,
-// x = h + m + l (h = bf16(x), m = bf16(x - h), l = x - h - m, which needs at
-// most 8 significant bits).  Every product dS * piece is then exact and the
-// sums run in float32, so dS . N equals a float32 contraction up to the order
-// of the float32 additions.  The kernel takes B as PL = 3 planes (pieces) and
-// adds the three products into one accumulator.
-//
 // Layout and schedule follow the float32 kernel: 256-thread workgroups of
 // 2 x 2 waves on 128 x BN tiles, buffer loads with hardware zero-fill,
 // register prefetch one k-slice ahead, double-buffered LDS tiles and all
@@ -233,9 +225,6 @@ __device__ __forceinline__ bool tile_geo(const GemmArgsH& a, int tiles_n, int ti
   // shared in-chunk blocks: side 1's full tiles of [0, Cc) x [0, Cc) come
   // from side 0's tiles (tn, tm), transposed
   if (a.share_cc && t.side == 1 && tm < Cc / TM && t.tn < Cc / BN) return false;
-  // merged ranking backward: the dN rows below Cc (rounded down to a 16-row
-  // bit word) are taken by the other side's dQ
-  if (a.merge_cc && a.mdim == DIM_NC) t.m0 += Cc & ~15;
   if (t.m0 >= t.M) return false;
   if (t.n0 >= t.N) {
     const int tid = threadIdx.x;
@@ -846,15 +835,6 @@ __device__ __forceinline__ void score_split_body(const GemmArgsH& a, int tiles_n
   }
 }
 
-// The ranking-bits epilogue keeps register use low enough for three waves per
-// SIMD (a few spill slots, one 16-byte slot in the k loop), which pays for the
-// short k loop of d = 128; the value epilogues spill more and run at two.
-template <int EPI, int NPROD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void score_split_kernel3(
-    GemmArgsH a, int tiles_n, int tiles_m) {
-  score_split_body<EPI, NPROD>(a, tiles_n, tiles_m);
-}
-
 template <int EPI, int NPROD>
 __global__ __launch_bounds__(256) void score_split_kernel(GemmArgsH a, int tiles_n, int tiles_m) {
   score_split_body<EPI, NPROD>(a, tiles_n, tiles_m);
@@ -1061,257 +1041,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_pair_kernel(GemmArgsH a0, int t
   else gemm_bf16_tile<BN, AM1, EPI_STORE, PL>(a1, tn1, tm1, (int)gridDim.x - nwg0, id - nwg0, sm);
 }
 
-// ---- ranking backward with dS as bits: 256-row tiles, B through LDS DMA ---
-// dQ = dS . N (AF = 0: A = dS rows from the bit matrix) and dN = dS^T . Q
-// (AF = 1: A = dS columns) with B as PL bf16 planes [n][k].  A workgroup
-// computes a 256 x BN tile as four waves of 128 x BN/2, so every B fragment
-// read from LDS feeds eight matrix instructions.  dS takes no LDS: each lane
-// loads the bits of its own eight A fragments (16 rows x 8 k each) straight
-// into registers one slice ahead and expands them to 0 / 1 bf16.  B moves
-// global -> LDS without registers (buffer loads with the LDS flag, 16 bytes a
-// lane) into a two-stage ring, so the next slice streams in while this one's
-// matrix instructions run, one barrier per slice.  The products and their
-// order per output element are those of gemm_bf16_tile (k slices in order,
-// planes in order), so the results are identical.
-constexpr int BT = 256;   // rows of a bits-backward tile
-
-template <int BN, int PL>
-struct SmemD {
-  uint16_t Bs[2][PL][BN * BK];
-  uint16_t Ab[2][2 * BT];   // the slice's bit-matrix words (see dma_bits)
-  uint16_t Ab1[2][2 * BT];  // merged dQ rows: the other side's words read by columns
-  float red[2][BT][2];
-  float rowv[2][BT];
-};
-
-// One plane's BN x BK tile of B into LDS at dst: wave w moves rows
-// [16 w + 64 j, +16) for j < BN / 64, lane L the 16-byte group L % 4 of row
-// L / 4 as the swizzle places it (the lane loads logical group
-// (L % 4) ^ f(row)); rows past xdim and k past kdim (rounded to 8) read zeros.
-template <int BN>
-__device__ __forceinline__ void dma_b_tile(uint16_t* dst, rsrc_t rs, int ld, int x0, int xdim, int k0, int kdim,
-                                           int w, int lane) {
-  const int k8 = (kdim + 7) & ~7;
-#pragma unroll
-  for (int j = 0; j < BN / 64; ++j) {
-    const int xr = 16 * w + 64 * j;
-    const int x = xr + (lane >> 2);
-    const int q = (lane & 3) ^ (((x >> 1) ^ ((x >> 3) & 1)) & 3);
-    const int gx = x0 + x, gk = k0 + 8 * q;
-    const uint32_t off = (gx < xdim && gk < k8) ? (uint32_t)(((int64_t)gx * ld + gk) * 2) : OOB;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + xr * BK), 16, off,
-                                             0, 0, 0);
-  }
-}
-
-// The bit-matrix words of one slice (k0 .. k0 + 31) of a 256-row tile, 1 KB,
-// into LDS: each wave moves 256 bytes, four bytes a lane.
-//   AF = 0 (rows of dS): the two word columns k0 / 16, + 1 for rows
-//          m0 .. m0 + 255; wave w: column k0 / 16 + w / 2, rows
-//          m0 + 128 (w % 2) + 2 lane, + 1; LDS word (w / 2) 256 + row
-//   AF = 1 (columns of dS): word columns m0 / 16 .. + 15, rows k0 .. k0 + 31;
-//          wave w: columns 4 w + lane / 16, rows k0 + 2 (lane % 16), + 1;
-//          LDS word 32 column + row
-// The lane's byte offset at k0 = 0 is fixed for the tile (OOB past the
-// matrix); soff moves it to the slice.
-__device__ __forceinline__ void dma_bits(uint16_t* dst, rsrc_t rs, uint32_t off, int soff, int w) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)(dst + 128 * w), 4, off,
-                                           soff, 0, 0);
-}
-
-template <int AF>
-__device__ __forceinline__ uint32_t bits_offset(int ld, int m0, int mdim, int kdim, int k0, int w, int lane) {
-  if (AF == 0) {
-    const int r = m0 + 128 * (w & 1) + 2 * lane;
-    return r < mdim ? (uint32_t)(((int64_t)(w >> 1) * ld + r) * 2) : OOB;
-  }
-  const int wc = (m0 >> 4) + 4 * w + (lane >> 4);
-  const int k = k0 + 2 * (lane & 15);
-  return (16 * wc < mdim && k < kdim) ? (uint32_t)(((int64_t)wc * ld + 2 * (lane & 15)) * 2) : OOB;
-}
-
-// this lane's fragment i of the slice in LDS -> eight bf16 0 / 1 (AF = 0:
-// row 16 i + l16 of the wave's 128, k = 8 g .. + 7; AF = 1: candidate
-// 16 i + l16 of the wave's 128, rows 8 g .. + 7 of the slice, nv of them
-// inside the chunk)
-// AF = 0 looks the fragment's byte up in lut (entry b: the eight bf16 0 / 1
-// of the bits of b, bit 0 first; see fill_bits_lut).
-template <int AF, bool TAIL>
-__device__ __forceinline__ v8bf expand_bits_frag(const uint16_t* ab, const u32x4* lut, int wm, int i, int l16, int g,
-                                                 int nv) {
-  u32x4 v;
-  if (AF == 0) {
-    const uint32_t word = ab[(g >> 1) * 256 + 128 * wm + 16 * i + l16];
-    v = lut[__builtin_amdgcn_ubfe(word, 8 * (g & 1), 8)];
-  } else {
-    v = *(const u32x4*)(ab + (8 * wm + i) * 32 + 8 * g);
-    const int b = l16;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = ((v[q] >> b) & 0x00010001u) * 0x3F80u;
-    if (TAIL && nv < 8) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] &= (2 * q + 1 < nv) ? 0xFFFFFFFFu : (2 * q < nv ? 0xFFFFu : 0u);
-    }
-  }
-  return __builtin_bit_cast(v8bf, v);
-}
-
-// the 256 expansions of a byte of dS bits, one per thread of the workgroup
-__device__ __forceinline__ void fill_bits_lut(u32x4* lut) {
-  const uint32_t b = threadIdx.x;
-  lut[b] = (u32x4){bit_pair(b & 3), bit_pair((b >> 2) & 3), bit_pair((b >> 4) & 3), bit_pair(b >> 6)};
-}
-
-// Merged dQ rows: each element of A is a count c in {0, 1, 2} (the bit of this
-// side's dS row plus the bit of the other side's dS column), whose bf16 value
-// 0, 1.0 (0x3F80) or 2.0 (0x4000) comes out of one byte permute: the selector
-// of an element pair is 0x03000300 + c0 * 0x0101 + c1 * 0x01010000 (low byte
-// c, high byte 3 + c) over the table bytes {00 80 00 | 00 3F 40}.
-constexpr uint32_t kCountLo = 0x00008000u, kCountHi = 0x0000403Fu;
-__device__ __forceinline__ void fill_count_lut(u32x4* lut) {
-  const uint32_t b = threadIdx.x;
-  u32x4 v;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = 0x03000300u + (((((b >> (2 * q)) & 3u) * 0x8001u) & 0x10001u) * 0x0101u);
-  lut[b] = v;
-}
-
-// fragment i of a merged slice: this side's row bits (by byte, from lutc) plus
-// the other side's column bits (AF = 1 layout in ab1, TAIL: only nv of the
-// eight k inside the chunk)
-template <bool TAIL>
-__device__ __forceinline__ v8bf expand_count_frag(const uint16_t* ab, const uint16_t* ab1, const u32x4* lutc, int wm,
-                                                  int i, int l16, int g, int nv) {
-  const uint32_t word = ab[(g >> 1) * 256 + 128 * wm + 16 * i + l16];
-  u32x4 sel = lutc[__builtin_amdgcn_ubfe(word, 8 * (g & 1), 8)];
-  const u32x4 v = *(const u32x4*)(ab1 + (8 * wm + i) * 32 + 8 * g);
-  u32x4 out;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    uint32_t e = ((v[q] >> l16) & 0x00010001u) * 0x0101u;
-    if (TAIL) e &= (2 * q + 1 < nv) ? 0xFFFFFFFFu : (2 * q < nv ? 0xFFFFu : 0u);
-    out[q] = __builtin_amdgcn_perm(kCountHi, kCountLo, sel[q] + e);
-  }
-  return __builtin_bit_cast(v8bf, out);
-}
-
-// MERGE (AF = 0, a.merge_cc): the merged dQ rows described at GemmArgsH; the
-// slices k < Cc take the other side's column bits too (counts, lutc).
-template <int BN, int AF, int PL, bool MERGE>
-__device__ __forceinline__ void gemm_bits_tile(const GemmArgsH& a, int tiles_n, int tiles_m, int nwg, int id,
-                                               SmemD<BN, PL>& sm, u32x4* lut, u32x4* lutc) {
-  constexpr int WN = BN / 2, WMR = BT / 2;
-  constexpr int JN = WN / 16, IM = WMR / 16;
-  TileGeo t;
-  if (!tile_geo<BN, EPI_STORE, BT>(a, tiles_n, tiles_m, nwg, id, t)) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int l16 = lane & 15, g = lane >> 4;
-  const rsrc_t ra = make_rsrc(a.A + t.c * a.a_cs + t.side * a.a_ss);
-  rsrc_t rb[PL];
-#pragma unroll
-  for (int p = 0; p < PL; ++p) rb[p] = make_rsrc(a.B + p * a.b_ps + t.c * a.b_cs + t.side * a.b_ss);
-
-  v4f acc[IM][JN];
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-  const int nk = (t.K + BK - 1) / BK;
-  // bytes per slice of the bit-matrix DMA; the lane's offset is fixed except
-  // in a ragged last slice of the AF = 1 rows
-  const int a_step = AF == 0 ? 4 * a.lda : 2 * BK;
-  uint32_t aoff = bits_offset<AF>(a.lda, t.m0, t.M, t.K, 0, w, lane);
-  if (AF == 0) fill_bits_lut(lut);   // visible after the barrier below
-  if (MERGE) fill_count_lut(lutc);
-  dma_bits(sm.Ab[0], ra, aoff, 0, w);
-  // merged rows: the other side's matrix by columns, rows k < kc = Cc (the dQ
-  // tile's M)
-  const rsrc_t ra1 = MERGE ? make_rsrc(a.A + t.c * a.a_cs + (1 - t.side) * a.a_ss) : ra;
-  const int kc = MERGE ? t.M : 0;
-  const int nk1 = (kc + BK - 1) / BK;
-  uint32_t aoff1 = MERGE ? bits_offset<1>(a.lda, t.m0, t.M, kc, 0, w, lane) : 0;
-  if (MERGE && nk1 > 0) dma_bits(sm.Ab1[0], ra1, aoff1, 0, w);
-#pragma unroll
-  for (int p = 0; p < PL; ++p) dma_b_tile<BN>(sm.Bs[0][p], rb[p], a.ldb, t.n0, t.N, 0, t.K, w, lane);
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads have landed
-  __syncthreads();
-
-  const int fb0 = swz(WN * wn + l16, g);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
-    v8bf af[IM];
-    const int nv = t.K - (kt * BK + 8 * g);
-    // rows of dS past the chunk's edges (AF = 1) are masked in a slice that
-    // reaches them only: the check is uniform, the masks are per lane
-    if (MERGE && kt < nk1) {
-      const int nv1 = kc - (kt * BK + 8 * g);
-      if ((kt + 1) * BK > kc) {
-#pragma unroll
-        for (int i = 0; i < IM; ++i) af[i] = expand_count_frag<true>(sm.Ab[buf], sm.Ab1[buf], lutc, wm, i, l16, g, nv1);
-      } else {
-#pragma unroll
-        for (int i = 0; i < IM; ++i) af[i] = expand_count_frag<false>(sm.Ab[buf], sm.Ab1[buf], lutc, wm, i, l16, g, nv1);
-      }
-    } else if (AF == 1 && (kt + 1) * BK > t.K) {
-#pragma unroll
-      for (int i = 0; i < IM; ++i) af[i] = expand_bits_frag<AF, true>(sm.Ab[buf], lut, wm, i, l16, g, nv);
-    } else {
-#pragma unroll
-      for (int i = 0; i < IM; ++i) af[i] = expand_bits_frag<AF, false>(sm.Ab[buf], lut, wm, i, l16, g, nv);
-    }
-    if (kt + 1 < nk) {
-      if (AF == 1 && kt + 2 == nk) aoff = bits_offset<AF>(a.lda, t.m0, t.M, t.K, (kt + 1) * BK, w, lane);
-      dma_bits(sm.Ab[buf ^ 1], ra, aoff, (kt + 1) * a_step, w);
-      if (MERGE && kt + 1 < nk1) {
-        if (kt + 2 == nk1) aoff1 = bits_offset<1>(a.lda, t.m0, t.M, kc, (kt + 1) * BK, w, lane);
-        dma_bits(sm.Ab1[buf ^ 1], ra1, aoff1, (kt + 1) * 2 * BK, w);
-      }
-#pragma unroll
-      for (int p = 0; p < PL; ++p)
-        dma_b_tile<BN>(sm.Bs[buf ^ 1][p], rb[p], a.ldb, t.n0, t.N, (kt + 1) * BK, t.K, w, lane);
-    }
-#pragma unroll
-    for (int p = 0; p < PL; ++p) {
-      const uint16_t* bs = sm.Bs[buf][p];
-      v8bf bf[JN];
-#pragma unroll
-      for (int j = 0; j < JN; ++j) bf[j] = *(const v8bf*)(bs + fb0 + 16 * j * BK);
-#pragma unroll
-      for (int i = 0; i < IM; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-    }
-    // the matrix instructions issue before the wait, so the loads of the next
-    // slice overlap them; then every wave's loads have landed and every wave
-    // is done with this buffer before it is refilled
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-  }
-  tile_epilogue<BN, EPI_STORE, BT>(a, t, acc, sm.red, sm.rowv);
-}
-
-template <int BN, int PL>
-__global__ __launch_bounds__(256) void gemm_bits_pair_kernel(GemmArgsH a0, int tn0, int tm0, int nwg0,
-                                                             GemmArgsH a1, int tn1, int tm1) {
-  __shared__ __align__(16) SmemD<BN, PL> sm;
-  __shared__ __align__(16) u32x4 lut[256];
-  __shared__ __align__(16) u32x4 lutc[256];
-  static_assert(sizeof(lut) / sizeof(lut[0]) == 256, "one entry per thread");
-  const int id = blockIdx.x;
-  if (id < nwg0) {
-    if (a0.merge_cc) gemm_bits_tile<BN, 0, PL, true>(a0, tn0, tm0, nwg0, id, sm, lut, lutc);
-    else gemm_bits_tile<BN, 0, PL, false>(a0, tn0, tm0, nwg0, id, sm, lut, lutc);
-  } else {
-    gemm_bits_tile<BN, 1, PL, false>(a1, tn1, tm1, (int)gridDim.x - nwg0, id - nwg0, sm, lut, lutc);
-  }
-}
-
 // fp32 rows [rows][ld_src] (columns [d, ld_src) zero) of Q and of N -> bf16
 // rows [rows][ld_dst] (columns up to kp) and the transposed copy [kp][ld_T]
 // (rows [rows, ld_T) zero), both operands in one launch (blockIdx.z < nz0:
@@ -1508,25 +1237,9 @@ void launch_pair_t(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStr
                                                                                  tn1, tm1);
 }
 
-template <int BN, int PL>
-void launch_bits_pair_t(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
-  const int tn0 = (dim_max(a0.ndim, a0.Nfix, a0.C, a0.U) + BN - 1) / BN;
-  const int tm0 = (dim_max(a0.mdim, a0.Mfix, a0.C, a0.U) + BT - 1) / BT;
-  const int tn1 = (dim_max(a1.ndim, a1.Nfix, a1.C, a1.U) + BN - 1) / BN;
-  // merged: dN rows from Cc rounded down to 16, at most U + 15 of them
-  const int rows1 = a1.merge_cc ? a1.U + 15 : dim_max(a1.mdim, a1.Mfix, a1.C, a1.U);
-  const int tm1 = (rows1 + BT - 1) / BT;
-  const int64_t nwg0 = (int64_t)tn0 * tm0 * batches, nwg1 = (int64_t)tn1 * tm1 * batches;
-  gemm_bits_pair_kernel<BN, PL><<<(unsigned)(nwg0 + nwg1), 256, 0, s>>>(a0, tn0, tm0, (int)nwg0, a1, tn1, tm1);
-}
-
 template <int BN>
 void launch_pair_bn(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
-  // three planes (float32 ranking backward): 256-row tiles with B streamed by
-  // LDS DMA (0.226 -> 0.185 ms per social-network step); one plane (bf16
-  // inputs): the 128-row tiles measured faster
-  if (a0.planes == 3) launch_bits_pair_t<BN, 3>(a0, a1, batches, s);
-  else if (a0.amode == GA_BITS_ROW) launch_pair_t<BN, GA_BITS_ROW, GA_BITS_COL, 1>(a0, a1, batches, s);
+  if (a0.amode == GA_BITS_ROW) launch_pair_t<BN, GA_BITS_ROW, GA_BITS_COL, 1>(a0, a1, batches, s);
   else launch_pair_t<BN, GA_KC, GA_MC, 1>(a0, a1, batches, s);
 }
 }  // namespace
@@ -1559,7 +1272,6 @@ void launch_score_split(const GemmArgsH& a, int epi, int batches, hipStream_t s)
   const int tiles_n = (maxN + 127) / 128;   // = nct (PBG_SCORE_BN columns per tile)
   const unsigned nwg = (unsigned)((int64_t)tiles_n * tiles_m * batches);
   if (epi == EPI_LOSS) score_split_kernel<EPI_LOSS, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
-  else if (epi == EPI_LOSS_BITS) score_split_kernel3<EPI_LOSS_BITS, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
   else if (epi == EPI_SOFTMAX_EXP) score_split_kernel<EPI_SOFTMAX_EXP, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
   else score_split_kernel<EPI_STORE, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
 }

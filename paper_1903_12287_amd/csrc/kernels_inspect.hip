@@ -50,6 +50,29 @@ __global__ __launch_bounds__(256) void expand_ds_kernel(StepGeom g, int mode, co
   }
 }
 
+// dL/dS [c][2][C][N] from the ranking bits in 16 x 16 blocks (BitsView)
+__device__ __forceinline__ float bit_of(const uint32_t* p, int RB, int row, int col) {
+  const uint32_t w = p[((int64_t)(col >> 4) * RB + (row >> 4)) * 8 + 4 * ((row >> 3) & 1) + (row & 3)];
+  return (w >> (16 * ((row >> 2) & 1) + (col & 15))) & 1u ? 1.0f : 0.0f;
+}
+
+__global__ __launch_bounds__(256) void expand_bits_kernel(StepGeom g, StepBufs b, float* out) {
+  const int z = blockIdx.z, c = z >> 1, side = z & 1;
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= g.N) return;
+  const int Cc = chunk_edges(g, c);
+  const uint32_t* p = b.bits0 + c * b.bits_cs + side * b.bits_ss;
+  for (int e = blockIdx.y; e < g.C; e += gridDim.y) {
+    float v = 0.0f;
+    if (e < Cc && t < Cc + g.U) {
+      if (!g.dq_has_dn || side == 0) v = bit_of(p, b.bits_rb, e, t);
+      else if (t < Cc) v = bit_of(b.bits1 + c * b.bits1_cs, b.bits_rb, t, e);   // stored transposed
+      else v = bit_of(p, b.bits_rb, e, t - Cc);
+    }
+    out[((int64_t)z * g.C + e) * g.N + t] = v;
+  }
+}
+
 // positive scores [c][C], or [c][2][C] with reciprocal predicates (0 past a
 // short chunk's edges)
 __global__ __launch_bounds__(256) void copy_pos_kernel(StepGeom g, const float* pos, float* out) {
@@ -73,6 +96,12 @@ void launch_expand_ds(const StepGeom& g, int mode, const uint16_t* bits, int nw,
   if (g.nchunks <= 0) return;
   dim3 grid((g.N + 255) / 256, g.C < 4096 ? g.C : 4096, g.nchunks * 2);
   expand_ds_kernel<<<grid, 256, 0, s>>>(g, mode, bits, nw, ldw, f32, scale, h, ld, out);
+}
+
+void launch_expand_bits(const StepGeom& g, const StepBufs& b, float* out, hipStream_t s) {
+  if (g.nchunks <= 0) return;
+  dim3 grid((g.N + 255) / 256, g.C < 4096 ? g.C : 4096, g.nchunks * 2);
+  expand_bits_kernel<<<grid, 256, 0, s>>>(g, b, out);
 }
 
 void launch_copy_pos(const StepGeom& g, const float* pos, float* out, hipStream_t s) {

@@ -11,12 +11,10 @@ static int rup(int v, int m) { return (v + m - 1) / m * m; }
 
 // dQ = dS . N and dN = dS^T . Q on the bf16 matrix instructions.  A is dS:
 // the ranking bit matrix (rows for dQ, columns for dN), else bf16 rows dsh.
-// B is N^T [f][t] / Q^T [f][e] in bf16, as `planes` pieces (1: bf16 operands;
-// 3: the exact pieces of the float32 operands, ranking only) n_ps / q_ps
-// elements apart.
+// B is N^T [f][t] / Q^T [f][e] in bf16.
 static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t* dsh, const uint16_t* nT,
-                           int64_t n_ps, const uint16_t* qT, int64_t q_ps, int64_t q_cs, int64_t q_ss, int q_ld,
-                           int planes, hipStream_t cs, bool merge = false) {
+                           const uint16_t* qT, int64_t q_cs, int64_t q_ss, int q_ld,
+                           hipStream_t cs) {
   const int C = g.C, N = g.N, dp = g.dp, Np = g.Np, nch = g.nchunks;
   const int dpb = rup(g.d, 32), Cpb = rup(C, 32), Npb = rup(N, 32);
   const bool bits = g.loss == LOSS_RANKING;
@@ -38,8 +36,7 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
     qa.lda = Npb;
   }
   qa.B = nT;
-  qa.planes = planes;
-  qa.b_ps = n_ps;
+  qa.planes = 1;
   qa.Cm = b.dq;
   qa.b_cs = 2ll * dpb * Npb;
   qa.b_ss = (int64_t)dpb * Npb;
@@ -60,7 +57,6 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
   GemmArgsH na = qa;
   na.amode = bits ? GA_BITS_COL : GA_MC;
   na.B = qT;
-  na.b_ps = q_ps;
   na.Cm = b.dn;
   na.b_cs = q_cs;
   na.b_ss = q_ss;
@@ -71,8 +67,6 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
   na.kdim = DIM_CC;
   // the relation weight of each chunk scales its gradients (NULL: weight 1)
   qa.cscale = na.cscale = g.cweight;
-  // dN rows e < Cc of side 1 - s into dQ of side s (the same vectors)
-  qa.merge_cc = na.merge_cc = merge ? 1 : 0;
   launch_gemm_bf16_pair(qa, na, nch * 2, cs);
 }
 
@@ -81,8 +75,6 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
 // the loss takes
 static GemmArgsH score_args_f32(const StepGeom& g, const StepBufs& b, int* epi_out) {
   const int C = g.C, U = g.U, N = g.N, dp = g.dp, Np = g.Np;
-  // ranking: dS is 0 or 1 and travels as bits, 16 columns per word
-  const bool bits = g.loss == LOSS_RANKING;
   GemmArgsH fa;
   memset(&fa, 0, sizeof(fa));
   fa.Bf = b.nn;
@@ -122,24 +114,132 @@ static GemmArgsH score_args_f32(const StepGeom& g, const StepBufs& b, int* epi_o
   fa.nct = g.nct;
   fa.loss = g.loss;
   fa.margin = g.margin;
-  const int nw = (Np + 15) / 16, ldw = rup(C, 8);   // bit-matrix words per row, row pitch
-  int epi = g.loss == LOSS_SOFTMAX ? EPI_SOFTMAX_EXP : EPI_LOSS;
-  if (bits) {
-    epi = EPI_LOSS_BITS;
-    fa.dsb = b.dsb;
-    fa.cb_cs = 2ll * nw * ldw;
-    fa.cb_ss = (int64_t)nw * ldw;
-    fa.ldcb = ldw;
-    fa.nwcb = nw;
-  }
+  const int epi = g.loss == LOSS_SOFTMAX ? EPI_SOFTMAX_EXP : EPI_LOSS;
   *epi_out = epi;
   return fa;
+}
+
+// Score contraction on row pieces: operands and per-row inputs
+static ScoreArgs score_args_pieces(const StepGeom& g, const StepBufs& b) {
+  const int64_t C = g.C, N = g.N, ld = g.pld;
+  ScoreArgs a;
+  memset(&a, 0, sizeof(a));
+  a.B = b.pn;
+  a.b_cs = 2 * N * ld;
+  a.b_ss = N * ld;
+  if (QK_IN_NN(g)) {
+    // side s reads the candidate rows of side 1 - s, so the scores of side 1
+    // against the chunk's own candidates are the transposed ones of side 0
+    a.A = b.pn + N * ld;
+    a.a_cs = 2 * N * ld;
+    a.a_ss = -N * ld;
+    a.share = 1;
+  } else {
+    a.A = b.pq;
+    a.a_cs = 2 * C * ld;
+    a.a_ss = C * ld;
+  }
+  a.unscale = 1.0f;
+  a.iunscale = 1.0f;
+  if (g.pieces == PIECES_SCALED) {
+    a.ia = b.pq_is;
+    a.ia_cs = 2 * C;
+    a.ia_ss = C;
+    a.ib = b.pn_is;
+    a.ib_cs = 2 * N;
+    a.ib_ss = N;
+  } else {
+    a.unscale = 0x1p-30f;
+    a.iunscale = 0x1p30f;
+  }
+  a.dh = g.dh;
+  a.ld = g.pld;
+  a.C = g.C;
+  a.U = g.U;
+  a.m_step = g.m_step;
+  a.cstart = g.cstart;
+  a.nsides = 2;
+  a.pos = b.pos;
+  a.pos_sides = g.recip ? 2 : 1;
+  a.bias = (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) ? b.bias : nullptr;
+  a.rowpart = b.rowpart;
+  a.nct = g.nct;
+  a.loss = g.loss;
+  a.margin = g.margin;
+  a.bits0 = b.bits0;
+  a.bits1 = b.bits1;
+  a.bits_cs = b.bits_cs;
+  a.bits_ss = b.bits_ss;
+  a.bits1_cs = b.bits1_cs;
+  a.RB = b.bits_rb;
+  return a;
+}
+
+// Ranking backward on row pieces
+static void run_bits_backward(const StepGeom& g, const StepBufs& b, hipStream_t cs) {
+  const int64_t C = g.C, N = g.N, ld = g.pld;
+  BitsArgs a;
+  memset(&a, 0, sizeof(a));
+  a.N = b.pn;
+  a.n_cs = 2 * N * ld;
+  a.n_ss = N * ld;
+  if (QK_IN_NN(g)) {
+    a.Q = b.pn + N * ld;
+    a.q_cs = 2 * N * ld;
+    a.q_ss = -N * ld;
+  } else {
+    a.Q = b.pq;
+    a.q_cs = 2 * C * ld;
+    a.q_ss = C * ld;
+  }
+  a.dh = g.dh;
+  a.ld = g.pld;
+  a.dp = g.dp;
+  a.bits0 = b.bits0;
+  a.bits1 = b.bits1;
+  a.bits_cs = b.bits_cs;
+  a.bits_ss = b.bits_ss;
+  a.bits1_cs = b.bits1_cs;
+  a.RB = b.bits_rb;
+  a.CB = b.bits_cb;
+  a.CB1 = b.bits_cb1;
+  a.C = g.C;
+  a.U = g.U;
+  a.m_step = g.m_step;
+  a.cstart = g.cstart;
+  a.merged = g.dq_has_dn;
+  a.unscale = 0x1p-1f;   // bits 2^-14, unit rows times 2^15
+  if (g.pieces == PIECES_SCALED) {
+    a.nks = b.nks;
+    a.nks_cs = 2ll * g.ks_n;
+    a.nks_ss = g.ks_n;
+    a.qks = b.qks;
+    a.qks_cs = 2ll * g.ks_q;
+    a.qks_ss = g.ks_q;
+    a.nmax = b.pn_max;
+    a.qmax = b.pq_max;
+  }
+  a.cscale = g.cweight;
+  a.dq = b.dq;
+  a.dn = b.dn;
+  a.dq_cs = 2 * C * g.dp;
+  a.dq_ss = C * g.dp;
+  a.dn_cs = 2 * N * g.dp;
+  a.dn_ss = N * g.dp;
+  launch_bits_backward(a, g.nchunks, cs);
 }
 
 void run_contractions_f32(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, int64_t t, hipStream_t cs,
                           const std::function<void(int)>& mark, bool forward_only) {
   const int C = g.C, U = g.U, N = g.N, dp = g.dp, Np = g.Np, nch = g.nchunks;
-  const bool bits = g.loss == LOSS_RANKING;
+  if (g.pieces != PIECES_NONE) {
+    launch_score(score_args_pieces(g, b), EPI_LOSS_BITS, nch, cs);
+    mark(2);
+    launch_finalize(g, b, ctx->lossparts + t * ctx->lossparts_pps, false, cs);
+    mark(3);
+    if (!forward_only) run_bits_backward(g, b, cs);
+    return;
+  }
   int epi = EPI_LOSS;
   const GemmArgsH fa = score_args_f32(g, b, &epi);
   launch_score_split(fa, epi, nch * 2, cs);
@@ -165,16 +265,6 @@ void run_contractions_f32(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, in
                            (int64_t)dpb * Cpb, h.q3_ps, Cpb, b.nn, (int64_t)N * dp, N, h.nnT3, (int64_t)dpb * Npb,
                            h.n3_ps, Npb, dp, dpb, nch * 2, cs);
   mark(3);
-  if (bits) {
-    // dS is 0 or 1: its products with the pieces are exact (float32 sums)
-    if (qn)
-      run_backward_h(g, b, nullptr, h.nnT3, h.n3_ps, h.nnT3 + (int64_t)dpb * Npb, h.n3_ps, 2ll * dpb * Npb,
-                     -(int64_t)dpb * Npb, Npb, 3, cs, g.dq_has_dn != 0);
-    else
-      run_backward_h(g, b, nullptr, h.nnT3, h.n3_ps, h.qkT3, h.q3_ps, 2ll * dpb * Cpb, (int64_t)dpb * Cpb, Cpb, 3,
-                     cs);
-    return;
-  }
   // general float32 dS (logistic, softmax): split into pieces as it is staged,
   // six piece products
   GemmArgsH qa;
@@ -315,10 +405,9 @@ void run_contractions_bf16(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, i
   if (forward_only) return;
 
   if (qn)
-    run_backward_h(g, b, h.ds, h.nnT, 0, h.nnT + (int64_t)dpb * Npb, 0, 2ll * dpb * Npb, -(int64_t)dpb * Npb, Npb,
-                   1, cs);
+    run_backward_h(g, b, h.ds, h.nnT, h.nnT + (int64_t)dpb * Npb, 2ll * dpb * Npb, -(int64_t)dpb * Npb, Npb, cs);
   else
-    run_backward_h(g, b, h.ds, h.nnT, 0, h.qkT, 0, 2ll * dpb * Cpb, (int64_t)dpb * Cpb, Cpb, 1, cs);
+    run_backward_h(g, b, h.ds, h.nnT, h.qkT, 2ll * dpb * Cpb, (int64_t)dpb * Cpb, Cpb, cs);
 }
 
 // Linear operator with one relation (Sec. 4.3: with a single relation the
@@ -444,6 +533,16 @@ int run_linear_relation_grad(const StepGeom& g, const StepBufs& b, float* partia
 // bias of the source side (translation with dot) is added afterwards, as the
 // epilogues add it.
 void run_score_store(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, float* out, hipStream_t cs) {
+  if (g.pieces != PIECES_NONE) {
+    ScoreArgs a = score_args_pieces(g, b);
+    a.Cm = out;
+    a.c_cs = 2ll * g.C * g.N;
+    a.c_ss = (int64_t)g.C * g.N;
+    a.ldc = g.N;
+    launch_score(a, EPI_STORE, g.nchunks, cs);
+    if (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) launch_add_side_bias(g, b.bias, out, cs);
+    return;
+  }
   GemmArgsH fa;
   if (ctx->flags & PBG_F_BF16_SCORE) {
     fa = score_args_bf16(ctx, g, b);

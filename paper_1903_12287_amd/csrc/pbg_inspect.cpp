@@ -78,7 +78,9 @@ extern "C" pbg_status pbg_inspect_step(pbg_ctx* ctx, int32_t i, int32_t j, const
   if (dscores) {
     const int Np = g.Np, Npb = rup(N, 32);
     const int nw = (Np + 15) / 16, ldw = rup(C, 8);
-    if (ctx->loss == PBG_LOSS_RANKING)
+    if (g.pieces != PIECES_NONE)
+      launch_expand_bits(g, b, dscores, cs);
+    else if (ctx->loss == PBG_LOSS_RANKING)
       launch_expand_ds(g, DS_BITS, b.dsb, nw, ldw, nullptr, nullptr, nullptr, 0, dscores, cs);
     else if (bf16)
       launch_expand_ds(g, DS_BF16, nullptr, 0, 0, nullptr, nullptr, ctx->h.ds, Npb, dscores, cs);

@@ -85,7 +85,7 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
   Arena& a = ctx->ws;
   const int N = C + U;
   const int d = ctx->d, dp = round_up(d, 4), Np = round_up(N, 4);
-  const int nct = (Np + PBG_SCORE_BN - 1) / PBG_SCORE_BN;
+  const int nct = score_tiles(ctx, C, U);
   const int64_t s = S;
   StepBufs& b = ctx->bufs;
   memset(&b, 0, sizeof(b));
@@ -93,14 +93,38 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
   b.nn = (float*)a.get(s * 2 * N * dp * 4);
   b.nrm = (float*)a.get(s * 2 * N * 4);
   const int64_t psides = reciprocal(ctx) ? 2 : 1;   // positive scores per edge
-  b.pos = (float*)a.get(s * psides * C * 4);
-  b.bias = (float*)a.get(s * C * 4);
+  // the score tiles read whole 256-row tiles of per-row values
+  b.pos = (float*)a.get((s * psides * C + 256) * 4);
+  b.bias = (float*)a.get((s * C + 256) * 4);
   b.neg = (int32_t*)a.get(s * 2 * std::max(U, 1) * 4);
   // the ranking loss keeps dS as bits (word-column major, row pitch C rounded
   // up to 8); dS as floats serves the other losses (raw scores for softmax)
   const bool ranking = ctx->loss == PBG_LOSS_RANKING;
   b.ds = ranking ? nullptr : (float*)a.get(s * 2 * C * (int64_t)Np * 4);
-  b.dsb = ranking ? (uint16_t*)a.get(s * 2 * (int64_t)round_up(C, 8) * ((Np + 15) / 16) * 2) : nullptr;
+  const bool pieces = pieces_of(ctx) != PIECES_NONE;
+  b.dsb = ranking && !pieces ? (uint16_t*)a.get(s * 2 * (int64_t)round_up(C, 8) * ((Np + 15) / 16) * 2) : nullptr;
+  if (pieces) {
+    const int64_t pld = round_up(d, 32) * 2;
+    b.pn = (uint16_t*)a.get(s * 2 * N * pld * 2);
+    if (!queries_in_candidates(ctx)) b.pq = (uint16_t*)a.get(s * 2 * C * pld * 2);
+    if (pieces_of(ctx) == PIECES_SCALED) {
+      b.pn_is = (float*)a.get((s * 2 * N + 256) * 4);
+      b.pq_is = (float*)a.get((s * 2 * C + 256) * 4);
+      b.pn_max = (int*)a.get(s * 4 * 4);
+      b.pq_max = b.pn_max ? b.pn_max + s * 2 : nullptr;
+      b.nks = (uint16_t*)a.get(s * 2 * round_up(N, 32) * 2);
+      b.qks = (uint16_t*)a.get(s * 2 * round_up(C, 32) * 2);
+    }
+    const BitsView v = bits_view(C, U);
+    b.bits_rb = v.RB;
+    b.bits_cb = v.CB;
+    b.bits_cb1 = v.CB1;
+    b.bits_ss = (int64_t)v.RB * v.CB * 8;
+    b.bits_cs = 2 * b.bits_ss;
+    b.bits1_cs = (int64_t)v.RB * v.CB1 * 8;
+    b.bits0 = (uint32_t*)a.get(s * b.bits_cs * 4);
+    if (queries_in_candidates(ctx)) b.bits1 = (uint32_t*)a.get(s * b.bits1_cs * 4);
+  }
   b.rowpart = (float*)a.get(s * 2 * C * nct * 2 * 4);
   if (ctx->loss == PBG_LOSS_SOFTMAX) b.rowscale = (float*)a.get(s * 2 * nct * (int64_t)C * 4);
   b.dpos = (float*)a.get(s * psides * C * 4);
@@ -155,7 +179,7 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
     ctx->h.qkT = (uint16_t*)a.get(s * 2 * dpb * Cpb * 2);
     ctx->h.nnT = (uint16_t*)a.get(s * 2 * dpb * Npb * 2);
     if (!ranking) ctx->h.ds = (uint16_t*)a.get(s * 2 * C * (int64_t)Npb * 2);
-  } else {
+  } else if (!pieces) {
     // float32 backward on the bf16 instructions: transposed pieces of Q and N
     const int dpb = round_up(d, 32), Cpb = round_up(C, 32), Npb = round_up(N, 32);
     ctx->h.q3_ps = s * 2 * dpb * (int64_t)Cpb;
@@ -472,7 +496,7 @@ void bucket_geom(const pbg_ctx* ctx, int32_t i, int32_t j, const BucketTables& t
   g.dp = dp;
   g.Np = Np;
   g.dr = ctx->dr;
-  g.nct = (Np + PBG_SCORE_BN - 1) / PBG_SCORE_BN;
+  g.nct = score_tiles(ctx, C, U);
   g.op = ctx->op;
   g.cmp = ctx->cmp;
   g.loss = ctx->loss;
@@ -488,7 +512,12 @@ void bucket_geom(const pbg_ctx* ctx, int32_t i, int32_t j, const BucketTables& t
   g.R = ctx->R;
   g.relN = g.recip ? 2 * C : N;
   g.relsum = single_relation_sums(ctx) ? 1 : 0;
-  g.dq_has_dn = merged_ranking_backward(ctx, g) ? 1 : 0;
+  g.dq_has_dn = merged_ranking_backward(ctx) ? 1 : 0;
+  g.pieces = pieces_of(ctx);
+  g.dh = round_up(d, 8);
+  g.pld = round_up(d, 32) * 2;
+  g.ks_n = round_up(N, 32);
+  g.ks_q = round_up(C, 32);
 }
 
 StepBufs bucket_bufs(pbg_ctx* ctx, const BucketTables& tb) {
@@ -513,6 +542,11 @@ void run_gather_forward(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, hipS
   launch_gather(g, b, cs);
   if (linear1) run_linear_forward(g, b, ctx->relA, ctx->relAT, cs);
   else if (ctx->op == OP_LINEAR) launch_linear_rows(g, b, cs);
+  if (ctx->op == OP_LINEAR) {
+    // the rows those products formed
+    if (QK_IN_NN(g)) launch_candidate_pieces(g, b, cs);
+    else launch_query_pieces(g, b, cs);
+  }
 }
 
 // Runs the step loop on already-validated, device-resident partitions.

@@ -192,10 +192,24 @@ inline bool sorted_relation_keys(const pbg_ctx* ctx) {
 inline bool single_relation_sums(const pbg_ctx* ctx) {
   return ctx->op != PBG_OP_IDENTITY && ctx->op != PBG_OP_LINEAR && !sorted_relation_keys(ctx);
 }
-// The float32 ranking backward with the queries as candidate rows (QK_IN_NN)
-// merges dN rows e < Cc of one side into dQ of the other (kernels.h, merge_cc).
-inline bool merged_ranking_backward(const pbg_ctx* ctx, const StepGeom& g) {
-  return QK_IN_NN(g) && g.loss == LOSS_RANKING && !(ctx->flags & PBG_F_BF16_SCORE);
+// Q and K of a chunk are its candidate rows (QK_IN_NN)
+inline bool queries_in_candidates(const pbg_ctx* ctx) { return ctx->cmp == PBG_CMP_COS && !reciprocal(ctx); }
+// row pieces that the step's contractions take (float32 ranking)
+inline int pieces_of(const pbg_ctx* ctx) {
+  if (ctx->loss != PBG_LOSS_RANKING || (ctx->flags & PBG_F_BF16_SCORE)) return PIECES_NONE;
+  return ctx->cmp == PBG_CMP_COS ? PIECES_UNIT : PIECES_SCALED;
+}
+// The float32 ranking backward with the queries as candidate rows merges dN
+// rows e < Cc of one side into dQ of the other (kernels_bits_backward.hip).
+inline bool merged_ranking_backward(const pbg_ctx* ctx) {
+  return pieces_of(ctx) != PIECES_NONE && queries_in_candidates(ctx);
+}
+// column tiles of a chunk side's row partials (merged: side 1's in-chunk and
+// uniform tiles are counted apart)
+inline int score_tiles(const pbg_ctx* ctx, int C, int U) {
+  const int bn = pieces_of(ctx) != PIECES_NONE ? PBG_PART_BN : PBG_SCORE_BN;
+  if (merged_ranking_backward(ctx)) return (C + bn - 1) / bn + (U + bn - 1) / bn;
+  return ((C + U + 3) / 4 * 4 + bn - 1) / bn;
 }
 // the linear operator as contractions over the whole step (one relation
 // matrix); otherwise one matrix-vector product per edge

@@ -1,0 +1,37 @@
+"""Contractions on row pieces (float32): one step against the oracle at the
+edges of the kernels' tiles: 64-wide wave blocks, 128- and 256-row tiles,
+16-column blocks, 32-deep slices and their remainders."""
+import numpy as np
+import pytest
+
+from oracle import pbg_oracle as O
+from tests.pbg_cases import GpuModel, make_problem, oracle_model
+
+pytestmark = pytest.mark.gpu
+
+# (C, U, edges, d): full and short chunks on both sides of the tile sizes
+# (not d = 1: with cos every gradient is then identically zero and the first
+# Adagrad step follows the sign of a rounding error)
+SHAPES = [(1, 1, 3, 8), (15, 17, 40, 16), (63, 65, 130, 31), (64, 64, 100, 32), (100, 28, 250, 33),
+          (127, 129, 300, 65), (128, 257, 250, 100), (129, 1, 270, 112), (255, 300, 260, 113), (256, 0, 300, 128),
+          (257, 100, 600, 130), (300, 511, 310, 225)]
+
+
+@pytest.mark.parametrize("C,U,m,d", SHAPES)
+@pytest.mark.parametrize("op,cmp", [("translation", "cos"), ("translation", "dot"), ("diagonal", "dot")])
+def test_ranking_step_at_tile_edges(op, cmp, C, U, m, d):
+    """Loss, embeddings and accumulators of one step to 1e-5 (float32 sums
+    over at most a few hundred candidates; the relation parameters' sums of
+    many such rows to 1e-4)."""
+    pb = make_problem(op, cmp, "ranking", R=1 if cmp == "cos" else 3, n=400, m=m, d=d, C=C, U=U, S=4, seed=5)
+    gm = GpuModel(pb)
+    try:
+        gl = gm.train()
+        st = gm.state()
+    finally:
+        gm.close()
+    om = oracle_model(pb)
+    ol = O.train_bucket(om, pb.i, pb.j, pb.src, pb.rel_ids, pb.dst, pb.C, pb.U, pb.S, pb.lr, pb.seed)
+    assert abs(gl - ol) <= 1e-5 * max(1.0, abs(ol))
+    for got, want, rel in ((st["G"][0], om.G[0], 1e-5), (st["emb"][0], om.emb[0], 1e-5), (st["rel"], om.rel, 1e-4)):
+        assert np.max(np.abs(got - want)) <= rel * max(1.0, float(np.max(np.abs(want)))) + 1e-6
