@@ -6,7 +6,7 @@
 #include "kernels.h"
 #include "device_common.h"
 
-// ---- row scales of the ranking backward --------------------------------------
+// ---- row scales of the backward --------------------------------------
 // Every row's fp16 scale relative to the largest row of its (chunk, side) of
 // nn and of qk, 2^(e - e_max + 15), 0 for rows more than 29 binades below it.
 // Each of the chunk's nblk workgroups finds the four largest exponents again
@@ -31,7 +31,16 @@ __device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b,
     int top = tops[0];
     for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) top = max(top, tops[w]);
     if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_max : b.pq_max)[z] = top;
-    uint16_t* ks = nn ? b.nks + (int64_t)z * g.ks_n : b.qks + (int64_t)z * g.ks_q;
+    const int64_t ko = (int64_t)z * (nn ? g.ks_n : g.ks_q);
+    if (g.loss != LOSS_RANKING) {
+      // the other losses take 2^(e - e_max + 15) as float32, zero up to the
+      // end of the last slice (dS is zero there)
+      float* kf = (nn ? b.nkf : b.qkf) + ko;
+      for (int t = blk * FIN_THREADS + threadIdx.x; t < ((rows + 31) & ~31); t += nblk * FIN_THREADS)
+        kf[t] = t < rows ? ldexpf(1.0f, 15 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top) : 0.0f;
+      continue;
+    }
+    uint16_t* ks = (nn ? b.nks : b.qks) + ko;
     for (int t = blk * FIN_THREADS + threadIdx.x; t < rows; t += nblk * FIN_THREADS) {
       const int ex = 30 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top;
       ks[t] = (uint16_t)(ex > 0 ? ex << 10 : 0);
@@ -47,20 +56,20 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
   const int Cc = chunk_edges(g, c);
   double acc = 0.0;
   const int e = blk * FIN_THREADS + threadIdx.x;
-  if (g.pieces == PIECES_SCALED && g.loss == LOSS_RANKING) row_scales(g, b, c, Cc, blk, nblk);
+  if (g.pieces == PIECES_SCALED) row_scales(g, b, c, Cc, blk, nblk);
   if (e < Cc) {
     const int64_t ce = (int64_t)c * g.C + e;
     const float p = b.pos[pos_index(g, c, 0, e)];
     const float p1 = b.pos[pos_index(g, c, 1, e)];   // p itself without reciprocal predicates
     float l0 = 0.f, l1 = 0.f, d0 = 0.f, d1 = 0.f;
+    // column tiles with candidates of this chunk (merged: side 1's in-chunk
+    // tiles, then its uniform ones)
+    const int bn = g.pieces != PIECES_NONE ? PBG_PART_BN : PBG_SCORE_BN;
+    const int n0 = (Cc + g.U + bn - 1) / bn;
+    const int n1 = g.dq_has_dn ? (Cc + bn - 1) / bn + (g.U + bn - 1) / bn : n0;
     if (g.loss != LOSS_SOFTMAX) {
       const float* r0 = b.rowpart + ((int64_t)(c * 2 + 0) * g.C + e) * g.nct * 2;
       const float* r1 = b.rowpart + ((int64_t)(c * 2 + 1) * g.C + e) * g.nct * 2;
-      // column tiles with candidates of this chunk (merged: side 1's in-chunk
-      // tiles, then its uniform ones)
-      const int bn = g.pieces != PIECES_NONE ? PBG_PART_BN : PBG_SCORE_BN;
-      const int n0 = (Cc + g.U + bn - 1) / bn;
-      const int n1 = g.dq_has_dn ? (Cc + bn - 1) / bn + (g.U + bn - 1) / bn : n0;
 #pragma unroll 8
       for (int ct = 0; ct < n0; ++ct) {
         const float2 a0 = *(const float2*)(r0 + 2 * ct);
@@ -95,16 +104,16 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
         } else {
           const float* rp = b.rowpart + ((int64_t)(c * 2 + side) * g.C + e) * g.nct * 2;
           float M = pp;
-          for (int ct = 0; ct < g.nct; ++ct) M = fmaxf(M, rp[2 * ct]);
+          for (int ct = 0; ct < n0; ++ct) M = fmaxf(M, rp[2 * ct]);
           float Z = expf(pp - M);
-          for (int ct = 0; ct < g.nct; ++ct) {
+          for (int ct = 0; ct < n0; ++ct) {
             const float mx = rp[2 * ct];
             if (mx > -INFINITY) Z += rp[2 * ct + 1] * expf(mx - M);
           }
           const float lse = M + logf(Z);
           if (softmax_scales) {
             float* rs = b.rowscale + (int64_t)(c * 2 + side) * g.nct * g.C + e;
-            for (int ct = 0; ct < g.nct; ++ct) {
+            for (int ct = 0; ct < n0; ++ct) {
               const float mx = rp[2 * ct];
               rs[(int64_t)ct * g.C] = mx > -INFINITY ? expf(mx - lse) : 0.0f;
             }
@@ -139,16 +148,16 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
       for (int side = 0; side < 2; ++side) {
         const float* rp = b.rowpart + ((int64_t)(c * 2 + side) * g.C + e) * g.nct * 2;
         float M = p;
-        for (int ct = 0; ct < g.nct; ++ct) M = fmaxf(M, rp[2 * ct]);
+        for (int ct = 0; ct < n0; ++ct) M = fmaxf(M, rp[2 * ct]);
         float Z = expf(p - M);
-        for (int ct = 0; ct < g.nct; ++ct) {
+        for (int ct = 0; ct < n0; ++ct) {
           const float mx = rp[2 * ct];
           if (mx > -INFINITY) Z += rp[2 * ct + 1] * expf(mx - M);
         }
         lse[side] = M + logf(Z);
         if (softmax_scales) {
           float* rs = b.rowscale + (int64_t)(c * 2 + side) * g.nct * g.C + e;
-          for (int ct = 0; ct < g.nct; ++ct) {
+          for (int ct = 0; ct < n0; ++ct) {
             const float mx = rp[2 * ct];
             rs[(int64_t)ct * g.C] = mx > -INFINITY ? expf(mx - lse[side]) : 0.0f;
           }

@@ -37,9 +37,6 @@ enum { LOSS_RANKING = 0, LOSS_LOGISTIC = 1, LOSS_SOFTMAX = 2 };
 #define PBG_EPS_ADAGRAD 1e-10f
 #define PBG_SCORE_BN 128  // column tile of the score contraction
 #define PBG_PART_BN 64    // columns of a row partial of the score contraction on row pieces
-// row tile of the score contraction on row pieces: 256, or 128 where a chunk
-// holds no more edges
-__host__ __device__ inline int score_rows(int C) { return C <= 128 ? 128 : 256; }
 
 // Row pieces of the packed rows (pieces.h) that the gather writes beside them
 enum { PIECES_NONE = 0, PIECES_UNIT = 1, PIECES_SCALED = 2 };
@@ -137,6 +134,8 @@ struct StepBufs {
   int* pq_max;          // [S][2]
   uint16_t* nks;        // [S][2][ks_n]
   uint16_t* qks;        // [S][2][ks_q]
+  float* nkf;           // the same for the logistic and softmax losses, as float32
+  float* qkf;
   float* pos;           // [S][C] positive scores ([S][2][C] with reciprocal predicates)
   float* bias;          // [S][C] <theta_r, x_d> (translation + dot)
   int32_t* neg;         // [S][2][U] uniform draws (side 0 from partition j, side 1 from i)

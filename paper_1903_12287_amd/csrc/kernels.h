@@ -48,8 +48,6 @@ struct GemmArgsH {
   int64_t b_ps;
   const float* Af;       // launch_score_split: float32 operands [m][k] and [n][k]
   const float* Bf;
-  const float* smscale;  // launch_gemm_split_pair: Af holds exp(s - tile max) of the softmax loss and
-                         // smscale[(z * nct + tile) * C + row] = exp(tile max - lse) (z = chunk*2 + side)
   float* Cm;             // fp32 output (STORE, SOFTMAX_STATS)
   uint16_t* dsh;         // EPI_LOSS: dS rows in bf16 (strides c_*, ldc)
   uint16_t* dsb;         // EPI_LOSS_BITS output (as in GemmArgs)
@@ -71,25 +69,14 @@ struct GemmArgsH {
   int loss;
   float margin;
   const float* cscale;   // EPI_STORE: output of chunk c times cscale[c] (NULL: as is)
-  int share_cc;          // launch_score_split with Q of each side the first C candidate rows of the
-                         // other: the in-chunk block of side 1 is the transpose of side 0's, and side 0's
-                         // full tiles inside it produce side 1's too
 };
 
 // bf16-input score contraction with a loss epilogue (EPI_LOSS, EPI_LOSS_BITS or
 // EPI_SOFTMAX_STATS) or the plain store (EPI_STORE: float32 scores to Cm)
 void launch_gemm_bf16(const GemmArgsH& a, int epi, int batches, hipStream_t s);
-// float32 score contraction with its loss epilogue (EPI_LOSS: float32 dS in
-// Cm; EPI_LOSS_BITS; EPI_SOFTMAX_STATS) on the bf16 instructions, operands
+// float32 product S = A . B^T (EPI_STORE) on the bf16 instructions, operands
 // Af / Bf split into exact bf16 pieces on the way into LDS
 void launch_score_split(const GemmArgsH& a, int epi, int batches, hipStream_t s);
-// dQ = dS . N (a0: Af = dS rows [e][t]) and dN = dS^T . Q (a1: Af = the same
-// dS rows, read by columns) in one launch, dS a general float32 matrix split
-// into exact bf16 pieces on the way into LDS, B the three transposed planes
-// of N / Q (planes = 3, b_ps apart); six piece products.  With smscale set,
-// Af holds the per-tile exponentials of the softmax loss and dS is formed on
-// the way
-void launch_gemm_split_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s);
 // two EPI_STORE products in one launch: a0 with A as dS rows (GA_BITS_ROW or
 // GA_KC), a1 with A as dS columns (GA_BITS_COL or GA_MC), same planes
 void launch_gemm_bf16_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s);
@@ -100,19 +87,6 @@ void launch_to_bf16_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qh, in
                       int64_t qT_bs, int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nh,
                       int64_t nh_bs, uint16_t* nT, int64_t nT_bs, int n_ldT, int ld_src, int kp, int batches,
                       hipStream_t s);
-// fp32 rows [rows][ld_src] of Q and of N -> the exact bf16 pieces
-// x = h + m + l as three transposed planes [kp][ld_T] each (ps elements
-// apart, rows past `rows` up to ld_T zero), both operands in one launch.
-// ld_src is a multiple of 4, ld_T of 8.  q = nullptr: N only.
-// launch_finalize and launch_split3_t (same arguments) as one launch
-void launch_finalize_split3_t(const StepGeom& g, const StepBufs& b, double* parts, bool softmax_scales,
-                              const float* q, int64_t q_bs, int q_rows, uint16_t* qT, int64_t qT_bs, int64_t q_ps,
-                              int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nT, int64_t nT_bs,
-                              int64_t n_ps, int n_ldT, int ld_src, int kp, int batches, hipStream_t s);
-void launch_split3_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qT, int64_t qT_bs, int64_t q_ps,
-                     int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nT, int64_t nT_bs,
-                     int64_t n_ps, int n_ldT, int ld_src, int kp, int batches, hipStream_t s);
-
 // ---- contractions on row pieces (pieces.h) ---------------------------------------
 // The ranking loss keeps dS (0 or 1) as bits, in 16 x 16 blocks of eight
 // 32-bit words [half][r], r = 0..3: the low and high 16 bits of word (half, r)
@@ -156,8 +130,8 @@ struct ScoreArgs {
   uint32_t *bits0, *bits1;
   int64_t bits_cs, bits_ss, bits1_cs;   // words
   int RB;
-  float* Cm;                    // float32 scores (EPI_STORE)
-  int64_t c_cs, c_ss;
+  float* Cm;                    // float32 scores (EPI_STORE), dS (EPI_LOSS) or exp(s - block maximum)
+  int64_t c_cs, c_ss;           // (EPI_SOFTMAX_EXP)
   int ldc;
 };
 void launch_score(const ScoreArgs& a, int epi, int nchunks, hipStream_t s);
@@ -183,6 +157,26 @@ struct BitsArgs {
   int64_t dq_cs, dq_ss, dn_cs, dn_ss;
 };
 void launch_bits_backward(const BitsArgs& a, int nchunks, hipStream_t s);
+// dQ = dS . N and dN = dS^T . Q of the logistic and softmax losses from the
+// float32 dS rows (softmax: exp(s - M) per 64-column block, times rowscale)
+struct ValueArgs {
+  const float* ds;              // [c][2][C][lds]
+  int lds;
+  const float* rowscale;        // [c][2][nct][C] (softmax), else NULL
+  int nct;
+  const uint16_t *N, *Q;
+  int64_t n_cs, n_ss, q_cs, q_ss;
+  int dh, ld, dp;
+  int C, U, m_step;
+  const int32_t* cstart;
+  const float *nkf, *qkf;       // [c][2][ks_n / ks_q] 2^15 times each row's scale relative to the largest
+  int ks_n, ks_q;               // (NULL: unit rows)
+  const int *nmax, *qmax;
+  const float* cscale;
+  float *dq, *dn;
+  int64_t dq_cs, dq_ss, dn_cs, dn_ss;
+};
+void launch_value_backward(const ValueArgs& a, int nchunks, hipStream_t s);
 // planes of the queries (qk) of both sides, or of side 1's candidates (nn):
 // the rows that the linear operator's products leave behind the gather
 void launch_query_pieces(const StepGeom& g, const StepBufs& b, hipStream_t s);

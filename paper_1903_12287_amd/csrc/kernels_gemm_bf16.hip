@@ -28,7 +28,6 @@
 
 #include "kernels.h"
 #include "device_common.h"
-#include "finalize_body.h"
 
 namespace {
 
@@ -222,15 +221,12 @@ __device__ __forceinline__ bool tile_geo(const GemmArgsH& a, int tiles_n, int ti
   t.K = pick_dim(a.kdim, a.Kfix, Cc, t.Nc);
   t.m0 = tm * TM;
   t.n0 = t.tn * BN;
-  // shared in-chunk blocks: side 1's full tiles of [0, Cc) x [0, Cc) come
-  // from side 0's tiles (tn, tm), transposed
-  if (a.share_cc && t.side == 1 && tm < Cc / TM && t.tn < Cc / BN) return false;
   if (t.m0 >= t.M) return false;
   if (t.n0 >= t.N) {
     const int tid = threadIdx.x;
     if (EPI != EPI_STORE && tid < TM && t.m0 + tid < t.M) {
       float* rp = a.rowpart + (((int64_t)(t.c * 2 + t.side) * a.C + t.m0 + tid) * a.nct + t.tn) * 2;
-      rp[0] = (EPI == EPI_SOFTMAX_STATS || EPI == EPI_SOFTMAX_EXP) ? -INFINITY : 0.0f;
+      rp[0] = EPI == EPI_SOFTMAX_STATS ? -INFINITY : 0.0f;
       rp[1] = 0.0f;
     }
     return false;
@@ -400,63 +396,6 @@ __device__ __forceinline__ void value_rows(const GemmArgsH& a, const TileGeo& t,
     }
 }
 
-// Softmax rows of a tile for the backward on split pieces: the tile's row
-// maximum M over the valid columns (both column halves), then exp(s - M) on
-// the valid columns and 0 elsewhere (columns past the batch, the diagonal)
-// goes to Cm and its row sum to the partials.  dS = exp(s - M) exp(M - lse)
-// is completed in the backward once lse is known.
-template <int BN, bool MASKED, int TM = BM>
-__device__ __forceinline__ void softmax_exp_rows(const GemmArgsH& a, const TileGeo& t,
-                                                 v4f (&acc)[TM / 32][BN / 32], float (&red)[2][TM][2],
-                                                 const float (&rowv)[2][TM]) {
-  constexpr int WN = BN / 2, WMR = TM / 2;
-  constexpr int JN = WN / 16, IM = TM / 32;
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int l16 = lane & 15, g = lane >> 4;
-  const int M = t.M, N = t.N, m0 = t.m0;
-  const int colb = t.n0 + WN * wn + l16;
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ml = WMR * wm + 16 * i + 4 * g + r;
-      const int m = m0 + ml;
-      const float bm = rowv[1][ml];
-      float mx = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const int n = colb + 16 * j;
-        acc[i][j][r] += bm;
-        if (m < M && !(MASKED && (n >= N || n == m))) mx = fmaxf(mx, acc[i][j][r]);
-      }
-      mx = group16_max(mx);
-      if (l16 == 0) red[wn][ml][0] = mx;
-    }
-  __syncthreads();
-  float* Cm = a.Cm + t.c * a.c_cs + t.side * a.c_ss;
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ml = WMR * wm + 16 * i + 4 * g + r;
-      const int m = m0 + ml;
-      const float mt = fmaxf(red[0][ml][0], red[1][ml][0]);
-      float se = 0.0f;
-#pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const int n = colb + 16 * j;
-        const bool valid = m < M && !(MASKED && (n >= N || n == m));
-        const float ev = valid ? expf(acc[i][j][r] - mt) : 0.0f;
-        se += ev;
-        if (m < M && n < a.ldc) Cm[(int64_t)m * a.ldc + n] = ev;
-      }
-      se = group16_sum(se);
-      if (l16 == 0) red[wn][ml][1] = se;
-    }
-}
-
 // Stores the tile (EPI_STORE) or runs the loss epilogue on it: dS leaves as
 // bits (ranking), as bf16 rows (logistic, when dsh is set) or float32 rows in
 // Cm, or the raw float32 scores go to Cm for the softmax row pass; row
@@ -501,9 +440,6 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgsH& a, const TileGeo&
   if (EPI == EPI_LOSS_BITS) {
     if (masked) bits_rows<BN, true, TM>(a, t, acc, red, rowv);
     else bits_rows<BN, false, TM>(a, t, acc, red, rowv);
-  } else if (EPI == EPI_SOFTMAX_EXP) {
-    if (masked) softmax_exp_rows<BN, true, TM>(a, t, acc, red, rowv);
-    else softmax_exp_rows<BN, false, TM>(a, t, acc, red, rowv);
   } else {
     if (masked) value_rows<BN, EPI, true, TM>(a, t, acc, red, rowv);
     else value_rows<BN, EPI, false, TM>(a, t, acc, red, rowv);
@@ -514,9 +450,6 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgsH& a, const TileGeo&
     float v0, v1;
     if (EPI == EPI_LOSS || EPI == EPI_LOSS_BITS) {
       v0 = red[0][ml][0] + red[1][ml][0];
-      v1 = red[0][ml][1] + red[1][ml][1];
-    } else if (EPI == EPI_SOFTMAX_EXP) {
-      v0 = fmaxf(red[0][ml][0], red[1][ml][0]);
       v1 = red[0][ml][1] + red[1][ml][1];
     } else {
       const float ma = red[0][ml][0], mb = red[1][ml][0];
@@ -532,42 +465,6 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgsH& a, const TileGeo&
   }
 }
 
-
-// The 128 x 128 tile held as four 64 x 64 wave blocks in the matrix-instruction
-// layout (acc[i][j][r] is row 16 i + 4 g + r, column 16 j + l16 of the block of
-// wave (wm, wn)) becomes its transpose: wave (wm, wn) ends with block (wn, wm)
-// transposed.  The two off-diagonal waves swap through LDS first, then the two
-// diagonal ones transpose in place; a block passes through a [64][68] float32
-// slot (rows padded so that the 4-byte writes and 16-byte reads meet distinct
-// banks).  L: kTransposeFloats floats.  Every wave of the workgroup calls it.
-constexpr int kTransposeLd = 68;
-constexpr int kTransposeFloats = 2 * 64 * kTransposeLd;
-__device__ __forceinline__ void transpose_tile(v4f (&acc)[4][4], float* L, int wm, int wn, int l16, int g) {
-  constexpr int LD = kTransposeLd;
-  const bool off = wm != wn;
-#pragma unroll
-  for (int phase = 0; phase < 2; ++phase) {
-    const bool mine = (phase == 0) == off;
-    if (mine) {
-      float* s = L + wm * 64 * LD;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) s[(16 * i + 4 * g + r) * LD + 16 * j + l16] = acc[i][j][r];
-    }
-    __syncthreads();
-    if (mine) {
-      const float* s = L + wn * 64 * LD;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = *(const v4f*)(s + (16 * j + l16) * LD + 16 * i + 4 * g);
-    }
-    __syncthreads();
-  }
-}
 
 // One 128 x BN output tile of A . B with bf16 operands (B in PL planes).
 template <int BN, int AMODE, int EPI, int PL>
@@ -740,7 +637,6 @@ struct SmemST {
   uint16_t Bs[3][128 * BK];
   float red[2][TM][2];
   float rowv[2][TM];
-  float rowv1[2][TM];
 };
 using SmemS = SmemST<BM>;
 
@@ -751,7 +647,6 @@ template <int EPI, int NPROD>
 __device__ __forceinline__ void score_split_body(const GemmArgsH& a, int tiles_n, int tiles_m) {
   constexpr int BN = 128, WN = 64, JN = 4, WMR = BM / 2, IM = BM / 32;
   __shared__ __align__(16) SmemS sm;
-  static_assert(sizeof(sm.As) + sizeof(sm.Bs) >= kTransposeFloats * sizeof(float), "transpose slots");
   TileGeo t;
   if (!tile_geo<BN, EPI>(a, tiles_n, tiles_m, gridDim.x, blockIdx.x, t)) return;
   if (EPI != EPI_STORE) load_rowv<EPI>(a, t, sm.rowv);
@@ -816,211 +711,12 @@ __device__ __forceinline__ void score_split_body(const GemmArgsH& a, int tiles_n
       __syncthreads();
     }
   }
-  // a full side-0 tile inside the in-chunk block also gives side 1's tile
-  // (tm, tn) -> (tn, tm), its transpose (M = the chunk's edges here): a second
-  // pass of the same epilogue on the transposed accumulators
-  const bool shared = a.share_cc && t.side == 0 && t.m0 / BM < t.M / BM && t.tn < t.M / BN;
-  for (int pass = 0; pass < (shared ? 2 : 1); ++pass) {
-    if (pass == 1) {
-      t.side = 1;
-      const int m0 = t.m0;
-      t.m0 = t.n0;
-      t.n0 = m0;
-      t.tn = m0 / BN;
-      if (EPI != EPI_STORE) load_rowv<EPI>(a, t, sm.rowv1);   // visible after the transpose's barriers
-      // every wave is past the first pass's barrier, so past its last reads of the planes
-      transpose_tile(acc, reinterpret_cast<float*>(&sm.As[0][0]), wm, wn, l16, g);
-    }
-    tile_epilogue<BN, EPI>(a, t, acc, sm.red, pass ? sm.rowv1 : sm.rowv);
-  }
+  tile_epilogue<BN, EPI>(a, t, acc, sm.red, sm.rowv);
 }
 
 template <int EPI, int NPROD>
 __global__ __launch_bounds__(256) void score_split_kernel(GemmArgsH a, int tiles_n, int tiles_m) {
   score_split_body<EPI, NPROD>(a, tiles_n, tiles_m);
-}
-
-// ---- float32 backward products of a general dS on the bf16 instructions ----
-// dQ = dS . N and dN = dS^T . Q for the logistic and softmax losses: dS is
-// float32, so it is split into its three pieces on the way into LDS like the
-// score operands, B comes as the three transposed planes of N or Q, and the
-// six products hh, hm, mh, hl, mm, lh are summed (as in the score).
-
-// TX rows (m) x 32 k of a float32 [k][m] matrix (m contiguous, ld floats):
-// each thread loads two consecutive k rows of four consecutive m, splits the
-// pairs (k, k + 1) of each m and stores them as one 32-bit word per plane
-// into the [m][k] tile.
-template <int TX>
-struct TileSM {
-  static constexpr int LOADS = TX * BK / 8 / 256;   // (k pair, m quad) per thread
-
-  __device__ __forceinline__ static void load(v4f* r, rsrc_t rs, int ld, int x0, int xdim, int k0, int kdim,
-                                              int tid) {
-    const int x4 = (xdim + 3) & ~3;
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      const int f = tid + 256 * q;
-      const int kp = f / (TX / 4), xq = f % (TX / 4);
-      const int gk = k0 + 2 * kp, gx = x0 + 4 * xq;
-      uint32_t o0 = OOB, o1 = OOB;
-      if (gx < x4) {
-        if (gk < kdim) o0 = (uint32_t)(((int64_t)gk * ld + gx) * 4);
-        if (gk + 1 < kdim) o1 = (uint32_t)(((int64_t)(gk + 1) * ld + gx) * 4);
-      }
-      r[2 * q] = __builtin_amdgcn_raw_buffer_load_b128(rs, o0, 0, 0);
-      r[2 * q + 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o1, 0, 0);
-    }
-  }
-
-  __device__ __forceinline__ static void store(uint16_t (*s)[TX * BK], const v4f* r, int tid) {
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      const int f = tid + 256 * q;
-      const int kp = f / (TX / 4), xq = f % (TX / 4);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t pc[3];
-        split3_pair(r[2 * q][i], r[2 * q + 1][i], pc);
-        const int o = swz(4 * xq + i, kp >> 2) + ((2 * kp) & 7);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) *(uint32_t*)(s[p] + o) = pc[p];
-      }
-    }
-  }
-};
-
-// One 128 x 128 output tile of dS . B (AF = 0: dS rows, A = dS [m][k]) or
-// dS^T . B (AF = 1: A[m][k] = dS[k][m]); one LDS buffer.  SM: softmax, dS is
-// formed as A is staged, dS[e][t] = exp(s[e][t] - lse[e]) on the valid
-// candidates t (t < Nc, t != e) of the valid rows e (e < Cc), else 0: the A
-// source holds exp(s - M) per score tile (0 off the valid set) and each row
-// is scaled by exp(M - lse) of its tile.
-template <int AF, bool SM>
-__device__ __forceinline__ void gemm_split_tile(const GemmArgsH& a, int tiles_n, int tiles_m, int nwg, int id,
-                                                SmemS& sm) {
-  constexpr int BN = 128, WN = 64, JN = 4;
-  using TB = TileH<BN, GA_KC>;
-  TileGeo t;
-  if (!tile_geo<BN, EPI_STORE>(a, tiles_n, tiles_m, nwg, id, t)) return;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int l16 = lane & 15, g = lane >> 4;
-  const rsrc_t ra = make_rsrc(a.Af + t.c * a.a_cs + t.side * a.a_ss);
-  rsrc_t rb[3];
-#pragma unroll
-  for (int p = 0; p < 3; ++p) rb[p] = make_rsrc(a.B + p * a.b_ps + t.c * a.b_cs + t.side * a.b_ss);
-  v4f acc[4][JN];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-  constexpr int AQ = AF == 0 ? TileS<BM>::LOADS : TileSM<BM>::LOADS;   // A groups per thread
-  v4f pa[2 * AQ];
-  u32x4 pb[3][TB::LOADS];
-  // softmax: the scale exp(M - lse) of this thread's rows in the score tile
-  // of the staged slice (AF = 0: one row per group, the tile of the slice's
-  // columns, reloaded when the slice enters a new tile; AF = 1: two rows per
-  // group, the tile of this output tile's rows)
-  static_assert(BM == PBG_SCORE_BN && BK <= PBG_SCORE_BN, "slices and tiles within one score tile");
-  const int Cc = AF == 0 ? t.M : t.K;
-  const float* rsc = SM ? a.smscale + (int64_t)(t.c * 2 + t.side) * a.nct * a.C : nullptr;
-  float lr[2 * AQ];
-  const int nk = (t.K + BK - 1) / BK;
-  auto load_a = [&](int k0) {
-    if (AF == 0) {
-      TileS<BM>::load(pa, ra, a.lda, t.m0, t.M, k0, t.K, tid);
-      if (SM && (k0 & 127) == 0) {
-        const float* rc = rsc + (int64_t)(k0 >> 7) * a.C;
-#pragma unroll
-        for (int q = 0; q < AQ; ++q) {
-          const int e = t.m0 + ((tid + 256 * q) >> 2);
-          lr[q] = e < Cc ? rc[e] : 0.0f;
-        }
-      }
-    } else {
-      TileSM<BM>::load(pa, ra, a.lda, t.m0, t.M, k0, t.K, tid);
-      if (SM) {
-        const float* rc = rsc + (int64_t)(t.m0 >> 7) * a.C;
-#pragma unroll
-        for (int q = 0; q < AQ; ++q) {
-          const int e = k0 + 2 * ((tid + 256 * q) / (BM / 4));
-          lr[2 * q] = e < Cc ? rc[e] : 0.0f;
-          lr[2 * q + 1] = e + 1 < Cc ? rc[e + 1] : 0.0f;
-        }
-      }
-    }
-  };
-  auto softmax_a = [&]() {
-#pragma unroll
-    for (int q = 0; q < AQ; ++q) {
-      if (AF == 0) {
-        pa[2 * q] *= lr[q];
-        pa[2 * q + 1] *= lr[q];
-      } else {
-        pa[2 * q] *= lr[2 * q];
-        pa[2 * q + 1] *= lr[2 * q + 1];
-      }
-    }
-  };
-  auto store_a = [&]() {
-    if (SM) softmax_a();
-    if (AF == 0) TileS<BM>::store(sm.As, pa, tid);
-    else TileSM<BM>::store(sm.As, pa, tid);
-  };
-  load_a(0);
-#pragma unroll
-  for (int p = 0; p < 3; ++p) TB::load(pb[p], rb[p], a.ldb, t.n0, t.N, 0, t.K, tid);
-  store_a();
-#pragma unroll
-  for (int p = 0; p < 3; ++p) TB::store(sm.Bs[p], pb[p], tid, 0, 0, 0);
-  __syncthreads();
-
-  const int fa0 = swz(64 * wm + l16, g), fb0 = swz(WN * wn + l16, g);
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) {
-      load_a((kt + 1) * BK);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) TB::load(pb[p], rb[p], a.ldb, t.n0, t.N, (kt + 1) * BK, t.K, tid);
-    }
-#pragma unroll
-    for (int pa_ = 0; pa_ < 3; ++pa_) {
-      v8bf af[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) af[i] = *(const v8bf*)(sm.As[pa_] + fa0 + 16 * i * BK);
-#pragma unroll
-      for (int pb_ = 0; pb_ < 3 - pa_; ++pb_) {
-        v8bf bf[JN];
-#pragma unroll
-        for (int j = 0; j < JN; ++j) bf[j] = *(const v8bf*)(sm.Bs[pb_] + fb0 + 16 * j * BK);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < JN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-      }
-    }
-    if (kt + 1 < nk) {
-      __syncthreads();
-      store_a();
-#pragma unroll
-      for (int p = 0; p < 3; ++p) TB::store(sm.Bs[p], pb[p], tid, 0, 0, 0);
-      __syncthreads();
-    }
-  }
-  tile_epilogue<BN, EPI_STORE>(a, t, acc, sm.red, sm.rowv);
-}
-
-// dQ (workgroups [0, nwg0)) and dN (the rest) of a step in one launch
-template <bool SM>
-__global__ __launch_bounds__(256) void gemm_split_pair_kernel(GemmArgsH a0, int tn0, int tm0, int nwg0,
-                                                              GemmArgsH a1, int tn1, int tm1) {
-  __shared__ __align__(16) SmemS sm;
-  const int id = blockIdx.x;
-  if (id < nwg0) gemm_split_tile<0, SM>(a0, tn0, tm0, nwg0, id, sm);
-  else gemm_split_tile<1, SM>(a1, tn1, tm1, (int)gridDim.x - nwg0, id - nwg0, sm);
 }
 
 template <int BN, int AMODE, int EPI, int PL>
@@ -1093,82 +789,6 @@ __global__ __launch_bounds__(256) void to_bf16_t_kernel(Bf16T o0, Bf16T o1, int 
     for (int i = 0; i < 4; ++i) w[i] = (uint32_t)tile[r8 + 2 * i][kk] | ((uint32_t)tile[r8 + 2 * i + 1][kk] << 16);
     *(u32x4*)(dT + (int64_t)k * o.ld_T + r) = (u32x4){w[0], w[1], w[2], w[3]};
   }
-}
-
-// fp32 rows [rows][ld_src] (columns [d, ld_src) zero) -> the three exact
-// bf16 pieces (split3_pair) of every element, transposed: planes [kp][ld_T],
-// ps elements apart, rows [rows, rows_p) and columns past ld_src zero.  Two
-// operands in one launch (blockIdx.z < nz0: the first).  64 x 64 tiles: each
-// thread loads 16-byte groups into an LDS tile, then gathers eight
-// consecutive rows of one column and writes 16 bytes per plane (eight lanes
-// cover 64 rows of a plane row).  ld_src is a multiple of 4, rows_p and ld_T
-// of 8.
-struct Split3T {
-  const float* src;
-  int64_t src_bs;
-  int rows, ld_src;
-  uint16_t* dst;
-  int64_t dst_bs, ps;
-  int ld_T, rows_p;
-};
-
-// workgroup (bx, by, bz) of the split's grid
-__device__ __forceinline__ void split3_t_block(const Split3T& o0, const Split3T& o1, int nz0, int kp, int bx, int by,
-                                               int bz) {
-  __shared__ float tile[64][65];
-  const bool first = bz < nz0;
-  const Split3T& o = first ? o0 : o1;
-  const int b = first ? bz : bz - nz0;
-  const int r0 = by * 64, k0 = bx * 64;
-  if (r0 >= o.rows_p) return;
-  const float* s = o.src + (int64_t)b * o.src_bs;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int it = threadIdx.x + 256 * j;
-    const int rr = it >> 4, k4 = 4 * (it & 15);
-    const int r = r0 + rr, k = k0 + k4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < o.rows && k < o.ld_src) v = *(const float4*)(s + (int64_t)r * o.ld_src + k);
-    tile[rr][k4] = v.x;
-    tile[rr][k4 + 1] = v.y;
-    tile[rr][k4 + 2] = v.z;
-    tile[rr][k4 + 3] = v.w;
-  }
-  __syncthreads();
-  uint16_t* dst = o.dst + (int64_t)b * o.dst_bs;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int it = threadIdx.x + 256 * j;
-    const int kk = it >> 3, r8 = 8 * (it & 7);
-    const int k = k0 + kk, r = r0 + r8;
-    if (k >= kp || r >= o.rows_p) continue;
-    uint32_t pc[4][3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split3_pair(tile[r8 + 2 * i][kk], tile[r8 + 2 * i + 1][kk], pc[i]);
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      *(u32x4*)(dst + p * o.ps + (int64_t)k * o.ld_T + r) = (u32x4){pc[0][p], pc[1][p], pc[2][p], pc[3][p]};
-  }
-}
-
-__global__ __launch_bounds__(256) void split3_t_kernel(Split3T o0, Split3T o1, int nz0, int kp) {
-  split3_t_block(o0, o1, nz0, kp, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-// The finalisation (nfin = fb x nchunks workgroups first) and the transposed
-// piece split (gx x gy x gz workgroups after them) in one launch: the split
-// reads only the candidate rows, so it need not wait for the finalisation,
-// whose short, latency-bound workgroups run beside its streaming ones.
-__global__ __launch_bounds__(256) void finalize_split3_t_kernel(StepGeom g, StepBufs b, int softmax_scales,
-                                                                double* parts, int fb, int nfin, Split3T o0,
-                                                                Split3T o1, int nz0, int kp, int gx, int gy) {
-  const int id = blockIdx.x;
-  if (id < nfin) {
-    finalize_block(g, b, softmax_scales, parts, id / fb, id % fb, fb);
-    return;
-  }
-  const int k = id - nfin;
-  split3_t_block(o0, o1, nz0, kp, k % gx, (k / gx) % gy, k / (gx * gy));
 }
 
 // softmax row pass in bf16 mode: raw fp32 scores -> dS = softmax (masked),
@@ -1244,18 +864,6 @@ void launch_pair_bn(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipSt
 }
 }  // namespace
 
-void launch_gemm_split_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
-  if (batches <= 0) return;
-  const int tn0 = (dim_max(a0.ndim, a0.Nfix, a0.C, a0.U) + 127) / 128;
-  const int tm0 = (dim_max(a0.mdim, a0.Mfix, a0.C, a0.U) + BM - 1) / BM;
-  const int tn1 = (dim_max(a1.ndim, a1.Nfix, a1.C, a1.U) + 127) / 128;
-  const int tm1 = (dim_max(a1.mdim, a1.Mfix, a1.C, a1.U) + BM - 1) / BM;
-  const int64_t nwg0 = (int64_t)tn0 * tm0 * batches, nwg1 = (int64_t)tn1 * tm1 * batches;
-  if (nwg0 + nwg1 <= 0) return;
-  if (a0.smscale) gemm_split_pair_kernel<true><<<(unsigned)(nwg0 + nwg1), 256, 0, s>>>(a0, tn0, tm0, (int)nwg0, a1, tn1, tm1);
-  else gemm_split_pair_kernel<false><<<(unsigned)(nwg0 + nwg1), 256, 0, s>>>(a0, tn0, tm0, (int)nwg0, a1, tn1, tm1);
-}
-
 void launch_gemm_bf16_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
   const int maxN = std::max(dim_max(a0.ndim, a0.Nfix, a0.C, a0.U), dim_max(a1.ndim, a1.Nfix, a1.C, a1.U));
   if (maxN <= 0 || batches <= 0) return;
@@ -1271,9 +879,7 @@ void launch_score_split(const GemmArgsH& a, int epi, int batches, hipStream_t s)
   const int tiles_m = (maxM + BM - 1) / BM;
   const int tiles_n = (maxN + 127) / 128;   // = nct (PBG_SCORE_BN columns per tile)
   const unsigned nwg = (unsigned)((int64_t)tiles_n * tiles_m * batches);
-  if (epi == EPI_LOSS) score_split_kernel<EPI_LOSS, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
-  else if (epi == EPI_SOFTMAX_EXP) score_split_kernel<EPI_SOFTMAX_EXP, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
-  else score_split_kernel<EPI_STORE, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
+  score_split_kernel<EPI_STORE, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
 }
 
 void launch_to_bf16_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qh, int64_t qh_bs, uint16_t* qT,
@@ -1286,33 +892,6 @@ void launch_to_bf16_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qh, in
   const int nq = q ? batches : 0;   // no Q: only N
   dim3 grid((kp + 63) / 64, (std::max(q ? q_ldT : 0, n_ldT) + 63) / 64, nq + batches);
   to_bf16_t_kernel<<<grid, 256, 0, s>>>(o0, o1, nq, kp);
-}
-
-void launch_finalize_split3_t(const StepGeom& g, const StepBufs& b, double* parts, bool softmax_scales,
-                              const float* q, int64_t q_bs, int q_rows, uint16_t* qT, int64_t qT_bs, int64_t q_ps,
-                              int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nT, int64_t nT_bs,
-                              int64_t n_ps, int n_ldT, int ld_src, int kp, int batches, hipStream_t s) {
-  const int fb = fin_blocks(g.C);
-  const int nfin = fb * g.nchunks;
-  const Split3T o0{q, q_bs, q_rows, ld_src, qT, qT_bs, q_ps, q_ldT, q_ldT};
-  const Split3T o1{n, n_bs, n_rows, ld_src, nT, nT_bs, n_ps, n_ldT, n_ldT};
-  const int nq = q ? batches : 0;
-  const int gx = (kp + 63) / 64, gy = (std::max(q ? q_ldT : 0, n_ldT) + 63) / 64;
-  const int nsplit = (batches > 0 && kp > 0) ? gx * gy * (nq + batches) : 0;
-  if (nfin + nsplit <= 0) return;
-  finalize_split3_t_kernel<<<nfin + nsplit, 256, 0, s>>>(g, b, softmax_scales ? 1 : 0, parts, fb, nfin, o0, o1, nq,
-                                                         kp, gx, gy);
-}
-
-void launch_split3_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qT, int64_t qT_bs, int64_t q_ps,
-                     int q_ldT, const float* n, int64_t n_bs, int n_rows, uint16_t* nT, int64_t nT_bs,
-                     int64_t n_ps, int n_ldT, int ld_src, int kp, int batches, hipStream_t s) {
-  if (batches <= 0 || kp <= 0) return;
-  const Split3T o0{q, q_bs, q_rows, ld_src, qT, qT_bs, q_ps, q_ldT, q_ldT};
-  const Split3T o1{n, n_bs, n_rows, ld_src, nT, nT_bs, n_ps, n_ldT, n_ldT};
-  const int nq = q ? batches : 0;   // no Q: only N
-  dim3 grid((kp + 63) / 64, (std::max(q ? q_ldT : 0, n_ldT) + 63) / 64, nq + batches);
-  split3_t_kernel<<<grid, 256, 0, s>>>(o0, o1, nq, kp);
 }
 
 void launch_softmax_rows_bf16(const StepGeom& g, const StepBufs& b, uint16_t* dsh, int ldh, hipStream_t s) {

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(256) void expand_ds_kernel(StepGeom g, int mode, co
         v = __uint_as_float((uint32_t)h[((int64_t)z * g.C + e) * ld + t] << 16);
       } else {
         v = f32[((int64_t)z * g.C + e) * ld + t];
-        if (mode == DS_F32_SCALED) v *= scale[((int64_t)z * g.nct + t / PBG_SCORE_BN) * g.C + e];
+        if (mode == DS_F32_SCALED) v *= scale[((int64_t)z * g.nct + t / PBG_PART_BN) * g.C + e];
       }
     }
     out[((int64_t)z * g.C + e) * g.N + t] = v;

@@ -317,6 +317,69 @@ __device__ __forceinline__ void bits_epilogue(const ScoreArgs& a, const ScoreTil
   }
 }
 
+// Logistic: dS = sigmoid(s) / K and the row's losses softplus(s) / K; softmax:
+// exp(s - M), M the row's maximum over the block's 64 columns, and (M, row
+// sum).  Float32 rows to Cm (zeros off the valid set), row partials per 64
+// columns.  Masked elements hold -inf.
+template <int EPI, bool SCALED, int WR>
+__device__ __forceinline__ void value_epilogue(const ScoreArgs& a, const ScoreTile& t, v4f (&acc)[4][4],
+                                               const ScoreSmem<WR>& sm, int wm, int wn, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  const int Nc = t.Cc + a.U;
+  const float kinv = Nc > 1 ? 1.0f / (float)(Nc - 1) : 0.0f;
+  float cscl[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) cscl[j] = SCALED ? sm.cscl[64 * wn + 16 * j + l16] : 1.0f;
+  float m0 = 0.0f, m1 = 0.0f;   // this lane's row: 16 (l16 / 4) + 4 g + l16 % 4
+  float* base = a.Cm + t.c * a.c_cs + t.side * a.c_ss;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int mb = 64 * wm + 16 * i + 4 * g;
+    const v4f scl = *(const v4f*)&sm.scl[mb];
+    const v4f bias = *(const v4f*)&sm.thr[mb];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = t.m0 + mb + r;
+      float s[4], v0 = 0.0f, v1 = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j] = (SCALED ? acc[i][j][r] * cscl[j] : acc[i][j][r]) * scl[r] + bias[r];
+      float* row = base + (int64_t)m * a.ldc;
+      if (EPI == EPI_LOSS) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float sg, sp;
+          logistic_pair(s[j], sg, sp);
+          s[j] = sg * kinv;
+          v0 += sp * kinv;
+          v1 += s[j];
+        }
+        v0 = group16_sum(v0);
+        v1 = group16_sum(v1);
+      } else {
+        v0 = group16_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          s[j] = v0 > -INFINITY ? expf(s[j] - v0) : 0.0f;
+          v1 += s[j];
+        }
+        v1 = group16_sum(v1);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int n = t.n0 + 64 * wn + 16 * j + l16;
+        if (m < t.M && n < a.ldc) row[n] = s[j];
+      }
+      const bool own = l16 == 4 * i + r;
+      m0 = own ? v0 : m0;
+      m1 = own ? v1 : m1;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const int m = t.m0 + 64 * wm + 16 * (l16 >> 2) + 4 * g + (l16 & 3), nb = t.n0 / 64 + wn;
+  if (m < t.M && 64 * nb < t.N)
+    *((float2*)a.rowpart + ((int64_t)(t.c * 2 + t.side) * a.C + m) * a.nct + nb) = make_float2(m0, m1);
+}
+
 // EPI_STORE: the scores as float32 rows in Cm
 template <bool SHARED, int WR>
 __device__ __forceinline__ void store_epilogue(const ScoreArgs& a, const ScoreTile& t, v4f (&acc)[4][4],
@@ -407,7 +470,7 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     const bool col = tid >= BM;
     const int own = col ? tid - BM : tid;
     float p = 0.0f, bias = 0.0f, scl = 1.0f;
-    if (EPI != EPI_STORE)
+    if (EPI == EPI_LOSS_BITS)
       p = a.pos[(int64_t)(cur.c * a.pos_sides + (a.pos_sides - 1) * cur.side) * a.C +
                 (col ? min(cur.n0, a.C) + (own & (BN - 1)) : cur.m0 + own)];
     if (SCALED)
@@ -437,6 +500,7 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     auto spread = [&]() {
       if (!col) {
         sm.scl[own] = SCALED ? scl : a.unscale;
+        if (EPI == EPI_LOSS || EPI == EPI_SOFTMAX_EXP) sm.thr[own] = bias;
         if (EPI == EPI_LOSS_BITS) {   // the scale's inverse is exact: a power of two
           sm.thr[own] = thr;
           sm.nthr[own] = cur.m0 + own < cur.M ? -thr * (SCALED ? __builtin_amdgcn_rcpf(scl) : a.iunscale) : INFINITY;
@@ -475,10 +539,11 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     if (EPI == EPI_STORE) {
       if (shared) store_epilogue<true, WR>(a, cur, acc, sm, wm, wn, lane);
       else store_epilogue<false, WR>(a, cur, acc, sm, wm, wn, lane);
-    } else if (EPI == EPI_LOSS_BITS) {
+    } else {
       const bool diag = cur.nrow0 == 0 && cur.m0 < cur.n0 + BN && cur.n0 < cur.m0 + BM;
       if (diag || cur.n0 + BN > cur.N || (shared && cur.m0 + BM > cur.M)) mask_tile(cur, acc, wm, wn, lane);
-      if (!SCALED && shared) bits_epilogue<true, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
+      if (EPI != EPI_LOSS_BITS) value_epilogue<EPI, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
+      else if (!SCALED && shared) bits_epilogue<true, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
       else bits_epilogue<false, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
     }
   }
@@ -504,7 +569,11 @@ void launch_wr(const ScoreArgs& a, int batches, hipStream_t s) {
 
 template <int EPI>
 void launch_t(const ScoreArgs& a, int batches, hipStream_t s) {
-  const bool few = score_rows(a.Mfix > 0 ? a.Mfix : a.C) == 128;
+  // four waves where no chunk fills more than their 128 rows.  Not by the
+  // average: relation-grouped chunks of about 70 edges (500 uniform negatives,
+  // d = 200) took 135 us with 128-row tiles, 100 us with 256-row ones, whose
+  // eight waves keep twice the loads in flight.
+  const bool few = (a.Mfix > 0 ? a.Mfix : a.C) <= 128;
   if (a.ia) few ? launch_wr<EPI, true, 2>(a, batches, s) : launch_wr<EPI, true, 4>(a, batches, s);
   else few ? launch_wr<EPI, false, 2>(a, batches, s) : launch_wr<EPI, false, 4>(a, batches, s);
 }
@@ -514,5 +583,7 @@ void launch_t(const ScoreArgs& a, int batches, hipStream_t s) {
 void launch_score(const ScoreArgs& a, int epi, int nchunks, hipStream_t s) {
   if (nchunks <= 0) return;
   if (epi == EPI_LOSS_BITS) launch_t<EPI_LOSS_BITS>(a, nchunks, s);
+  else if (epi == EPI_LOSS) launch_t<EPI_LOSS>(a, nchunks, s);
+  else if (epi == EPI_SOFTMAX_EXP) launch_t<EPI_SOFTMAX_EXP>(a, nchunks, s);
   else launch_t<EPI_STORE>(a, nchunks, s);
 }

@@ -70,55 +70,6 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
   launch_gemm_bf16_pair(qa, na, nch * 2, cs);
 }
 
-// Arguments of the float32 score contraction of a step with its loss
-// epilogue (operands, dS and row-partial outputs); *epi receives the epilogue
-// the loss takes
-static GemmArgsH score_args_f32(const StepGeom& g, const StepBufs& b, int* epi_out) {
-  const int C = g.C, U = g.U, N = g.N, dp = g.dp, Np = g.Np;
-  GemmArgsH fa;
-  memset(&fa, 0, sizeof(fa));
-  fa.Bf = b.nn;
-  fa.Cm = b.ds;
-  if (QK_IN_NN(g)) {
-    // side s reads the candidate rows of side 1 - s, so the scores of side 1
-    // against the chunk's own candidates are the transposed ones of side 0
-    fa.Af = b.nn + (int64_t)N * dp;
-    fa.a_cs = 2ll * N * dp;
-    fa.a_ss = -(int64_t)N * dp;
-    fa.share_cc = 1;
-  } else {
-    fa.Af = b.qk;
-    fa.a_cs = 2ll * C * dp;
-    fa.a_ss = (int64_t)C * dp;
-  }
-  fa.b_cs = 2ll * N * dp;
-  fa.b_ss = (int64_t)N * dp;
-  fa.c_cs = 2ll * C * Np;
-  fa.c_ss = (int64_t)C * Np;
-  fa.lda = dp;
-  fa.ldb = dp;
-  fa.ldc = Np;
-  fa.mdim = DIM_CC;
-  fa.ndim = DIM_NC;
-  fa.kdim = DIM_FIXED;
-  fa.Kfix = g.d;
-  fa.C = C;
-  fa.U = U;
-  fa.m_step = g.m_step;
-  fa.cstart = g.cstart;
-  fa.nsides = 2;
-  fa.pos = b.pos;
-  fa.pos_sides = g.recip ? 2 : 1;
-  fa.bias = (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) ? b.bias : nullptr;
-  fa.rowpart = b.rowpart;
-  fa.nct = g.nct;
-  fa.loss = g.loss;
-  fa.margin = g.margin;
-  const int epi = g.loss == LOSS_SOFTMAX ? EPI_SOFTMAX_EXP : EPI_LOSS;
-  *epi_out = epi;
-  return fa;
-}
-
 // Score contraction on row pieces: operands and per-row inputs
 static ScoreArgs score_args_pieces(const StepGeom& g, const StepBufs& b) {
   const int64_t C = g.C, N = g.N, ld = g.pld;
@@ -133,7 +84,7 @@ static ScoreArgs score_args_pieces(const StepGeom& g, const StepBufs& b) {
     a.A = b.pn + N * ld;
     a.a_cs = 2 * N * ld;
     a.a_ss = -N * ld;
-    a.share = 1;
+    a.share = g.dq_has_dn;
   } else {
     a.A = b.pq;
     a.a_cs = 2 * C * ld;
@@ -229,92 +180,73 @@ static void run_bits_backward(const StepGeom& g, const StepBufs& b, hipStream_t 
   launch_bits_backward(a, g.nchunks, cs);
 }
 
+// Backward of the logistic and softmax losses on row pieces
+static void run_value_backward(const StepGeom& g, const StepBufs& b, hipStream_t cs) {
+  const int64_t C = g.C, N = g.N, ld = g.pld;
+  ValueArgs a;
+  memset(&a, 0, sizeof(a));
+  a.ds = b.ds;
+  a.lds = g.Np;
+  a.rowscale = g.loss == LOSS_SOFTMAX ? b.rowscale : nullptr;
+  a.nct = g.nct;
+  a.N = b.pn;
+  a.n_cs = 2 * N * ld;
+  a.n_ss = N * ld;
+  if (QK_IN_NN(g)) {
+    a.Q = b.pn + N * ld;
+    a.q_cs = 2 * N * ld;
+    a.q_ss = -N * ld;
+  } else {
+    a.Q = b.pq;
+    a.q_cs = 2 * C * ld;
+    a.q_ss = C * ld;
+  }
+  a.dh = g.dh;
+  a.ld = g.pld;
+  a.dp = g.dp;
+  a.C = g.C;
+  a.U = g.U;
+  a.m_step = g.m_step;
+  a.cstart = g.cstart;
+  a.ks_n = g.ks_n;
+  a.ks_q = g.ks_q;
+  if (g.pieces == PIECES_SCALED) {
+    a.nkf = b.nkf;
+    a.qkf = b.qkf;
+    a.nmax = b.pn_max;
+    a.qmax = b.pq_max;
+  }
+  a.cscale = g.cweight;
+  a.dq = b.dq;
+  a.dn = b.dn;
+  a.dq_cs = 2 * C * g.dp;
+  a.dq_ss = C * g.dp;
+  a.dn_cs = 2 * N * g.dp;
+  a.dn_ss = N * g.dp;
+  launch_value_backward(a, g.nchunks, cs);
+}
+
 void run_contractions_f32(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, int64_t t, hipStream_t cs,
                           const std::function<void(int)>& mark, bool forward_only) {
-  const int C = g.C, U = g.U, N = g.N, dp = g.dp, Np = g.Np, nch = g.nchunks;
-  if (g.pieces != PIECES_NONE) {
-    launch_score(score_args_pieces(g, b), EPI_LOSS_BITS, nch, cs);
-    mark(2);
-    launch_finalize(g, b, ctx->lossparts + t * ctx->lossparts_pps, false, cs);
-    mark(3);
-    if (!forward_only) run_bits_backward(g, b, cs);
-    return;
+  ScoreArgs a = score_args_pieces(g, b);
+  int epi = EPI_LOSS_BITS;
+  if (g.loss != LOSS_RANKING) {
+    epi = g.loss == LOSS_SOFTMAX ? EPI_SOFTMAX_EXP : EPI_LOSS;
+    a.Cm = b.ds;
+    a.c_cs = 2ll * g.C * g.Np;
+    a.c_ss = (int64_t)g.C * g.Np;
+    a.ldc = g.Np;
   }
-  int epi = EPI_LOSS;
-  const GemmArgsH fa = score_args_f32(g, b, &epi);
-  launch_score_split(fa, epi, nch * 2, cs);
+  launch_score(a, epi, g.nchunks, cs);
   mark(2);
-  // softmax: the score pass leaves exp(s - tile max), the finalisation each
-  // row's log-sum-exp and per-tile scales, and the backward forms dS as it
-  // stages the exponentials
-  double* const parts = ctx->lossparts + t * ctx->lossparts_pps;
-  if (forward_only) {
-    launch_finalize(g, b, parts, g.loss == LOSS_SOFTMAX, cs);
-    mark(3);
-    return;
-  }
-  // Q and N in three exact bf16 pieces each, transposed (the B operands of
-  // both backward products), in the same launch as the finalisation.  On the
-  // second stream beside the score contraction it delays the score kernel by
-  // as much as it saves here.
-  const int dpb = rup(g.d, 32), Cpb = rup(C, 32), Npb = rup(N, 32);
-  const BufsH& h = ctx->h;
-  // with QK_IN_NN, Q^T of side s is the first C columns of N^T of side 1 - s
-  const bool qn = QK_IN_NN(g);
-  launch_finalize_split3_t(g, b, parts, g.loss == LOSS_SOFTMAX, qn ? nullptr : b.qk, (int64_t)C * dp, C, h.qkT3,
-                           (int64_t)dpb * Cpb, h.q3_ps, Cpb, b.nn, (int64_t)N * dp, N, h.nnT3, (int64_t)dpb * Npb,
-                           h.n3_ps, Npb, dp, dpb, nch * 2, cs);
+  // softmax: the score pass leaves exp(s - block maximum), the finalisation
+  // each row's log-sum-exp and per-block scales, and the backward forms dS as
+  // it stages the exponentials
+  launch_finalize(g, b, ctx->lossparts + t * ctx->lossparts_pps, g.loss == LOSS_SOFTMAX, cs);
   mark(3);
-  // general float32 dS (logistic, softmax): split into pieces as it is staged,
-  // six piece products
-  GemmArgsH qa;
-  memset(&qa, 0, sizeof(qa));
-  qa.Af = b.ds;
-  qa.smscale = g.loss == LOSS_SOFTMAX ? b.rowscale : nullptr;
-  qa.nct = g.nct;
-  qa.a_cs = 2ll * C * Np;
-  qa.a_ss = (int64_t)C * Np;
-  qa.lda = Np;
-  qa.B = h.nnT3;
-  qa.planes = 3;
-  qa.b_ps = h.n3_ps;
-  qa.b_cs = 2ll * dpb * Npb;
-  qa.b_ss = (int64_t)dpb * Npb;
-  qa.ldb = Npb;
-  qa.Cm = b.dq;
-  qa.c_cs = 2ll * C * dp;
-  qa.c_ss = (int64_t)C * dp;
-  qa.ldc = dp;
-  qa.mdim = DIM_CC;
-  qa.ndim = DIM_FIXED;
-  qa.Nfix = dp;
-  qa.kdim = DIM_NC;
-  qa.C = C;
-  qa.U = U;
-  qa.m_step = g.m_step;
-  qa.cstart = g.cstart;
-  qa.nsides = 2;
-  GemmArgsH na = qa;
-  if (qn) {
-    na.B = h.nnT3 + (int64_t)dpb * Npb;   // Q^T of side s: N^T of side 1 - s
-    na.b_ps = h.n3_ps;
-    na.b_cs = 2ll * dpb * Npb;
-    na.b_ss = -(int64_t)dpb * Npb;
-    na.ldb = Npb;
-  } else {
-    na.B = h.qkT3;
-    na.b_ps = h.q3_ps;
-    na.b_cs = 2ll * dpb * Cpb;
-    na.b_ss = (int64_t)dpb * Cpb;
-    na.ldb = Cpb;
-  }
-  na.Cm = b.dn;
-  na.c_cs = 2ll * N * dp;
-  na.c_ss = (int64_t)N * dp;
-  na.mdim = DIM_NC;
-  na.kdim = DIM_CC;
-  qa.cscale = na.cscale = g.cweight;   // the chunks' relation weights
-  launch_gemm_split_pair(qa, na, nch * 2, cs);
+  if (forward_only) return;
+  if (g.loss == LOSS_RANKING) run_bits_backward(g, b, cs);
+  else run_value_backward(g, b, cs);
 }
 
 // Operands of the bf16-input score contraction of a step (the rounded copies
@@ -543,20 +475,13 @@ void run_score_store(pbg_ctx* ctx, const StepGeom& g, const StepBufs& b, float* 
     if (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) launch_add_side_bias(g, b.bias, out, cs);
     return;
   }
-  GemmArgsH fa;
-  if (ctx->flags & PBG_F_BF16_SCORE) {
-    fa = score_args_bf16(ctx, g, b);
-  } else {
-    int epi = EPI_LOSS;
-    fa = score_args_f32(g, b, &epi);
-  }
+  GemmArgsH fa = score_args_bf16(ctx, g, b);
   fa.Cm = out;
   fa.dsh = nullptr;
   fa.dsb = nullptr;
   fa.c_cs = 2ll * g.C * g.N;
   fa.c_ss = (int64_t)g.C * g.N;
   fa.ldc = g.N;
-  if (ctx->flags & PBG_F_BF16_SCORE) launch_gemm_bf16(fa, EPI_STORE, g.nchunks * 2, cs);
-  else launch_score_split(fa, EPI_STORE, g.nchunks * 2, cs);
+  launch_gemm_bf16(fa, EPI_STORE, g.nchunks * 2, cs);
   if (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) launch_add_side_bias(g, b.bias, out, cs);
 }

@@ -78,7 +78,7 @@ extern "C" pbg_status pbg_inspect_step(pbg_ctx* ctx, int32_t i, int32_t j, const
   if (dscores) {
     const int Np = g.Np, Npb = rup(N, 32);
     const int nw = (Np + 15) / 16, ldw = rup(C, 8);
-    if (g.pieces != PIECES_NONE)
+    if (g.pieces != PIECES_NONE && ctx->loss == PBG_LOSS_RANKING)
       launch_expand_bits(g, b, dscores, cs);
     else if (ctx->loss == PBG_LOSS_RANKING)
       launch_expand_ds(g, DS_BITS, b.dsb, nw, ldw, nullptr, nullptr, nullptr, 0, dscores, cs);

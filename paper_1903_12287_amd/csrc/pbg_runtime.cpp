@@ -112,9 +112,16 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
       b.pq_is = (float*)a.get((s * 2 * C + 256) * 4);
       b.pn_max = (int*)a.get(s * 4 * 4);
       b.pq_max = b.pn_max ? b.pn_max + s * 2 : nullptr;
-      b.nks = (uint16_t*)a.get(s * 2 * round_up(N, 32) * 2);
-      b.qks = (uint16_t*)a.get(s * 2 * round_up(C, 32) * 2);
+      if (ranking) {
+        b.nks = (uint16_t*)a.get(s * 2 * round_up(N, 32) * 2);
+        b.qks = (uint16_t*)a.get(s * 2 * round_up(C, 32) * 2);
+      } else {
+        b.nkf = (float*)a.get(s * 2 * round_up(N, 32) * 4);
+        b.qkf = (float*)a.get(s * 2 * round_up(C, 32) * 4);
+      }
     }
+  }
+  if (pieces && ranking) {
     const BitsView v = bits_view(C, U);
     b.bits_rb = v.RB;
     b.bits_cb = v.CB;
@@ -179,13 +186,6 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
     ctx->h.qkT = (uint16_t*)a.get(s * 2 * dpb * Cpb * 2);
     ctx->h.nnT = (uint16_t*)a.get(s * 2 * dpb * Npb * 2);
     if (!ranking) ctx->h.ds = (uint16_t*)a.get(s * 2 * C * (int64_t)Npb * 2);
-  } else if (!pieces) {
-    // float32 backward on the bf16 instructions: transposed pieces of Q and N
-    const int dpb = round_up(d, 32), Cpb = round_up(C, 32), Npb = round_up(N, 32);
-    ctx->h.q3_ps = s * 2 * dpb * (int64_t)Cpb;
-    ctx->h.n3_ps = s * 2 * dpb * (int64_t)Npb;
-    ctx->h.qkT3 = (uint16_t*)a.get(3 * ctx->h.q3_ps * 2);
-    ctx->h.nnT3 = (uint16_t*)a.get(3 * ctx->h.n3_ps * 2);
   }
   if (a.failed) {
     ctx->ws.release();

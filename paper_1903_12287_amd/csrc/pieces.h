@@ -41,13 +41,18 @@ constexpr uint32_t kOob = 0x80000000u;   // a buffer offset that reads zero
 
 // x = h + l in the low and high half of the result
 __device__ __forceinline__ uint32_t split2(float x) {
+  __asm__("" : "+v"(x));
   _Float16 h = (_Float16)x;
   const _Float16 l = (_Float16)(x - (float)h);
   return (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, l) << 16);
 }
 
 // two values: packed h pair and packed l pair
+// The empty asm statement keeps a and b the rounded float32 values they are:
+// a product that ends in them would otherwise be rounded to fp16 in one step
+// for h and in two for the remainder, which now and then differ by a unit.
 __device__ __forceinline__ void split2_pair(float a, float b, uint32_t& h, uint32_t& l) {
+  __asm__("" : "+v"(a), "+v"(b));
   const h2_t hh = {(_Float16)a, (_Float16)b};
   const h2_t ll = {(_Float16)(a - (float)hh.x), (_Float16)(b - (float)hh.y)};
   h = __builtin_bit_cast(uint32_t, hh);

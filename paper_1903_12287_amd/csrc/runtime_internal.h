@@ -43,11 +43,6 @@ struct BufsH {
   uint16_t* qkT = nullptr;  // [S][2][dpb][Cpb]
   uint16_t* nnT = nullptr;  // [S][2][dpb][Npb]
   uint16_t* ds = nullptr;   // [S][2][C][Npb] dS rows (logistic, softmax)
-  // float32 ranking backward: the exact three-piece split of Q^T and N^T,
-  // [3][S][2][dpb][Cpb] and [3][S][2][dpb][Npb], planes q3_ps / n3_ps apart
-  uint16_t* qkT3 = nullptr;
-  uint16_t* nnT3 = nullptr;
-  int64_t q3_ps = 0, n3_ps = 0;
 };
 
 struct pbg_ctx {
@@ -194,15 +189,15 @@ inline bool single_relation_sums(const pbg_ctx* ctx) {
 }
 // Q and K of a chunk are its candidate rows (QK_IN_NN)
 inline bool queries_in_candidates(const pbg_ctx* ctx) { return ctx->cmp == PBG_CMP_COS && !reciprocal(ctx); }
-// row pieces that the step's contractions take (float32 ranking)
+// row pieces that the step's contractions take (float32 score inputs)
 inline int pieces_of(const pbg_ctx* ctx) {
-  if (ctx->loss != PBG_LOSS_RANKING || (ctx->flags & PBG_F_BF16_SCORE)) return PIECES_NONE;
+  if (ctx->flags & PBG_F_BF16_SCORE) return PIECES_NONE;
   return ctx->cmp == PBG_CMP_COS ? PIECES_UNIT : PIECES_SCALED;
 }
 // The float32 ranking backward with the queries as candidate rows merges dN
 // rows e < Cc of one side into dQ of the other (kernels_bits_backward.hip).
 inline bool merged_ranking_backward(const pbg_ctx* ctx) {
-  return pieces_of(ctx) != PIECES_NONE && queries_in_candidates(ctx);
+  return ctx->loss == PBG_LOSS_RANKING && pieces_of(ctx) != PIECES_NONE && queries_in_candidates(ctx);
 }
 // column tiles of a chunk side's row partials (merged: side 1's in-chunk and
 // uniform tiles are counted apart)

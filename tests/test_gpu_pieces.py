@@ -35,3 +35,25 @@ def test_ranking_step_at_tile_edges(op, cmp, C, U, m, d):
     assert abs(gl - ol) <= 1e-5 * max(1.0, abs(ol))
     for got, want, rel in ((st["G"][0], om.G[0], 1e-5), (st["emb"][0], om.emb[0], 1e-5), (st["rel"], om.rel, 1e-4)):
         assert np.max(np.abs(got - want)) <= rel * max(1.0, float(np.max(np.abs(want)))) + 1e-6
+
+
+@pytest.mark.parametrize("C,U,m,d", SHAPES + [(40, 30, 100, 400)])
+@pytest.mark.parametrize("op,cmp,loss", [("translation", "dot", "logistic"), ("diagonal", "cos", "softmax"),
+                                         ("diagonal", "dot", "softmax"), ("translation", "cos", "logistic")])
+def test_value_loss_step_at_tile_edges(op, cmp, loss, C, U, m, d):
+    """As above for the losses whose dS is a float32 matrix.  Embeddings and
+    relations to 1e-4: the first Adagrad step is lr g / |g|, so an error of
+    K 2^-24 of a row's absolute sum (K up to 800 terms) counts lr K 2^-24 A / |g|
+    = 5e-6 A / |g|, and the smooth losses' rows cancel to A / |g| of about 20."""
+    pb = make_problem(op, cmp, loss, R=1 if cmp == "cos" else 3, n=400, m=m, d=d, C=C, U=U, S=4, seed=5)
+    gm = GpuModel(pb)
+    try:
+        gl = gm.train()
+        st = gm.state()
+    finally:
+        gm.close()
+    om = oracle_model(pb)
+    ol = O.train_bucket(om, pb.i, pb.j, pb.src, pb.rel_ids, pb.dst, pb.C, pb.U, pb.S, pb.lr, pb.seed)
+    assert abs(gl - ol) <= 1e-5 * max(1.0, abs(ol))
+    for got, want, rel in ((st["G"][0], om.G[0], 1e-5), (st["emb"][0], om.emb[0], 1e-4), (st["rel"], om.rel, 1e-4)):
+        assert np.max(np.abs(got - want)) <= rel * max(1.0, float(np.max(np.abs(want)))) + 1e-6
