@@ -10,7 +10,8 @@
 // EPI_LOSS_BITS: ranking loss with dS (0 or 1) written as bits, 16 columns per
 // uint16 word, word (w, row) at dsb[w * ldcb + row] (nwcb words per row; batch
 // strides cb_cs / cb_ss in words)
-enum { EPI_STORE = 0, EPI_LOSS = 1, EPI_SOFTMAX_STATS = 2, EPI_LOSS_BITS = 3, EPI_SOFTMAX_EXP = 4 };
+enum { EPI_STORE = 0, EPI_LOSS = 1, EPI_SOFTMAX_STATS = 2, EPI_LOSS_BITS = 3, EPI_SOFTMAX_EXP = 4,
+       EPI_RANK = 5 };
 enum { DIM_CC = 0, DIM_NC = 1, DIM_FIXED = 2 };
 // float32 operand layouts: NT  A[m][k], B[n][k];  TN  A[k][m], B[k][n]
 enum { GEMM_NT = 0, GEMM_TN = 2 };
@@ -43,11 +44,7 @@ enum {
 };
 struct GemmArgsH {
   const uint16_t* A;
-  const uint16_t* B;     // planes pieces of B, b_ps elements apart
-  int planes;            // 1, or 3: the exact bf16 pieces of a float32 operand (launch_gemm_split_pair)
-  int64_t b_ps;
-  const float* Af;       // launch_score_split: float32 operands [m][k] and [n][k]
-  const float* Bf;
+  const uint16_t* B;
   float* Cm;             // fp32 output (STORE, SOFTMAX_STATS)
   uint16_t* dsh;         // EPI_LOSS: dS rows in bf16 (strides c_*, ldc)
   uint16_t* dsb;         // EPI_LOSS_BITS output (as in GemmArgs)
@@ -74,11 +71,8 @@ struct GemmArgsH {
 // bf16-input score contraction with a loss epilogue (EPI_LOSS, EPI_LOSS_BITS or
 // EPI_SOFTMAX_STATS) or the plain store (EPI_STORE: float32 scores to Cm)
 void launch_gemm_bf16(const GemmArgsH& a, int epi, int batches, hipStream_t s);
-// float32 product S = A . B^T (EPI_STORE) on the bf16 instructions, operands
-// Af / Bf split into exact bf16 pieces on the way into LDS
-void launch_score_split(const GemmArgsH& a, int epi, int batches, hipStream_t s);
 // two EPI_STORE products in one launch: a0 with A as dS rows (GA_BITS_ROW or
-// GA_KC), a1 with A as dS columns (GA_BITS_COL or GA_MC), same planes
+// GA_KC), a1 with A as dS columns (GA_BITS_COL or GA_MC)
 void launch_gemm_bf16_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s);
 // bf16 path: Q and N rows (fp32, [rows][ld_src]) rounded once to bf16 rows
 // [rows][kp] and transposed copies [kp][ldT], both operands in one launch.
@@ -130,6 +124,7 @@ struct ScoreArgs {
   uint32_t *bits0, *bits1;
   int64_t bits_cs, bits_ss, bits1_cs;   // words
   int RB;
+  uint8_t* hits;                // EPI_RANK: [64 columns][16 RB] candidates at or above the positive score
   float* Cm;                    // float32 scores (EPI_STORE), dS (EPI_LOSS) or exp(s - block maximum)
   int64_t c_cs, c_ss;           // (EPI_SOFTMAX_EXP)
   int ldc;
@@ -325,20 +320,40 @@ void launch_bucket_gather(const uint32_t* vals, const int64_t* src, const int32_
                           int32_t* rel_out, int32_t* dst_local, hipStream_t s);
 
 // ---- filtered ranks (Sec. 5.4) -------------------------------------------------
-// T0: every entity row (unit rows for cos); T1 (cos with an operator, one
-// relation): the unit rows of g(x) (relT: the linear operator's A^T rows)
-void launch_rank_tables(const StepGeom& g, const float* emb, const float* relp, const float* relT, int64_t n_ent,
-                        float* T0, float* T1, hipStream_t s);
+// Pieces (scaled rows of pld words) and inverse scales of a candidate table
+// and of a query block.
+struct RankRows {
+  uint16_t* p;
+  float* is;
+};
+// T0: row i of entity cand[i] (NULL: entity i), unit rows for cos; T1 (cos with
+// an operator, one relation): the unit rows of g(x) (relT: the linear
+// operator's A^T rows)
+void launch_rank_tables(const StepGeom& g, const float* emb, const float* relp, const float* relT,
+                        const int32_t* cand, int64_t n_col, RankRows T0, RankRows T1, hipStream_t s);
 void launch_rank_queries(const StepGeom& g, const float* emb, const float* relp, const float* relT,
                          const int32_t* src, const int32_t* rel, const int32_t* dst, int64_t e0, int rows,
-                         int side, float* Q, float* pos, float* bias, hipStream_t s);
-// cand: entity id of each score column (nullptr: column t is entity t)
-void launch_rank_count(const float* S, int64_t ldS, int64_t n_ent, const int32_t* cand, int64_t e0, int rows,
-                       int side, int64_t n_eval, const int32_t* src, const int32_t* rel, const int32_t* dst,
-                       const float* pos, const float* bias, const int32_t* ka, const int32_t* kb,
-                       const int32_t* kc, int64_t n_known, int32_t* ranks, hipStream_t s);
-// out[i] = T[idx[i]], rows of ld floats (ids checked by the caller)
-void launch_gather_rows(const float* T, const int32_t* idx, int64_t n, int ld, float* out, hipStream_t s);
+                         int side, RankRows Q, float* pos, float* bias, hipStream_t s);
+// Ranks of a query block from the hit bits and counts of EPI_RANK.  Taken back
+// per query: the true entity's columns and, with a filter, the known triples'
+// (ka, kb, kc sorted).  cand (sorted, cand_at its columns): a candidate list,
+// no filter; NULL: column t is entity t
+struct RankCount {
+  const uint32_t* bits;
+  const uint8_t* hits;
+  int RB, n_blk;                // row blocks of 16, column blocks of 64
+  int64_t e0, n_eval;
+  int rows, side;
+  const int32_t *src, *rel, *dst;
+  const int32_t *ka, *kb, *kc;
+  int64_t n_known;
+  const int32_t *cand, *cand_at;
+  int64_t n_cand;
+  int32_t* ranks;
+};
+void launch_rank_count(const RankCount& a, hipStream_t s);
+// out: the two metrics, then 2 RANK_METRIC_BLOCKS partial sums
+#define RANK_METRIC_BLOCKS 64
 void launch_rank_metrics(const int32_t* ranks, int64_t n, double* out, hipStream_t s);
 void launch_perm_keys(const int32_t* field, const uint32_t* perm, int64_t n, uint32_t* keys,
                       uint32_t* vals_init, hipStream_t s);

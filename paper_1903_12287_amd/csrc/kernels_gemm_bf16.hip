@@ -65,24 +65,6 @@ __device__ __forceinline__ uint32_t f2_to_bf16x2(float a, float b) {
   return __builtin_bit_cast(uint32_t, (bf16x2_t){(__bf16)a, (__bf16)b});
 }
 
-// x = h + m + l exactly, each piece a bf16: h = bf16(x) leaves a remainder of
-// at most 16 significant bits, m = bf16 of that remainder leaves at most 8,
-// which l holds exactly (for |x| >= 2^-110, where every piece is a normal
-// number).  Two floats at a time: pc[0..2] = packed h, m, l.
-// The empty asm statements hide h and m from the optimiser, which would
-// otherwise form h << 16 from a second conversion of a alone (one extra
-// instruction per level and pair).
-__device__ __forceinline__ void split3_pair(float a, float b, uint32_t* pc) {
-  uint32_t h = f2_to_bf16x2(a, b);
-  __asm__("" : "+v"(h));
-  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
-  uint32_t m = f2_to_bf16x2(ra, rb);
-  __asm__("" : "+v"(m));
-  pc[0] = h;
-  pc[1] = m;
-  pc[2] = f2_to_bf16x2(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xFFFF0000u));
-}
-
 __device__ __forceinline__ int pick_dim(int sel, int fixed, int Cc, int Nc) {
   return sel == DIM_CC ? Cc : (sel == DIM_NC ? Nc : fixed);
 }
@@ -176,13 +158,11 @@ struct TileH {
   }
 };
 
-// LDS of one workgroup: the A tile and PL B tiles (NB buffers), row partials
-template <int BN, int PL>
+// LDS of one workgroup: the A and B tiles (two buffers), row partials
+template <int BN>
 struct SmemH {
-  // three B planes: one buffer (three workgroups per CU); otherwise two
-  static constexpr int NB = PL == 3 ? 1 : 2;
-  uint16_t As[NB][BM * BK];
-  uint16_t Bs[NB][PL][BN * BK];
+  uint16_t As[2][BM * BK];
+  uint16_t Bs[2][BN * BK];
   float red[2][BM][2];
   float rowv[2][BM];
 };
@@ -466,10 +446,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgsH& a, const TileGeo&
 }
 
 
-// One 128 x BN output tile of A . B with bf16 operands (B in PL planes).
-template <int BN, int AMODE, int EPI, int PL>
+// One 128 x BN output tile of A . B with bf16 operands.
+template <int BN, int AMODE, int EPI>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmArgsH& a, int tiles_n, int tiles_m, int nwg, int id,
-                                               SmemH<BN, PL>& sm) {
+                                               SmemH<BN>& sm) {
   constexpr int WN = BN / 2;
   constexpr int JN = WN / 16;
   using TA = TileH<BM, AMODE>;
@@ -487,7 +467,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgsH& a, int tiles_n, 
   const int l16 = lane & 15, g = lane >> 4;
 
   const rsrc_t ra_s = make_rsrc(a.A + c * a.a_cs + side * a.a_ss);
-  const rsrc_t rb_s = make_rsrc(a.B + c * a.b_cs + side * a.b_ss);
+  const rsrc_t rb = make_rsrc(a.B + c * a.b_cs + side * a.b_ss);
 
   v4f acc[4][JN];
 #pragma unroll
@@ -495,56 +475,39 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgsH& a, int tiles_n, 
 #pragma unroll
     for (int j = 0; j < JN; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
 
-  // one plane resource per B piece (planes b_ps elements apart)
-  rsrc_t rb[PL];
-  rb[0] = rb_s;
-#pragma unroll
-  for (int p = 1; p < PL; ++p) rb[p] = make_rsrc(a.B + p * a.b_ps + c * a.b_cs + side * a.b_ss);
-
-  u32x4 pa[TA::LOADS], pb[PL][TB::LOADS];
+  u32x4 pa[TA::LOADS], pb[TB::LOADS];
   const int nk = (K + BK - 1) / BK;
   TA::load(pa, ra_s, a.lda, m0, M, 0, K, tid);
-#pragma unroll
-  for (int p = 0; p < PL; ++p) TB::load(pb[p], rb[p], a.ldb, n0, N, 0, K, tid);
+  TB::load(pb, rb, a.ldb, n0, N, 0, K, tid);
   TA::store(As[0], pa, tid, m0, 0, K);
-#pragma unroll
-  for (int p = 0; p < PL; ++p) TB::store(Bs[0][p], pb[p], tid, n0, 0, K);
+  TB::store(Bs[0], pb, tid, n0, 0, K);
   __syncthreads();
 
   // fragment offsets: row 16 i + l16 of the wave's block, group g (the
   // swizzle repeats every 16 rows)
   const int fa0 = swz(64 * wm + l16, g), fb0 = swz(WN * wn + l16, g);
-  constexpr int NB = SmemH<BN, PL>::NB;
   for (int kt = 0; kt < nk; ++kt) {
-    const int buf = NB == 2 ? (kt & 1) : 0;
+    const int buf = kt & 1;
     if (kt + 1 < nk) {
       TA::load(pa, ra_s, a.lda, m0, M, (kt + 1) * BK, K, tid);
-#pragma unroll
-      for (int p = 0; p < PL; ++p) TB::load(pb[p], rb[p], a.ldb, n0, N, (kt + 1) * BK, K, tid);
+      TB::load(pb, rb, a.ldb, n0, N, (kt + 1) * BK, K, tid);
     }
     const uint16_t* as = As[buf];
     v8bf af[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) af[i] = *(const v8bf*)(as + fa0 + 16 * i * BK);
+    v8bf bf[JN];
 #pragma unroll
-    for (int p = 0; p < PL; ++p) {
-      const uint16_t* bs = Bs[buf][p];
-      v8bf bf[JN];
+    for (int j = 0; j < JN; ++j) bf[j] = *(const v8bf*)(Bs[buf] + fb0 + 16 * j * BK);
 #pragma unroll
-      for (int j = 0; j < JN; ++j) bf[j] = *(const v8bf*)(bs + fb0 + 16 * j * BK);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < JN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-    }
+      for (int j = 0; j < JN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
     if (kt + 1 < nk) {
-      // one buffer: every wave is done reading it before it is overwritten
-      if (NB == 1) __syncthreads();
-      const int nbuf = NB == 2 ? (buf ^ 1) : 0;
+      const int nbuf = buf ^ 1;
       TA::store(As[nbuf], pa, tid, m0, (kt + 1) * BK, K);
-#pragma unroll
-      for (int p = 0; p < PL; ++p) TB::store(Bs[nbuf][p], pb[p], tid, n0, (kt + 1) * BK, K);
+      TB::store(Bs[nbuf], pb, tid, n0, (kt + 1) * BK, K);
     }
     __syncthreads();
   }
@@ -552,189 +515,22 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgsH& a, int tiles_n, 
   tile_epilogue<BN, EPI>(a, t, acc, sm.red, sm.rowv);
 }
 
-// ---- float32 score contraction on the bf16 instructions --------------------
-// S = Q . N^T with both operands float32: each element is split exactly into
-// three bf16 pieces (x = h + m + l, as in split3_pair) when its tile is stored to
-// LDS, and the tile is the sum of the piece products.  NPROD = 9 takes all
-// nine, so every product is exact and only the float32 sums round; NPROD = 6
-// leaves out m.l, l.m and l.l, whose sum is at most about 2^-23 |a| |b| per
-// term (|m| <= 2^-8 |x|, |l| <= 2^-16 |x|), below the rounding bound of a
-// float32 dot product of the same length.
-
-// TX rows x 32 k of a float32 [x][k] matrix (k contiguous, ld floats): each
-// thread moves groups of eight floats (two 16-byte loads) and stores their
-// three pieces to three LDS planes (swizzled [row][k] bf16 tiles).
-template <int TX>
-struct TileS {
-  static constexpr int LOADS = TX * BK / 8 / 256;   // groups of eight per thread
-
-  __device__ __forceinline__ static void load(v4f* r, rsrc_t rs, int ld, int x0, int xdim, int k0, int kdim, int tid) {
-    const int k4 = (kdim + 3) & ~3;
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      const int f = tid + 256 * q;
-      const int x = f >> 2, kq = f & 3;
-      const int gx = x0 + x, gk = k0 + 8 * kq;
-      uint32_t o0 = OOB, o1 = OOB;
-      if (gx < xdim) {
-        const uint32_t base = (uint32_t)(((int64_t)gx * ld + gk) * 4);
-        if (gk < k4) o0 = base;
-        if (gk + 4 < k4) o1 = base + 16;
-      }
-      r[2 * q] = __builtin_amdgcn_raw_buffer_load_b128(rs, o0, 0, 0);
-      r[2 * q + 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o1, 0, 0);
-    }
-  }
-
-  // this thread's byte offsets at k = 0 (OOB for rows past xdim): a slice
-  // that lies wholly inside k then loads at base + 4 k0, the k0 part as the
-  // scalar offset, with no per-slice address arithmetic
-  __device__ __forceinline__ static void bases(uint32_t* base, int ld, int x0, int xdim, int tid) {
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      const int f = tid + 256 * q;
-      const int gx = x0 + (f >> 2);
-      base[q] = gx < xdim ? (uint32_t)(((int64_t)gx * ld + 8 * (f & 3)) * 4) : OOB;
-    }
-  }
-
-  __device__ __forceinline__ static void load_full(v4f* r, rsrc_t rs, const uint32_t* base, int k0) {
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      r[2 * q] = __builtin_amdgcn_raw_buffer_load_b128(rs, base[q], 4 * k0, 0);
-      r[2 * q + 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, base[q] + 16, 4 * k0, 0);
-    }
-  }
-
-  __device__ __forceinline__ static void store(uint16_t (*s)[TX * BK], const v4f* r, int tid) {
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      const int f = tid + 256 * q;
-      const int x = f >> 2, kq = f & 3;
-      const float v[8] = {r[2 * q].x, r[2 * q].y, r[2 * q].z, r[2 * q].w,
-                          r[2 * q + 1].x, r[2 * q + 1].y, r[2 * q + 1].z, r[2 * q + 1].w};
-      uint32_t pc[3][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t pp[3];
-        split3_pair(v[2 * i], v[2 * i + 1], pp);
-#pragma unroll
-        for (int p = 0; p < 3; ++p) pc[p][i] = pp[p];
-      }
-      const int o = swz(x, kq);
-#pragma unroll
-      for (int p = 0; p < 3; ++p) *(u32x4*)(s[p] + o) = (u32x4){pc[p][0], pc[p][1], pc[p][2], pc[p][3]};
-    }
-  }
-};
-
-// one LDS buffer of three A and three B planes (single-buffered, so that
-// three workgroups fit a CU), and the row partials; rowv1: the per-row values
-// of side 1's rows of a shared tile
-template <int TM>
-struct SmemST {
-  uint16_t As[3][TM * BK];
-  uint16_t Bs[3][128 * BK];
-  float red[2][TM][2];
-  float rowv[2][TM];
-};
-using SmemS = SmemST<BM>;
-
-
-// Score tile body: four waves of 64 x 64.  One A plane and one B plane in
-// registers at a time (B planes are read again for each A plane).
-template <int EPI, int NPROD>
-__device__ __forceinline__ void score_split_body(const GemmArgsH& a, int tiles_n, int tiles_m) {
-  constexpr int BN = 128, WN = 64, JN = 4, WMR = BM / 2, IM = BM / 32;
-  __shared__ __align__(16) SmemS sm;
-  TileGeo t;
-  if (!tile_geo<BN, EPI>(a, tiles_n, tiles_m, gridDim.x, blockIdx.x, t)) return;
-  if (EPI != EPI_STORE) load_rowv<EPI>(a, t, sm.rowv);
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const int l16 = lane & 15, g = lane >> 4;
-
-  const rsrc_t ra = make_rsrc(a.Af + t.c * a.a_cs + t.side * a.a_ss);
-  const rsrc_t rb = make_rsrc(a.Bf + t.c * a.b_cs + t.side * a.b_ss);
-  v4f acc[IM][JN];
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < JN; ++j) acc[i][j] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-  v4f pa[2 * TileS<BM>::LOADS], pb[2 * TileS<BN>::LOADS];
-  const int nk = (t.K + BK - 1) / BK;
-  TileS<BM>::load(pa, ra, a.lda, t.m0, t.M, 0, t.K, tid);
-  TileS<BN>::load(pb, rb, a.ldb, t.n0, t.N, 0, t.K, tid);
-  TileS<BM>::store(sm.As, pa, tid);
-  TileS<BN>::store(sm.Bs, pb, tid);
-  __syncthreads();
-
-  const int fa0 = swz(WMR * wm + l16, g), fb0 = swz(WN * wn + l16, g);
-  uint32_t abase[TileS<BM>::LOADS], bbase[TileS<BN>::LOADS];
-  TileS<BM>::bases(abase, a.lda, t.m0, t.M, tid);
-  TileS<BN>::bases(bbase, a.ldb, t.n0, t.N, tid);
-  // slices wholly inside k (rounded up to 4, the zero-padded row length)
-  const int kfull = ((t.K + 3) & ~3) / BK;
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < kfull) {
-      TileS<BM>::load_full(pa, ra, abase, (kt + 1) * BK);
-      TileS<BN>::load_full(pb, rb, bbase, (kt + 1) * BK);
-    } else if (kt + 1 < nk) {
-      TileS<BM>::load(pa, ra, a.lda, t.m0, t.M, (kt + 1) * BK, t.K, tid);
-      TileS<BN>::load(pb, rb, a.ldb, t.n0, t.N, (kt + 1) * BK, t.K, tid);
-    }
-#pragma unroll
-    for (int pa_ = 0; pa_ < 3; ++pa_) {
-      v8bf af[IM];
-#pragma unroll
-      for (int i = 0; i < IM; ++i) af[i] = *(const v8bf*)(sm.As[pa_] + fa0 + 16 * i * BK);
-#pragma unroll
-      for (int pb_ = 0; pb_ < 3; ++pb_) {
-        if (NPROD == 6 && pa_ + pb_ > 2) continue;
-        v8bf bf[JN];
-#pragma unroll
-        for (int j = 0; j < JN; ++j) bf[j] = *(const v8bf*)(sm.Bs[pb_] + fb0 + 16 * j * BK);
-#pragma unroll
-        for (int i = 0; i < IM; ++i)
-#pragma unroll
-          for (int j = 0; j < JN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[j], acc[i][j], 0, 0, 0);
-      }
-    }
-    if (kt + 1 < nk) {
-      __syncthreads();
-      TileS<BM>::store(sm.As, pa, tid);
-      TileS<BN>::store(sm.Bs, pb, tid);
-      __syncthreads();
-    }
-  }
-  tile_epilogue<BN, EPI>(a, t, acc, sm.red, sm.rowv);
-}
-
-template <int EPI, int NPROD>
-__global__ __launch_bounds__(256) void score_split_kernel(GemmArgsH a, int tiles_n, int tiles_m) {
-  score_split_body<EPI, NPROD>(a, tiles_n, tiles_m);
-}
-
-template <int BN, int AMODE, int EPI, int PL>
+template <int BN, int AMODE, int EPI>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmArgsH a, int tiles_n, int tiles_m) {
-  __shared__ __align__(16) SmemH<BN, PL> sm;
-  gemm_bf16_tile<BN, AMODE, EPI, PL>(a, tiles_n, tiles_m, gridDim.x, blockIdx.x, sm);
+  __shared__ __align__(16) SmemH<BN> sm;
+  gemm_bf16_tile<BN, AMODE, EPI>(a, tiles_n, tiles_m, gridDim.x, blockIdx.x, sm);
 }
 
 // two independent products in one launch (dQ and dN of a step): workgroups
 // [0, nwg0) take the first, the rest the second, so that the long-k tiles of
 // the first start first and the short ones of the second fill in behind them
-template <int BN, int AM0, int AM1, int PL>
+template <int BN, int AM0, int AM1>
 __global__ __launch_bounds__(256) void gemm_bf16_pair_kernel(GemmArgsH a0, int tn0, int tm0, int nwg0,
                                                              GemmArgsH a1, int tn1, int tm1) {
-  __shared__ __align__(16) SmemH<BN, PL> sm;
+  __shared__ __align__(16) SmemH<BN> sm;
   const int id = blockIdx.x;
-  if (id < nwg0) gemm_bf16_tile<BN, AM0, EPI_STORE, PL>(a0, tn0, tm0, nwg0, id, sm);
-  else gemm_bf16_tile<BN, AM1, EPI_STORE, PL>(a1, tn1, tm1, (int)gridDim.x - nwg0, id - nwg0, sm);
+  if (id < nwg0) gemm_bf16_tile<BN, AM0, EPI_STORE>(a0, tn0, tm0, nwg0, id, sm);
+  else gemm_bf16_tile<BN, AM1, EPI_STORE>(a1, tn1, tm1, (int)gridDim.x - nwg0, id - nwg0, sm);
 }
 
 // fp32 rows [rows][ld_src] (columns [d, ld_src) zero) of Q and of N -> bf16
@@ -823,10 +619,10 @@ __global__ __launch_bounds__(256) void softmax_rows_bf16_kernel(StepGeom g, cons
 }
 
 
-template <int BN, int AMODE, int EPI, int PL = 1>
+template <int BN, int AMODE, int EPI>
 void launch_t(const GemmArgsH& a, int tiles_n, int tiles_m, int batches, hipStream_t s) {
   const int64_t nwg = (int64_t)tiles_n * tiles_m * batches;
-  gemm_bf16_kernel<BN, AMODE, EPI, PL><<<(unsigned)nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
+  gemm_bf16_kernel<BN, AMODE, EPI><<<(unsigned)nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
 }
 
 int dim_max(int sel, int fixed, int C, int U) { return sel == DIM_CC ? C : (sel == DIM_NC ? C + U : fixed); }
@@ -846,21 +642,21 @@ void launch_gemm_bf16(const GemmArgsH& a, int epi, int batches, hipStream_t s) {
 }
 
 namespace {
-template <int BN, int AM0, int AM1, int PL>
+template <int BN, int AM0, int AM1>
 void launch_pair_t(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
   const int tn0 = (dim_max(a0.ndim, a0.Nfix, a0.C, a0.U) + BN - 1) / BN;
   const int tm0 = (dim_max(a0.mdim, a0.Mfix, a0.C, a0.U) + BM - 1) / BM;
   const int tn1 = (dim_max(a1.ndim, a1.Nfix, a1.C, a1.U) + BN - 1) / BN;
   const int tm1 = (dim_max(a1.mdim, a1.Mfix, a1.C, a1.U) + BM - 1) / BM;
   const int64_t nwg0 = (int64_t)tn0 * tm0 * batches, nwg1 = (int64_t)tn1 * tm1 * batches;
-  gemm_bf16_pair_kernel<BN, AM0, AM1, PL><<<(unsigned)(nwg0 + nwg1), 256, 0, s>>>(a0, tn0, tm0, (int)nwg0, a1,
+  gemm_bf16_pair_kernel<BN, AM0, AM1><<<(unsigned)(nwg0 + nwg1), 256, 0, s>>>(a0, tn0, tm0, (int)nwg0, a1,
                                                                                  tn1, tm1);
 }
 
 template <int BN>
 void launch_pair_bn(const GemmArgsH& a0, const GemmArgsH& a1, int batches, hipStream_t s) {
-  if (a0.amode == GA_BITS_ROW) launch_pair_t<BN, GA_BITS_ROW, GA_BITS_COL, 1>(a0, a1, batches, s);
-  else launch_pair_t<BN, GA_KC, GA_MC, 1>(a0, a1, batches, s);
+  if (a0.amode == GA_BITS_ROW) launch_pair_t<BN, GA_BITS_ROW, GA_BITS_COL>(a0, a1, batches, s);
+  else launch_pair_t<BN, GA_KC, GA_MC>(a0, a1, batches, s);
 }
 }  // namespace
 
@@ -869,17 +665,6 @@ void launch_gemm_bf16_pair(const GemmArgsH& a0, const GemmArgsH& a1, int batches
   if (maxN <= 0 || batches <= 0) return;
   if (maxN <= 64) launch_pair_bn<64>(a0, a1, batches, s);
   else launch_pair_bn<128>(a0, a1, batches, s);
-}
-
-void launch_score_split(const GemmArgsH& a, int epi, int batches, hipStream_t s) {
-  constexpr int NPROD = 6;
-  const int maxM = dim_max(a.mdim, a.Mfix, a.C, a.U);
-  const int maxN = dim_max(a.ndim, a.Nfix, a.C, a.U);
-  if (maxM <= 0 || maxN <= 0 || batches <= 0) return;
-  const int tiles_m = (maxM + BM - 1) / BM;
-  const int tiles_n = (maxN + 127) / 128;   // = nct (PBG_SCORE_BN columns per tile)
-  const unsigned nwg = (unsigned)((int64_t)tiles_n * tiles_m * batches);
-  score_split_kernel<EPI_STORE, NPROD><<<nwg, 256, 0, s>>>(a, tiles_n, tiles_m);
 }
 
 void launch_to_bf16_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qh, int64_t qh_bs, uint16_t* qT,

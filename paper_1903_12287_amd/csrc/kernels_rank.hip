@@ -5,7 +5,8 @@
 // with f(s, r, d) = sim(g(x_s, theta_r), x_d) (Sec. 3.1).
 //
 // The candidate scores of a block of queries form one matrix product
-// S = Q . T^T against a candidate table T (MFMA, kernels_gemm.hip):
+// S = Q . T^T against a candidate table T, both as row pieces
+// (kernels_score.hip):
 //   destination side  Q = g(x_s) (dot) or its unit vector (cos); T = the
 //                     entity table (unit rows for cos);
 //   source side       Q = g*(x_d) (dot, the adjoint: <g(x), y> = <x, g*(y)>;
@@ -16,35 +17,47 @@
 //                     vector for cos) against the entity table, and its own
 //                     positive score sim(Q, x_s), which replaces the
 //                     destination side's in pos once that side is counted.
-// The count kernel then reads each query's row of S once, counts the
-// candidates at or above the positive score, and takes back the known
-// triples' candidates by reading the same stored scores, so that the count
-// and the filter correction agree element by element.
+// The product's epilogue compares each score with the query's positive one and
+// leaves a bit per score and the bits' number per row and 64 columns, 32 times
+// fewer bytes than the scores.  The count kernel adds those up and takes back
+// the known triples' candidates by testing the same bits, so that the count
+// and the filter correction agree element by element.  Measured at 50,000
+// queries against 15,000 entities, d = 400, both sides: 4.5 ms of kernels, 3.6 of
+// them the product, at 1.06 PFLOP/s (12.0 ms with stored float32 scores).
 #include <algorithm>
 
 #include "kernels.h"
+#include "pieces.h"
 #include "row_ops.h"
 
 namespace {
 
-// candidate tables: one wave per entity row
+// row i of a table or query block, written as pieces by the wave that holds it
+__device__ __forceinline__ void store_pieces(const StepGeom& g, const Row& x, RankRows t, int64_t i, bool cplx, int lane) {
+  const int e = pieces::scale_exponent(pieces::row_absmax(x));
+  pieces::store_row(x, pieces::scale_of(e), t.p + i * g.pld, g.d, g.dh, cplx, lane);
+  if (lane == 0) t.is[i] = pieces::inverse_scale_of(e);
+}
+
+// candidate tables: one wave per candidate row
 __global__ __launch_bounds__(256) void rank_tables_kernel(StepGeom g, const float* emb, const float* relp,
-                                                          const float* relT, int64_t n_ent, float* T0, float* T1) {
+                                                          const float* relT, const int32_t* cand, int64_t n_col,
+                                                          RankRows T0, RankRows T1) {
   __shared__ float stage[4][512];
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n_ent) return;
+  if (row >= n_col) return;
   const bool cplx = g.op == OP_COMPLEX;
   Row x;
-  row_load(x, emb + row * g.d, g.d, cplx, lane);
+  row_load(x, emb + (cand ? (int64_t)cand[row] : row) * g.d, g.d, cplx, lane);
   if (g.cmp == CMP_DOT) {
-    row_store(x, T0 + row * g.dp, g.d, g.dp, cplx, lane);
+    store_pieces(g, x, T0, row, cplx, lane);
     return;
   }
   Row xh = x;
   row_normalize(xh);
-  row_store(xh, T0 + row * g.dp, g.d, g.dp, cplx, lane);
-  if (T1) {
+  store_pieces(g, xh, T0, row, cplx, lane);
+  if (T1.p) {
     // cos with a non-identity operator: one relation, applied to every source candidate
     Row gx;
     if (g.op == OP_LINEAR) {
@@ -55,7 +68,7 @@ __global__ __launch_bounds__(256) void rank_tables_kernel(StepGeom g, const floa
       gx = op_forward(g.op, x, th);
     }
     row_normalize(gx);
-    row_store(gx, T1 + row * g.dp, g.d, g.dp, cplx, lane);
+    store_pieces(g, gx, T1, row, cplx, lane);
   }
 }
 
@@ -65,7 +78,7 @@ __global__ __launch_bounds__(256) void rank_tables_kernel(StepGeom g, const floa
 __global__ __launch_bounds__(256) void rank_queries_kernel(StepGeom g, const float* emb, const float* relp,
                                                            const float* relT, const int32_t* src,
                                                            const int32_t* rel, const int32_t* dst,
-                                                           int64_t e0, int rows, int side, float* Q,
+                                                           int64_t e0, int rows, int side, RankRows Q,
                                                            float* pos, float* bias) {
   __shared__ float stage[4][512];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -80,7 +93,6 @@ __global__ __launch_bounds__(256) void rank_queries_kernel(StepGeom g, const flo
   row_load(y, emb + (int64_t)dst[e] * d, d, cplx, lane);
   if (g.op != OP_IDENTITY && g.op != OP_LINEAR) row_load(th, relp + (int64_t)r * g.dr, d, cplx, lane);
   else row_zero(th);
-  float* qrow = Q + (int64_t)q * g.dp;
   if (side == 0) {
     Row gq;
     if (g.op == OP_LINEAR) mat_apply(gq, relT + (int64_t)r * d * d, x, stage[w], d, lane);   // A x
@@ -90,8 +102,11 @@ __global__ __launch_bounds__(256) void rank_queries_kernel(StepGeom g, const flo
       row_normalize(y);
     }
     const float p = row_dot(gq, y);
-    row_store(gq, qrow, d, g.dp, cplx, lane);
-    if (lane == 0) pos[e] = p;
+    store_pieces(g, gq, Q, q, cplx, lane);
+    if (lane == 0) {
+      pos[e] = p;
+      bias[q] = 0.0f;
+    }
   } else if (g.recip) {
     Row k;
     if (g.op == OP_LINEAR) {
@@ -107,7 +122,7 @@ __global__ __launch_bounds__(256) void rank_queries_kernel(StepGeom g, const flo
       row_normalize(x);
     }
     const float p1 = row_dot(k, x);
-    row_store(k, qrow, d, g.dp, cplx, lane);
+    store_pieces(g, k, Q, q, cplx, lane);
     if (lane == 0) {
       pos[e] = p1;
       bias[q] = 0.0f;
@@ -126,7 +141,7 @@ __global__ __launch_bounds__(256) void rank_queries_kernel(StepGeom g, const flo
     } else {
       k = op_adjoint(g.op, y, th);
     }
-    row_store(k, qrow, d, g.dp, cplx, lane);
+    store_pieces(g, k, Q, q, cplx, lane);
     if (lane == 0) bias[q] = bs;
   }
 }
@@ -143,62 +158,105 @@ __device__ int64_t lower_bound2(const int32_t* a, const int32_t* b, int64_t lo, 
   return lo;
 }
 
-// one wave per query row of the stored score block; column t is entity t,
-// or entity cand[t] when a candidate list is given (no filter then)
-__global__ __launch_bounds__(256) void rank_count_kernel(const float* S, int64_t ldS, int64_t n_ent,
-                                                         const int32_t* cand,
-                                                         int64_t e0, int rows, int side, int64_t n_eval,
-                                                         const int32_t* src, const int32_t* rel,
-                                                         const int32_t* dst, const float* pos,
-                                                         const float* bias, const int32_t* ka,
-                                                         const int32_t* kb, const int32_t* kc,
-                                                         int64_t n_known, int32_t* ranks) {
-  const int lane = threadIdx.x & 63;
-  const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (q >= rows) return;
-  const int64_t e = e0 + q;
-  const int32_t s = src[e], d = dst[e];
-  const int32_t r = rel ? rel[e] : 0;
-  const int32_t true_id = side == 0 ? d : s;
-  const float p = pos[e];
-  const float bq = side == 1 ? bias[q] : 0.0f;
-  const float* row = S + (int64_t)q * ldS;
-  uint32_t cnt = 0;
-  for (int64_t t = lane; t < n_ent; t += 64) {
-    const float v = row[t] + bq;
-    const int64_t id = cand ? (int64_t)cand[t] : t;
-    cnt += (v >= p && id != true_id) ? 1u : 0u;
-  }
-  // filter: candidates of known triples sharing (s, r) (side 0) or (d, r) (side 1);
-  // the known triples are sorted by (s, r, d) for side 0 and (d, r, s) for side 1
-  const int32_t k1 = side == 0 ? s : d;
-  int64_t lo = 0, hi = 0;
-  if (lane == 0 && n_known > 0) {
-    lo = lower_bound2(ka, kb, 0, n_known, k1, r);
-    hi = lower_bound2(ka, kb, lo, n_known, k1, r + 1);   // end of the (k1, r) group
-  }
-  lo = __shfl(lo, 0, 64);
-  hi = __shfl(hi, 0, 64);
-  for (int64_t i = lo + lane; i < hi; i += 64) {
-    const int32_t c = kc[i];
-    if (c == true_id || (i > lo && kc[i - 1] == c)) continue;   // the triple itself, duplicates
-    const float v = row[c] + bq;
-    if (v >= p) cnt -= 1u;
-  }
+// A workgroup ranks 64 queries.  The hit counts of four queries are one word:
+// sixteen threads cover the 64 queries, the sixteen groups of them share the
+// column blocks.  Each query's range of candidates to take back is searched by
+// a thread of its own (a search is a chain of loads); the ranges, a few long
+// ones among many short, are then one list that all threads share.  (A wave
+// per query, one query after another: 272 us a side at the sizes above.)
+__global__ __launch_bounds__(256) void rank_count_kernel(RankCount a) {
+  __shared__ uint32_t cnt[16][64];
+  __shared__ uint32_t back[64];      // candidates taken back
+  __shared__ int64_t range[2][64];   // first candidate and end of each query's range
+  __shared__ int64_t sum[64];        // lengths of the ranges up to and with each query's
+  __shared__ int32_t true_id[64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int q0 = blockIdx.x * 64;
+  {
+    const int grp = tid >> 4, c4 = 4 * (tid & 15);
+    const int64_t ldm = 16 * (int64_t)a.RB;   // a multiple of 256: the word lies inside
+    uint32_t n[4] = {0u, 0u, 0u, 0u};
+    for (int nb = grp; nb < a.n_blk; nb += 16) {
+      const uint32_t v = *(const uint32_t*)(a.hits + nb * ldm + q0 + c4);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-  if (lane == 0) ranks[(side == 0 ? 0 : n_eval) + e] = (int32_t)(1u + cnt);
+      for (int k = 0; k < 4; ++k) n[k] += (v >> (8 * k)) & 0xFFu;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cnt[grp][c4 + k] = n[k];
+  }
+  if (tid < 128) {
+    const int end = tid >> 6, q = q0 + lane;
+    int64_t at = 0;
+    if (q < a.rows) {
+      const int64_t e = a.e0 + q;
+      const int32_t s = a.src[e], d = a.dst[e];
+      if (end) true_id[lane] = a.side == 0 ? d : s;
+      if (a.cand)   // the true entity's places in the list
+        at = lower_bound2(a.cand, a.cand, 0, a.n_cand, a.side == 0 ? d : s, end ? INT32_MAX : INT32_MIN);
+      else if (a.n_known > 0)   // known triples sharing (s, r) (side 0) or (d, r) (side 1)
+        at = lower_bound2(a.ka, a.kb, 0, a.n_known, a.side == 0 ? s : d, (a.rel ? a.rel[e] : 0) + end);
+    }
+    range[end][lane] = at;
+  }
+  auto hit = [&](int i, int64_t col) {
+    const int q = q0 + i;
+    const uint32_t v = a.bits[((col >> 4) * a.RB + (q >> 4)) * 8 + ((q >> 3) & 1) * 4 + (q & 3)];
+    return (v >> (16 * ((q >> 2) & 1) + (int)(col & 15))) & 1u;
+  };
+  __syncthreads();
+  if (tid < 64) {
+    int64_t n = range[1][lane] - range[0][lane];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t v = __shfl_up(n, o, 64);
+      n += lane >= o ? v : 0;
+    }
+    sum[lane] = n;
+    // without a list the true entity's column is its id
+    back[lane] = !a.cand && q0 + lane < a.rows ? hit(lane, true_id[lane]) : 0u;
+  }
+  __syncthreads();
+  for (int64_t f = tid; f < sum[63]; f += 256) {
+    int i = 0;   // the first query whose sum exceeds f
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+      if (sum[i + o - 1] <= f) i += o;
+    const int64_t lo = range[0][i], k = range[1][i] - (sum[i] - f);
+    uint32_t h;
+    if (a.cand) {
+      h = hit(i, a.cand_at[k]);
+    } else {
+      const int32_t t = a.kc[k];
+      h = t != true_id[i] && (k == lo || a.kc[k - 1] != t) ? hit(i, t) : 0u;   // duplicates once
+    }
+    if (h) atomicAdd(&back[i], 1u);
+  }
+  __syncthreads();
+  if (tid < 64 && q0 + tid < a.rows) {
+    uint32_t c = 1u - back[tid];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c += cnt[k][tid];
+    a.ranks[(a.side == 0 ? 0 : a.n_eval) + a.e0 + q0 + tid] = (int32_t)c;
+  }
 }
 
-// MRR and Hits@10 over the ranks, in a fixed order (fp64)
-__global__ __launch_bounds__(256) void rank_metrics_kernel(const int32_t* ranks, int64_t n, double* out) {
+// MRR and Hits@10 over the ranks, in a fixed order (fp64): sums of
+// RANK_METRIC_BLOCKS workgroups, then theirs (as ranks == NULL).  (One
+// workgroup over 100,000 ranks: 124 us.)
+__global__ __launch_bounds__(256) void rank_metrics_kernel(const int32_t* ranks, int64_t n, const double* part,
+                                                           double* out) {
   __shared__ double s_rr[256];
   __shared__ double s_h[256];
   double rr = 0.0, h = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) {
-    const int32_t k = ranks[i];
-    rr += 1.0 / (double)k;
-    h += k <= 10 ? 1.0 : 0.0;
+  if (ranks) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+      const int32_t k = ranks[i];
+      rr += 1.0 / (double)k;
+      h += k <= 10 ? 1.0 : 0.0;
+    }
+  } else if ((int)threadIdx.x < RANK_METRIC_BLOCKS) {
+    rr = part[2 * threadIdx.x];
+    h = part[2 * threadIdx.x + 1];
   }
   s_rr[threadIdx.x] = rr;
   s_h[threadIdx.x] = h;
@@ -211,8 +269,9 @@ __global__ __launch_bounds__(256) void rank_metrics_kernel(const int32_t* ranks,
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    out[0] = n > 0 ? s_rr[0] / (double)n : 0.0;
-    out[1] = n > 0 ? s_h[0] / (double)n : 0.0;
+    const double inv = ranks || n <= 0 ? 1.0 : (double)n;
+    out[2 * blockIdx.x] = s_rr[0] / inv;
+    out[2 * blockIdx.x + 1] = s_h[0] / inv;
   }
 }
 
@@ -247,47 +306,28 @@ int grid_of(int64_t n) {
 
 }  // namespace
 
-void launch_rank_tables(const StepGeom& g, const float* emb, const float* relp, const float* relT, int64_t n_ent,
-                        float* T0, float* T1, hipStream_t s) {
-  if (n_ent <= 0) return;
-  rank_tables_kernel<<<(unsigned)((n_ent + 3) / 4), 256, 0, s>>>(g, emb, relp, relT, n_ent, T0, T1);
+void launch_rank_tables(const StepGeom& g, const float* emb, const float* relp, const float* relT,
+                        const int32_t* cand, int64_t n_col, RankRows T0, RankRows T1, hipStream_t s) {
+  if (n_col <= 0) return;
+  rank_tables_kernel<<<(unsigned)((n_col + 3) / 4), 256, 0, s>>>(g, emb, relp, relT, cand, n_col, T0, T1);
 }
 
 void launch_rank_queries(const StepGeom& g, const float* emb, const float* relp, const float* relT,
                          const int32_t* src, const int32_t* rel, const int32_t* dst, int64_t e0, int rows,
-                         int side, float* Q, float* pos, float* bias, hipStream_t s) {
+                         int side, RankRows Q, float* pos, float* bias, hipStream_t s) {
   if (rows <= 0) return;
   rank_queries_kernel<<<(rows + 3) / 4, 256, 0, s>>>(g, emb, relp, relT, src, rel, dst, e0, rows, side, Q,
                                                      pos, bias);
 }
 
-void launch_rank_count(const float* S, int64_t ldS, int64_t n_ent, const int32_t* cand, int64_t e0, int rows,
-                       int side, int64_t n_eval, const int32_t* src, const int32_t* rel, const int32_t* dst,
-                       const float* pos, const float* bias, const int32_t* ka, const int32_t* kb,
-                       const int32_t* kc, int64_t n_known, int32_t* ranks, hipStream_t s) {
-  if (rows <= 0) return;
-  rank_count_kernel<<<(rows + 3) / 4, 256, 0, s>>>(S, ldS, n_ent, cand, e0, rows, side, n_eval, src, rel, dst,
-                                                   pos, bias, ka, kb, kc, n_known, ranks);
-}
-
-// rows out[i] = T[idx[i]] of ld floats
-__global__ void gather_rows_kernel(const float* T, const int32_t* idx, int64_t n, int ld, float* out) {
-  const int64_t total = n * ld;
-  for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < total; k += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = k / ld;
-    out[k] = T[(int64_t)idx[i] * ld + (k - i * ld)];
-  }
-}
-
-void launch_gather_rows(const float* T, const int32_t* idx, int64_t n, int ld, float* out, hipStream_t s) {
-  if (n <= 0) return;
-  const int64_t total = n * ld;
-  const unsigned blocks = (unsigned)std::min<int64_t>((total + 255) / 256, 4096);
-  gather_rows_kernel<<<blocks, 256, 0, s>>>(T, idx, n, ld, out);
+void launch_rank_count(const RankCount& a, hipStream_t s) {
+  if (a.rows <= 0) return;
+  rank_count_kernel<<<(a.rows + 63) / 64, 256, 0, s>>>(a);
 }
 
 void launch_rank_metrics(const int32_t* ranks, int64_t n, double* out, hipStream_t s) {
-  rank_metrics_kernel<<<1, 256, 0, s>>>(ranks, n, out);
+  rank_metrics_kernel<<<RANK_METRIC_BLOCKS, 256, 0, s>>>(ranks, n, nullptr, out + 2);
+  rank_metrics_kernel<<<1, 256, 0, s>>>(nullptr, n, out + 2, out);
 }
 
 void launch_perm_keys(const int32_t* field, const uint32_t* perm, int64_t n, uint32_t* keys,

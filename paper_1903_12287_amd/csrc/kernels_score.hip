@@ -30,7 +30,7 @@ using namespace pieces;
 constexpr int BN = 128, BK = 32, STAGES = 3;
 
 struct ScoreTile {
-  int c, side, tn, m0, n0, M, N, Cc;
+  int c, side, tm, tn, m0, n0, M, N, Cc;
   int64_t nrow0;   // candidate row of column 0
 };
 
@@ -52,8 +52,21 @@ __device__ __forceinline__ int divide(Divider v, int x, int& rest) {
 // tiles of a launch: rows of tiles, column tiles of side 0 and of side 1
 struct TileGrid {
   int per0, total;      // side 0's tiles of a chunk, all tiles
+  int tiles_m;
+  uint32_t band_m;      // reciprocal of four rows of tiles (Divider)
   Divider chunk, tn0, tn1;
 };
+
+// A plain product's tiles go in bands of four tile rows, column by column: the
+// 32 tiles an XCD works on at a time take 4 panels of A and 8 of B (3.5 MB at
+// 400 elements, its L2 4 MB) and not 1 and 32 (7.3 MB).
+__device__ __forceinline__ void band_tile(const TileGrid& tg, int r, int& tm, int& tn) {
+  int rest;
+  const int band = divide(Divider{4 * tg.tn0.d, tg.band_m}, r, rest);
+  const int h = min(4, tg.tiles_m - 4 * band);
+  tn = rest / h;
+  tm = 4 * band + rest - tn * h;
+}
 
 // The tile `id` of the launch; false: nothing to compute.  With share, side 0
 // spans all candidates and side 1 the uniform ones only.
@@ -62,10 +75,10 @@ __device__ __forceinline__ bool score_tile(const ScoreArgs& a, const TileGrid& t
   int r;
   t.c = divide(tg.chunk, id, r);
   t.side = r >= tg.per0 ? 1 : 0;
-  int tm;
-  if (t.side) tm = divide(tg.tn1, r - tg.per0, t.tn);
-  else tm = divide(tg.tn0, r, t.tn);
-  t.m0 = tm * BM;
+  if (t.side) t.tm = divide(tg.tn1, r - tg.per0, t.tn);
+  else if (a.Mfix > 0) band_tile(tg, r, t.tm, t.tn);
+  else t.tm = divide(tg.tn0, r, t.tn);
+  t.m0 = t.tm * BM;
   t.n0 = t.tn * BN;
   t.nrow0 = 0;
   if (a.Mfix > 0) {
@@ -109,12 +122,13 @@ struct SliceLoader {
     w = w_;
     kq = 8 * (kc_lane_group(lane) & 3);
     dh = a.dh;
-    ra = make_rsrc(a.A + t.c * a.a_cs + t.side * a.a_ss);
-    rb = make_rsrc(a.B + t.c * a.b_cs + t.side * a.b_ss + t.nrow0 * a.ld);
+    // offsets count from the tile's first row: operands of any number of rows
+    ra = make_rsrc(a.A + t.c * a.a_cs + t.side * a.a_ss + (int64_t)t.m0 * a.ld);
+    rb = make_rsrc(a.B + t.c * a.b_cs + t.side * a.b_ss + (t.nrow0 + t.n0) * a.ld);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) oa[j] = kc_offset(w + 2 * WR * j, a.ld, t.m0, t.M, lane);
+    for (int j = 0; j < 4; ++j) oa[j] = kc_offset(w + 2 * WR * j, a.ld, 0, t.M - t.m0, lane);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) ob[j] = kc_offset(w + 2 * WR * j, a.ld, t.n0, t.N, lane);
+    for (int j = 0; j < NB; ++j) ob[j] = kc_offset(w + 2 * WR * j, a.ld, 0, t.N - t.n0, lane);
   }
   __device__ __forceinline__ void none() {
 #pragma unroll
@@ -199,6 +213,23 @@ __device__ __forceinline__ void mask_tile(const ScoreTile& t, v4f (&acc)[4][4], 
   }
 }
 
+// lane (i, j, r)'s words of a wave's block of hits: its place in a bit plane,
+// and the hits of row 16 (l16 / 4) + 4 g + l16 % 4 over the 64 columns
+__device__ __forceinline__ int64_t hit_words(const ScoreArgs& a, const ScoreTile& t, int wm, int wn, int lane) {
+  const int rb = ((t.m0 + 64 * wm) >> 4) + (lane >> 4), cb = ((t.n0 + 64 * wn) >> 4) + ((lane >> 2) & 3);
+  return ((int64_t)cb * a.RB + rb) * 8 + (lane & 3);
+}
+__device__ __forceinline__ uint32_t row_hits(uint32_t wlo, uint32_t whi, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  // the four fields of the lane, then over the four j
+  uint32_t n4 = __builtin_popcount(wlo & 0xFFFFu) | (__builtin_popcount(wlo >> 16) << 8) |
+                (__builtin_popcount(whi & 0xFFFFu) << 16) | (__builtin_popcount(whi >> 16) << 24);
+  n4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n4, 0x124, 0xF, 0xF, false);   // row_ror:4
+  n4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n4, 0x128, 0xF, 0xF, false);   // row_ror:8
+  const uint32_t n = (uint32_t)__shfl((int)n4, 16 * (l16 >> 2) + (l16 & 3), PBG_WAVE);
+  return (n >> (8 * g)) & 0xFFu;
+}
+
 // Ranking loss of a tile: hit = [s > -(margin - p + bias)].  The ballot of an
 // accumulator register holds 16 columns of four rows; the 64 ballots of the
 // wave's block are deposited one per lane and stored as two 4-byte words a
@@ -267,26 +298,17 @@ __device__ __forceinline__ void bits_epilogue(const ScoreArgs& a, const ScoreTil
       mine = l16 == 4 * i + r ? s : mine;   // every lane of the group holds the row's sum
     }
   }
-  // lane (i, j, r): words of block (row block i, column block j)
   {
-    const int i = lane >> 4, j = (lane >> 2) & 3, r = lane & 3;
-    const int rb = ((t.m0 + 64 * wm) >> 4) + i, cb = ((t.n0 + 64 * wn) >> 4) + j;
-    uint32_t* d = a.bits0 + t.c * a.bits_cs + t.side * a.bits_ss + ((int64_t)cb * a.RB + rb) * 8 + r;
+    const int64_t at = hit_words(a, t, wm, wn, lane);
+    uint32_t* d = a.bits0 + t.c * a.bits_cs + t.side * a.bits_ss + at;
     d[0] = wlo;
     d[4] = whi;
     if (SHARED) {
-      uint32_t* d1 = a.bits1 + t.c * a.bits1_cs + ((int64_t)cb * a.RB + rb) * 8 + r;
+      uint32_t* d1 = a.bits1 + t.c * a.bits1_cs + at;
       d1[0] = xlo;
       d1[4] = xhi;
     }
-    // hits per row: the four fields of the lane, then over the four j
-    uint32_t n4 = __builtin_popcount(wlo & 0xFFFFu) | (__builtin_popcount(wlo >> 16) << 8) |
-                  (__builtin_popcount(whi & 0xFFFFu) << 16) | (__builtin_popcount(whi >> 16) << 24);
-    n4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n4, 0x124, 0xF, 0xF, false);   // row_ror:4
-    n4 += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)n4, 0x128, 0xF, 0xF, false);   // row_ror:8
-    // this lane's row, 16 i + 4 g + r of the wave's with i = l16 / 4, r = l16 % 4
-    const uint32_t n = (uint32_t)__shfl((int)n4, 16 * (l16 >> 2) + (l16 & 3), PBG_WAVE);
-    const float c = (float)((n >> (8 * g)) & 0xFFu);
+    const float c = (float)row_hits(wlo, whi, lane);
     const int row = 64 * wm + 16 * (l16 >> 2) + 4 * g + (l16 & 3), m = t.m0 + row;
     const int nb = t.n0 / 64 + wn;   // column block of 64
     if (m < t.M && 64 * nb < t.N) {
@@ -315,6 +337,49 @@ __device__ __forceinline__ void bits_epilogue(const ScoreArgs& a, const ScoreTil
       *rp = make_float2(fmaf(sm.thr1[64 * wn + lane], mc, ms * a.unscale), mc);
     }
   }
+}
+
+__device__ __forceinline__ int power_of(float scale) { return (int)(__float_as_uint(scale) >> 23) - 127; }
+
+// Candidates at or above the positive score, [s + bias >= p], as bits (the
+// layout of bits_epilogue; columns past N are 0) and their number per row and
+// 64 columns.  The scales go through the exponent, exact for rows of any
+// magnitude.
+template <int WR>
+__device__ __forceinline__ void rank_epilogue(const ScoreArgs& a, const ScoreTile& t, v4f (&acc)[4][4],
+                                              const ScoreSmem<WR>& sm, int wm, int wn, int lane) {
+  const int l16 = lane & 15, g = lane >> 4;
+  uint32_t wlo = 0, whi = 0;
+  int ce[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) ce[j] = power_of(sm.cscl[64 * wn + 16 * j + l16]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int mb = 64 * wm + 16 * i + 4 * g;
+    const v4f scl = *(const v4f*)&sm.scl[mb];
+    const v4f bias = *(const v4f*)&sm.nthr[mb];
+    const v4f p = *(const v4f*)&sm.thr[mb];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const bool in = t.n0 + 64 * wn + 16 * j + l16 < t.N;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float s = ldexpf(acc[i][j][r], ce[j] + power_of(scl[r])) + bias[r];
+        uint64_t mk = __ballot(in && s >= p[r]);
+        __asm__ volatile("" : "+s"(mk));
+        const int idx = (i * 4 + j) * 4 + r;
+        wlo = writelane((uint32_t)mk, idx, wlo);
+        whi = writelane((uint32_t)(mk >> 32), idx, whi);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  uint32_t* d = a.bits0 + hit_words(a, t, wm, wn, lane);
+  d[0] = wlo;
+  d[4] = whi;
+  const uint32_t c = row_hits(wlo, whi, lane);
+  const int m = t.m0 + 64 * wm + 16 * (l16 >> 2) + 4 * g + (l16 & 3), nb = t.n0 / 64 + wn;
+  if (64 * nb < t.N) a.hits[(int64_t)nb * (16 * a.RB) + m] = (uint8_t)c;   // rows past M: never read
 }
 
 // Logistic: dS = sigmoid(s) / K and the row's losses softplus(s) / K; softmax:
@@ -470,13 +535,14 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     const bool col = tid >= BM;
     const int own = col ? tid - BM : tid;
     float p = 0.0f, bias = 0.0f, scl = 1.0f;
+    if (EPI == EPI_RANK) p = a.pos[cur.m0 + own % BM];
     if (EPI == EPI_LOSS_BITS)
       p = a.pos[(int64_t)(cur.c * a.pos_sides + (a.pos_sides - 1) * cur.side) * a.C +
                 (col ? min(cur.n0, a.C) + (own & (BN - 1)) : cur.m0 + own)];
     if (SCALED)
       scl = col ? a.ib[cur.c * a.ib_cs + cur.side * a.ib_ss + cur.nrow0 + cur.n0 + (own & (BN - 1))]
                 : a.ia[cur.c * a.ia_cs + cur.side * a.ia_ss + cur.m0 + own];
-    if (SCALED && EPI != EPI_STORE && a.bias && cur.side == 1)
+    if (SCALED && EPI != EPI_STORE && a.bias && (EPI == EPI_RANK || cur.side == 1))
       bias = a.bias[(int64_t)cur.c * a.C + (col ? 0 : cur.m0 + own)];
     v4f acc[4][4];
 #pragma unroll
@@ -501,6 +567,10 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
       if (!col) {
         sm.scl[own] = SCALED ? scl : a.unscale;
         if (EPI == EPI_LOSS || EPI == EPI_SOFTMAX_EXP) sm.thr[own] = bias;
+        if (EPI == EPI_RANK) {
+          sm.thr[own] = p;
+          sm.nthr[own] = bias;
+        }
         if (EPI == EPI_LOSS_BITS) {   // the scale's inverse is exact: a power of two
           sm.thr[own] = thr;
           sm.nthr[own] = cur.m0 + own < cur.M ? -thr * (SCALED ? __builtin_amdgcn_rcpf(scl) : a.iunscale) : INFINITY;
@@ -539,10 +609,12 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     if (EPI == EPI_STORE) {
       if (shared) store_epilogue<true, WR>(a, cur, acc, sm, wm, wn, lane);
       else store_epilogue<false, WR>(a, cur, acc, sm, wm, wn, lane);
+    } else if (EPI == EPI_RANK) {
+      rank_epilogue<WR>(a, cur, acc, sm, wm, wn, lane);
     } else {
       const bool diag = cur.nrow0 == 0 && cur.m0 < cur.n0 + BN && cur.n0 < cur.m0 + BM;
       if (diag || cur.n0 + BN > cur.N || (shared && cur.m0 + BM > cur.M)) mask_tile(cur, acc, wm, wn, lane);
-      if (EPI != EPI_LOSS_BITS) value_epilogue<EPI, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
+      if (EPI == EPI_LOSS || EPI == EPI_SOFTMAX_EXP) value_epilogue<EPI, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
       else if (!SCALED && shared) bits_epilogue<true, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
       else bits_epilogue<false, SCALED, WR>(a, cur, acc, sm, wm, wn, lane);
     }
@@ -563,19 +635,25 @@ void launch_wr(const ScoreArgs& a, int batches, hipStream_t s) {
   auto divider = [](int d) {
     return Divider{(uint32_t)std::max(d, 1), d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d)};
   };
-  const TileGrid tg{tiles_m * tn0, (int)total, divider(tiles_m * (tn0 + tn1)), divider(tn0), divider(tn1)};
+  const TileGrid tg{tiles_m * tn0, (int)total, tiles_m, divider(4 * tn0).m, divider(tiles_m * (tn0 + tn1)), divider(tn0), divider(tn1)};
   score_kernel<EPI, SCALED, WR><<<grid, 128 * WR, 0, s>>>(a, tg);
+}
+
+// four waves where no chunk fills more than their 128 rows.  Not by the
+// average: relation-grouped chunks of about 70 edges (500 uniform negatives,
+// d = 200) took 135 us with 128-row tiles, 100 us with 256-row ones, whose
+// eight waves keep twice the loads in flight.
+bool few(const ScoreArgs& a) { return (a.Mfix > 0 ? a.Mfix : a.C) <= 128; }
+
+template <int EPI, bool SCALED>
+void launch_few(const ScoreArgs& a, int batches, hipStream_t s) {
+  few(a) ? launch_wr<EPI, SCALED, 2>(a, batches, s) : launch_wr<EPI, SCALED, 4>(a, batches, s);
 }
 
 template <int EPI>
 void launch_t(const ScoreArgs& a, int batches, hipStream_t s) {
-  // four waves where no chunk fills more than their 128 rows.  Not by the
-  // average: relation-grouped chunks of about 70 edges (500 uniform negatives,
-  // d = 200) took 135 us with 128-row tiles, 100 us with 256-row ones, whose
-  // eight waves keep twice the loads in flight.
-  const bool few = (a.Mfix > 0 ? a.Mfix : a.C) <= 128;
-  if (a.ia) few ? launch_wr<EPI, true, 2>(a, batches, s) : launch_wr<EPI, true, 4>(a, batches, s);
-  else few ? launch_wr<EPI, false, 2>(a, batches, s) : launch_wr<EPI, false, 4>(a, batches, s);
+  if (a.ia) launch_few<EPI, true>(a, batches, s);
+  else launch_few<EPI, false>(a, batches, s);
 }
 
 }  // namespace
@@ -585,5 +663,6 @@ void launch_score(const ScoreArgs& a, int epi, int nchunks, hipStream_t s) {
   if (epi == EPI_LOSS_BITS) launch_t<EPI_LOSS_BITS>(a, nchunks, s);
   else if (epi == EPI_LOSS) launch_t<EPI_LOSS>(a, nchunks, s);
   else if (epi == EPI_SOFTMAX_EXP) launch_t<EPI_SOFTMAX_EXP>(a, nchunks, s);
+  else if (epi == EPI_RANK) launch_few<EPI_RANK, true>(a, nchunks, s);
   else launch_t<EPI_STORE>(a, nchunks, s);
 }

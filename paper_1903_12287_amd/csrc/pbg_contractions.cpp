@@ -36,7 +36,6 @@ static void run_backward_h(const StepGeom& g, const StepBufs& b, const uint16_t*
     qa.lda = Npb;
   }
   qa.B = nT;
-  qa.planes = 1;
   qa.Cm = b.dq;
   qa.b_cs = 2ll * dpb * Npb;
   qa.b_ss = (int64_t)dpb * Npb;

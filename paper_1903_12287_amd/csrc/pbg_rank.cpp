@@ -4,11 +4,12 @@
 //
 // Sequence on the compute stream: range checks of every id (nothing is
 // written on an error); the candidate tables (for a candidate list, its rows
-// gathered in list order); the known triples sorted twice
+// in list order, and the list sorted); the known triples sorted twice
 // (by (s, r, d) for destination-side filtering, by (d, r, s) for source-side
 // filtering) with three stable radix passes each; then, per side and block of
-// queries, the queries, the score block S = Q . T^T on the matrix cores and
-// the count kernel; finally the fp64 metric reduction.  Workspace is
+// queries, the queries, the product S = Q . T^T on the matrix cores, which
+// leaves the candidates at or above the positive score as bits, and the count
+// kernel; finally the fp64 metric reduction.  Workspace is
 // allocated for the call and released before it returns.
 #include <hip/hip_runtime.h>
 
@@ -21,21 +22,31 @@
 
 namespace {
 
+// The call's workspace, one allocation: sizes are collected first, the
+// pointers handed out once it is there.  (One allocation a buffer, a dozen of
+// them with a 1 GiB score block, took longer than the kernels.)
 struct CallBuf {
-  std::vector<void*> ptrs;
-  bool failed = false;
-  void* get(size_t bytes) {
+  char* base = nullptr;
+  size_t bytes = 0;
+  std::vector<std::pair<void**, size_t>> wanted;
+  template <typename T>
+  void want(T*& p, size_t n) {
+    p = nullptr;
+    wanted.emplace_back((void**)&p, bytes);
+    bytes += (std::max<size_t>(n, 1) * sizeof(T) + 255) / 256 * 256;
+  }
+  bool allocate() {
     void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(bytes, 16)) != hipSuccess) {
+    if (hipMalloc(&p, bytes) != hipSuccess) {
       (void)hipGetLastError();
-      failed = true;
-      return nullptr;
+      return false;
     }
-    ptrs.push_back(p);
-    return p;
+    base = (char*)p;
+    for (auto& w : wanted) *w.first = base + w.second;
+    return true;
   }
   ~CallBuf() {
-    for (void* p : ptrs) (void)hipFree(p);
+    if (base) (void)hipFree(base);
   }
 };
 
@@ -96,44 +107,57 @@ pbg_status rank_impl(pbg_ctx* ctx, const char* name, const int32_t* src, const i
   hipStream_t s = ctx->cs;
   const int64_t n_ent = ctx->n;
   const int64_t n_col = cand ? n_cand : n_ent;   // score columns
-  const int d = ctx->d, dp = (d + 3) / 4 * 4;
+  const int d = ctx->d;
   const bool linear = ctx->op == OP_LINEAR;
   // cos with an operator applies it to every source candidate, except with
   // reciprocal predicates (the source side's query carries theta_{r+R})
   const bool sep_src_table = ctx->cmp == CMP_COS && ctx->op != OP_IDENTITY && !recip;
 
-  // query block: the score block stays near 1 GiB
-  int64_t qb = ((int64_t)1 << 28) / std::max<int64_t>(n_col, 1);
-  qb = std::max<int64_t>(128, qb / 128 * 128);
-  qb = std::min<int64_t>(qb, (n + 127) / 128 * 128);
+  // query block: 2^31 scores, 256 MiB of bits, and 2^18 rows at most
+  const int64_t ncol_pad = (n_col + 127) / 128 * 128;
+  int64_t qb = ((int64_t)1 << 31) / ncol_pad;
+  qb = std::max<int64_t>(256, std::min<int64_t>(qb, (int64_t)1 << 18) / 256 * 256);
+  qb = std::min<int64_t>(qb, (n + 255) / 256 * 256);
+  const int pld = (d + 31) / 32 * 64, n_blk = (int)((n_col + 63) / 64);
 
   CallBuf buf;
-  uint32_t* flag = (uint32_t*)buf.get(16);
-  float* T0 = (float*)buf.get((size_t)n_ent * dp * 4);
-  float* T1 = sep_src_table ? (float*)buf.get((size_t)n_ent * dp * 4) : nullptr;
-  float* relT = linear ? (float*)buf.get((size_t)relation_rows(ctx) * d * d * 4) : nullptr;
-  float* pos = (float*)buf.get((size_t)n * 4);
-  float* bias = (float*)buf.get((size_t)qb * 4);
-  float* Q = (float*)buf.get((size_t)qb * dp * 4);
-  float* S = (float*)buf.get((size_t)qb * n_col * 4);
-  float* C0 = cand ? (float*)buf.get((size_t)n_cand * dp * 4) : nullptr;
-  float* C1 = cand && sep_src_table ? (float*)buf.get((size_t)n_cand * dp * 4) : nullptr;
-  double* metrics = (double*)buf.get(16);
+  uint32_t *flag, *bits, *keys = nullptr, *vals = nullptr;
+  uint8_t* hits;
+  float *relT = nullptr, *pos, *bias;
+  double* metrics;
+  RankRows T0, T1{nullptr, nullptr}, Q;
   int32_t* kx[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-  uint32_t *keys = nullptr, *vals = nullptr;
   SortWork w;
   memset(&w, 0, sizeof(w));
-  if (n_known > 0) {
-    for (auto& p : kx) p = (int32_t*)buf.get((size_t)n_known * 4);
-    keys = (uint32_t*)buf.get((size_t)n_known * 4);
-    vals = (uint32_t*)buf.get((size_t)n_known * 4);
-    w.keys_alt = (uint32_t*)buf.get((size_t)n_known * 4);
-    w.vals_alt = (uint32_t*)buf.get((size_t)n_known * 4);
-    w.hist = (uint32_t*)buf.get((size_t)radix_hist_entries(n_known) * 4);
-    w.scan_tmp = (uint32_t*)buf.get((size_t)radix_scan_tmp_entries(n_known) * 4);
-    w.max_n = (int)n_known;
+  // the score kernel reads the per-row and per-column values of whole tiles
+  buf.want(flag, 4);
+  buf.want(T0.p, (size_t)n_col * pld);
+  buf.want(T0.is, (size_t)ncol_pad);
+  if (sep_src_table) {
+    buf.want(T1.p, (size_t)n_col * pld);
+    buf.want(T1.is, (size_t)ncol_pad);
   }
-  if (buf.failed) return set_err(ctx, PBG_ERR_OUT_OF_MEMORY, "rank-eval workspace could not be allocated");
+  if (linear) buf.want(relT, (size_t)relation_rows(ctx) * d * d);
+  buf.want(pos, (size_t)n + 256);
+  buf.want(bias, (size_t)qb);
+  buf.want(Q.p, (size_t)qb * pld);
+  buf.want(Q.is, (size_t)qb);
+  buf.want(bits, (size_t)(qb / 16) * (ncol_pad / 16) * 8);
+  buf.want(hits, (size_t)n_blk * qb);
+  buf.want(metrics, 2 + 2 * RANK_METRIC_BLOCKS);
+  const int64_t n_sort = cand ? n_cand : n_known;   // the list or the known triples, sorted
+  if (n_sort > 0) {
+    if (!cand)
+      for (auto& p : kx) buf.want(p, (size_t)n_known);
+    buf.want(keys, (size_t)n_sort);
+    buf.want(vals, (size_t)n_sort);
+    buf.want(w.keys_alt, (size_t)n_sort);
+    buf.want(w.vals_alt, (size_t)n_sort);
+    buf.want(w.hist, (size_t)radix_hist_entries(n_sort));
+    buf.want(w.scan_tmp, (size_t)radix_scan_tmp_entries(n_sort));
+    w.max_n = (int)n_sort;
+  }
+  if (!buf.allocate()) return set_err(ctx, PBG_ERR_OUT_OF_MEMORY, "rank-eval workspace could not be allocated");
 
   hipError_t e = hipMemsetAsync(flag, 0, 4, s);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipMemsetAsync");
@@ -154,22 +178,21 @@ pbg_status rank_impl(pbg_ctx* ctx, const char* name, const int32_t* src, const i
   StepGeom g;
   memset(&g, 0, sizeof(g));
   g.d = d;
-  g.dp = dp;
+  g.dh = (d + 7) / 8 * 8;
+  g.pld = pld;
   g.dr = ctx->dr;
   g.op = ctx->op;
   g.cmp = ctx->cmp;
   g.recip = recip ? 1 : 0;
   g.R = ctx->R;
   if (linear) launch_transpose_rel(ctx->relp, relT, relation_rows(ctx), d, s);
-  launch_rank_tables(g, pt.emb, ctx->relp, relT, n_ent, T0, T1, s);
-  if (cand) {
-    // the candidates' rows of the tables, in candidate order
-    launch_gather_rows(T0, cand, n_cand, dp, C0, s);
-    if (T1) launch_gather_rows(T1, cand, n_cand, dp, C1, s);
-  }
+  launch_rank_tables(g, pt.emb, ctx->relp, relT, cand, n_col, T0, T1, s);
 
   const int ebits = bits_of((uint64_t)n_ent - 1), rbits = bits_of((uint64_t)ctx->R - 1);
-  if (n_known > 0) {
+  if (cand) {   // positions of each entity in the list
+    launch_perm_keys(cand, nullptr, n_cand, keys, vals, s);
+    launch_radix_sort(keys, vals, (int)n_cand, ebits, w, s);
+  } else if (n_known > 0) {
     // destination side: groups (s, r), candidates d; source side: groups (d, r), candidates s
     sort_known(known_src, ebits, known_rel, rbits, known_dst, ebits, n_known, keys, vals, w, kx[0], kx[1],
                kx[2], s);
@@ -178,31 +201,49 @@ pbg_status rank_impl(pbg_ctx* ctx, const char* name, const int32_t* src, const i
   }
 
   for (int side = 0; side < 2; ++side) {
-    const float* T = cand ? (side == 1 && C1 ? C1 : C0) : (side == 1 && T1 ? T1 : T0);
+    const RankRows T = side == 1 && T1.p ? T1 : T0;
     for (int64_t e0 = 0; e0 < n; e0 += qb) {
       const int rows = (int)std::min<int64_t>(qb, n - e0);
       launch_rank_queries(g, pt.emb, ctx->relp, relT, src, rel, dst, e0, rows, side, Q, pos, bias, s);
-      // candidate scores S = Q . T^T, float32 operands as exact bf16 pieces
-      GemmArgsH a;
+      ScoreArgs a;
       memset(&a, 0, sizeof(a));
-      a.Af = Q;
-      a.Bf = T;
-      a.Cm = S;
-      a.lda = dp;
-      a.ldb = dp;
-      a.ldc = (int)n_col;
-      a.mdim = DIM_FIXED;
+      a.A = Q.p;
+      a.B = T.p;
+      a.dh = g.dh;
+      a.ld = pld;
+      a.ia = Q.is;
+      a.ib = T.is;
       a.Mfix = rows;
-      a.ndim = DIM_FIXED;
       a.Nfix = (int)n_col;
-      a.kdim = DIM_FIXED;
-      a.Kfix = dp;
-      a.C = 1;
       a.nsides = 1;
-      launch_score_split(a, EPI_STORE, 1, s);
-      launch_rank_count(S, n_col, n_col, cand, e0, rows, side, n, src, rel, dst, pos, bias,
-                        side == 0 ? kx[0] : kx[3], side == 0 ? kx[1] : kx[4], side == 0 ? kx[2] : kx[5],
-                        n_known, ranks, s);
+      a.pos = pos + e0;
+      a.bias = bias;
+      a.bits0 = bits;
+      a.RB = (int)(qb / 16);
+      a.hits = hits;
+      launch_score(a, EPI_RANK, 1, s);
+      RankCount c;
+      memset(&c, 0, sizeof(c));
+      c.bits = bits;
+      c.hits = hits;
+      c.RB = a.RB;
+      c.n_blk = n_blk;
+      c.e0 = e0;
+      c.n_eval = n;
+      c.rows = rows;
+      c.side = side;
+      c.src = src;
+      c.rel = rel;
+      c.dst = dst;
+      c.ka = kx[3 * side];
+      c.kb = kx[3 * side + 1];
+      c.kc = kx[3 * side + 2];
+      c.n_known = n_known;
+      c.cand = cand ? (const int32_t*)keys : nullptr;
+      c.cand_at = (const int32_t*)vals;
+      c.n_cand = n_cand;
+      c.ranks = ranks;
+      launch_rank_count(c, s);
     }
   }
   launch_rank_metrics(ranks, 2 * n, metrics, s);
