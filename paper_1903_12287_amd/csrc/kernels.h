@@ -299,7 +299,7 @@ int64_t exclusive_scan_tmp_entries(int64_t n);
 int64_t bucket_direct_units(int64_t n);
 void launch_bucket_count(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t n_ent,
                          int32_t n_rel, int64_t ps, int P, uint32_t* hist, uint32_t* flag, hipStream_t s);
-void launch_bucket_scatter(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t ps,
+void launch_bucket_scatter(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t n_ent, int64_t ps,
                            int P, const uint32_t* start, int64_t* offsets, int32_t* src_local,
                            int32_t* rel_out, int32_t* dst_local, hipStream_t s);
 void launch_bucket_keys(const int64_t* src, const int64_t* dst, int64_t n, int64_t ps, int P,

@@ -4,6 +4,8 @@
 // sort of (b, position) pairs, so the input order survives inside a bucket;
 // bucket offsets are the lower bounds of each b in the sorted keys, and the
 // local ids are gathered through the sorted positions.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace {
@@ -97,12 +99,37 @@ __global__ void typed_bucket_gather_kernel(const uint32_t* vals, const int64_t* 
 // positions, so the global writes are contiguous runs.
 constexpr int BT_WAVES = BUCKET_TILE / 512;     // waves per tile, 512 edges (8 rounds) each
 
-// part(v) = floor(v / ps) through a double reciprocal, corrected to exact
-__device__ __forceinline__ int64_t part_of(int64_t v, int64_t ps, double inv_ps) {
-  int64_t q = (int64_t)((double)v * inv_ps);
-  if (q * ps > v) --q;
-  else if ((q + 1) * ps <= v) ++q;
+// The partition v / ps and the local id v % ps.  Ids below 2^32: the high word
+// of v times floor(2^32 / ps) is the quotient or one less, six instructions
+// in place of some forty (the count's time was vector instructions, not memory:
+// at 69 million edges in 64 buckets 286 us, now 219 to 244 us).
+// Wider ids: through a double reciprocal, corrected to exact.
+struct PartDivider {
+  int64_t ps;
+  double inv_ps;
+  uint32_t m;
+};
+template <bool NARROW>
+__device__ __forceinline__ uint32_t part_of(int64_t v, const PartDivider& p, int32_t& local);
+template <>
+__device__ __forceinline__ uint32_t part_of<true>(int64_t v, const PartDivider& p, int32_t& local) {
+  const uint32_t x = (uint32_t)v, ps = (uint32_t)p.ps;
+  uint32_t q = __umulhi(x, p.m);
+  uint32_t r = x - q * ps;
+  if (r >= ps) {
+    ++q;
+    r -= ps;
+  }
+  local = (int32_t)r;
   return q;
+}
+template <>
+__device__ __forceinline__ uint32_t part_of<false>(int64_t v, const PartDivider& p, int32_t& local) {
+  int64_t q = (int64_t)((double)v * p.inv_ps);
+  if (q * p.ps > v) --q;
+  else if ((q + 1) * p.ps <= v) ++q;
+  local = (int32_t)(v - q * p.ps);
+  return (uint32_t)q;
 }
 
 // lanes of this wave whose key equals mine (keys < 2^bits, active lanes only)
@@ -115,10 +142,11 @@ __device__ __forceinline__ uint64_t match_key(uint32_t key, int bits, uint64_t a
   return m;
 }
 
+template <bool NARROW>
 __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_count_kernel(const int64_t* src, const int64_t* dst,
                                                                        const int32_t* rel, int64_t n,
-                                                                       int64_t n_ent, int32_t n_rel, int64_t ps,
-                                                                       double inv_ps, int P, int bits,
+                                                                       int64_t n_ent, int32_t n_rel, PartDivider pd,
+                                                                       int P, int bits,
                                                                        int64_t tiles, uint32_t* hist,
                                                                        uint32_t* flag) {
   __shared__ uint32_t cnt[BUCKET_DIRECT_MAX];
@@ -127,40 +155,49 @@ __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_count_kernel(const int
   const int64_t tile = blockIdx.x;
   for (int b = threadIdx.x; b < nb; b += blockDim.x) cnt[b] = 0u;
   __syncthreads();
-  const int64_t e0 = tile * BUCKET_TILE + (int64_t)w * 512, e1 = min(n, e0 + 512);
+  const int64_t e0 = tile * BUCKET_TILE + (int64_t)w * 512;
   uint32_t bad = 0u;
-  for (int64_t r = e0; r < e1; r += 64) {
-    const int64_t i = r + lane;
-    const bool act = i < e1;
-    uint32_t key = 0u;
-    if (act) {
-      const int64_t s = src[i], d = dst[i];
-      if (s < 0 || s >= n_ent) bad |= 1u;
-      if (d < 0 || d >= n_ent) bad |= 2u;
-      if (rel) {
-        const int32_t q = rel[i];
-        if (q < 0 || q >= n_rel) bad |= 4u;
-      }
-      const int64_t pi = part_of(min(max(s, (int64_t)0), n_ent - 1), ps, inv_ps);
-      const int64_t pj = part_of(min(max(d, (int64_t)0), n_ent - 1), ps, inv_ps);
-      key = (uint32_t)(pi * P + pj);
+  // half of the wave's ids on their way at a time
+#pragma unroll
+  for (int h = 0; h < 8; h += 4) {
+    int64_t s[4], d[4];
+    int32_t q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = e0 + 64 * (h + u) + lane;
+      s[u] = i < n ? src[i] : 0;
+      d[u] = i < n ? dst[i] : 0;
+      q[u] = rel && i < n ? rel[i] : 0;
     }
-    const uint64_t m = match_key(key, bits, __ballot(act));
-    // the lowest lane of each key adds the key's count
-    if (act && (m & ((1ull << lane) - 1ull)) == 0ull) atomicAdd(&cnt[key], (uint32_t)__popcll(m));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool act = e0 + 64 * (h + u) + lane < n;
+      // 0 past the edges: in range; an id that is not counts as 0
+      const bool bs = (uint64_t)s[u] >= (uint64_t)n_ent, bd = (uint64_t)d[u] >= (uint64_t)n_ent;
+      bad |= (bs ? 1u : 0u) | (bd ? 2u : 0u) | (q[u] < 0 || q[u] >= n_rel ? 4u : 0u);
+      int32_t local;
+      const uint32_t key = part_of<NARROW>(bs ? 0 : s[u], pd, local) * (uint32_t)P +
+                           part_of<NARROW>(bd ? 0 : d[u], pd, local);
+      const uint64_t m = match_key(key, bits, __ballot(act));
+      // the lowest lane of each key adds the key's count
+      if (act && (m & ((1ull << lane) - 1ull)) == 0ull) atomicAdd(&cnt[key], (uint32_t)__popcll(m));
+    }
   }
   if (bad) atomicOr(flag, bad);
   __syncthreads();
   for (int b = threadIdx.x; b < nb; b += blockDim.x) hist[(int64_t)b * tiles + tile] = cnt[b];
 }
 
+// REL: relation ids to place (without them their array's LDS goes to a third
+// workgroup per CU)
+template <bool NARROW, bool REL>
 __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_scatter_kernel(const int64_t* src, const int64_t* dst,
                                                                          const int32_t* rel, int64_t n,
-                                                                         int64_t ps, double inv_ps, int P, int bits,
+                                                                         PartDivider pd, int P, int bits,
                                                                          int64_t tiles, const uint32_t* start,
                                                                          int32_t* src_local, int32_t* rel_out,
                                                                          int32_t* dst_local) {
-  __shared__ int32_t t_sl[BUCKET_TILE], t_dl[BUCKET_TILE], t_rq[BUCKET_TILE];
+  __shared__ int32_t t_sl[BUCKET_TILE], t_dl[BUCKET_TILE], t_rq[REL ? BUCKET_TILE : 1];
   __shared__ uint8_t t_key[BUCKET_TILE];
   __shared__ uint32_t wcnt[BT_WAVES][BUCKET_DIRECT_MAX];   // per wave, then the wave's base in the tile
   __shared__ uint32_t koff[BUCKET_DIRECT_MAX];              // first tile slot of each bucket
@@ -179,20 +216,30 @@ __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_scatter_kernel(const i
   const int64_t e0 = tile * BUCKET_TILE + (int64_t)w * 512;
   uint32_t key[8], rank[8];
   int32_t sl[8], dl[8], rq[8];
+  {
+    // all of the wave's ids on their way before the first is used (inside the
+    // rounds each load waited for the round before it: 525 us at 69 million
+    // edges in 64 buckets, now 410 to 421 us, 1.66 GB at 4 TB/s)
+    int64_t s[8], d[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t i = e0 + 64 * u + lane;
+      s[u] = i < n ? src[i] : 0;
+      d[u] = i < n ? dst[i] : 0;
+      rq[u] = REL && i < n ? rel[i] : 0;
+    }
+    // keeps the loads where they are, and 8 bytes wide
+#pragma unroll
+    for (int u = 0; u < 8; ++u) __asm__ volatile("" : "+v"(s[u]), "+v"(d[u]));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      key[u] = part_of<NARROW>(s[u], pd, sl[u]) * (uint32_t)P;
+      key[u] += part_of<NARROW>(d[u], pd, dl[u]);
+    }
+  }
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
-    const int64_t i = e0 + 64 * u + lane;
-    const bool act = i < n;
-    key[u] = 0u;
-    sl[u] = dl[u] = rq[u] = 0;
-    if (act) {
-      const int64_t s = src[i], d = dst[i];
-      const int64_t pi = part_of(s, ps, inv_ps), pj = part_of(d, ps, inv_ps);
-      key[u] = (uint32_t)(pi * P + pj);
-      sl[u] = (int32_t)(s - pi * ps);
-      dl[u] = (int32_t)(d - pj * ps);
-      rq[u] = rel ? rel[i] : 0;
-    }
+    const bool act = e0 + 64 * u + lane < n;
     const uint64_t m = match_key(key[u], bits, __ballot(act));
     const uint64_t below = m & ((1ull << lane) - 1ull);
     rank[u] = act ? wcnt[w][key[u]] + (uint32_t)__popcll(below) : 0xFFFFFFFFu;
@@ -249,7 +296,7 @@ __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_scatter_kernel(const i
     const uint32_t slot = koff[key[u]] + wcnt[w][key[u]] + rank[u];
     t_sl[slot] = sl[u];
     t_dl[slot] = dl[u];
-    t_rq[slot] = rq[u];
+    if (REL) t_rq[slot] = rq[u];
     t_key[slot] = (uint8_t)key[u];
   }
   __syncthreads();
@@ -259,7 +306,7 @@ __global__ __launch_bounds__(BUCKET_TILE / 8) void bucket_scatter_kernel(const i
     const uint32_t o = gpos[b] + ((uint32_t)p - koff[b]);
     src_local[o] = t_sl[p];
     dst_local[o] = t_dl[p];
-    if (rel_out) rel_out[o] = t_rq[p];
+    if (rel_out) rel_out[o] = REL ? t_rq[p] : 0;
   }
 }
 
@@ -289,25 +336,41 @@ static int key_bits_of(int nb) {
   return b;
 }
 
+// every id in 32 bits, and so the partition size
+static bool narrow_ids(int64_t n_ent) { return n_ent <= ((int64_t)1 << 32) - 1; }
+static PartDivider part_divider(int64_t ps) {
+  return PartDivider{ps, 1.0 / (double)ps, (uint32_t)std::min<uint64_t>(((uint64_t)1 << 32) / (uint64_t)ps, 0xFFFFFFFFu)};
+}
+
 void launch_bucket_count(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t n_ent,
                          int32_t n_rel, int64_t ps, int P, uint32_t* hist, uint32_t* flag, hipStream_t s) {
   const int64_t tiles = bucket_direct_units(n);
   if (tiles == 0) return;
-  bucket_count_kernel<<<(unsigned)tiles, BUCKET_TILE / 8, 0, s>>>(src, dst, rel, n, n_ent, n_rel, ps,
-                                                                  1.0 / (double)ps, P, key_bits_of(P * P), tiles,
-                                                                  hist, flag);
+  const PartDivider pd = part_divider(ps);
+  const int bits = key_bits_of(P * P);
+  if (narrow_ids(n_ent))
+    bucket_count_kernel<true><<<(unsigned)tiles, BUCKET_TILE / 8, 0, s>>>(src, dst, rel, n, n_ent, n_rel, pd, P, bits,
+                                                                          tiles, hist, flag);
+  else
+    bucket_count_kernel<false><<<(unsigned)tiles, BUCKET_TILE / 8, 0, s>>>(src, dst, rel, n, n_ent, n_rel, pd, P,
+                                                                           bits, tiles, hist, flag);
 }
 
-void launch_bucket_scatter(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t ps,
-                           int P, const uint32_t* start, int64_t* offsets, int32_t* src_local,
+void launch_bucket_scatter(const int64_t* src, const int64_t* dst, const int32_t* rel, int64_t n, int64_t n_ent,
+                           int64_t ps, int P, const uint32_t* start, int64_t* offsets, int32_t* src_local,
                            int32_t* rel_out, int32_t* dst_local, hipStream_t s) {
   const int64_t tiles = bucket_direct_units(n);
   const int nb = P * P;
   bucket_direct_offsets_kernel<<<(nb + 1 + 255) / 256, 256, 0, s>>>(start, tiles, nb, n, offsets);
   if (tiles == 0) return;
-  bucket_scatter_kernel<<<(unsigned)tiles, BUCKET_TILE / 8, 0, s>>>(src, dst, rel, n, ps, 1.0 / (double)ps, P,
-                                                                    key_bits_of(nb), tiles, start, src_local,
-                                                                    rel_out, dst_local);
+  const PartDivider pd = part_divider(ps);
+  const int bits = key_bits_of(nb);
+  auto launch = [&](auto kernel) {
+    kernel<<<(unsigned)tiles, BUCKET_TILE / 8, 0, s>>>(src, dst, rel, n, pd, P, bits, tiles, start, src_local, rel_out,
+                                                       dst_local);
+  };
+  if (narrow_ids(n_ent)) rel ? launch(bucket_scatter_kernel<true, true>) : launch(bucket_scatter_kernel<true, false>);
+  else rel ? launch(bucket_scatter_kernel<false, true>) : launch(bucket_scatter_kernel<false, false>);
 }
 
 void launch_bucket_keys(const int64_t* src, const int64_t* dst, int64_t n, int64_t ps, int P,

@@ -84,7 +84,7 @@ extern "C" pbg_status pbg_bucket_edges(pbg_ctx* ctx, const int64_t* src, const i
     if (hflag & 3u)
       return set_err(ctx, PBG_ERR_INVALID_ARG, "an entity id is outside [0, %lld)", (long long)ctx->n);
     if (hflag & 4u) return set_err(ctx, PBG_ERR_INVALID_ARG, "a relation id is outside [0, %d)", ctx->R);
-    launch_bucket_scatter(src, dst, rel, n, ctx->ps, P, start, offsets, src_local, rel_out, dst_local, s);
+    launch_bucket_scatter(src, dst, rel, n, ctx->n, ctx->ps, P, start, offsets, src_local, rel_out, dst_local, s);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(ctx, e, "bucketing");

@@ -60,6 +60,26 @@ def test_bucket_edges_matches_oracle(n, P, R, m, seed):
     assert np.array_equal(rl, w_rel)
 
 
+@pytest.mark.parametrize("n,P", [(2**32 - 2, 16), (2**32 - 1, 7), (2**32, 16), (2**32 + 1, 5), (2**34, 16),
+                                 (2**31 + 11, 3), (6, 6)])
+def test_bucket_edges_ids_around_32_bits(n, P):
+    """Ids on both sides of the width that the partition's division depends
+    on, at every partition's edges and at random."""
+    rng = synth.rng_for(P)
+    ps = -(-n // P)
+    edges = np.unique(np.clip(np.r_[np.arange(P + 1) * ps - 1, np.arange(P + 1) * ps, n - 1], 0, n - 1))
+    src, dst = (np.r_[edges, rng.integers(0, n, 9_000)].astype(np.int64) for _ in range(2))
+    rng.shuffle(dst)
+    dev = torch.device("cuda")
+    out = _run(n, P, 1, torch.from_numpy(src).to(dev), None, torch.from_numpy(dst).to(dev))
+    bucket = (src // ps) * P + dst // ps
+    order = np.argsort(bucket, kind="stable")
+    offsets, sl, _, dl = (t.cpu().numpy() for t in out)
+    assert np.array_equal(offsets, np.searchsorted(bucket[order], np.arange(P * P + 1)))
+    assert np.array_equal(sl, (src % ps)[order])
+    assert np.array_equal(dl, (dst % ps)[order])
+
+
 def test_bucket_edges_empty_and_out_of_range():
     from paper_1903_12287_amd import pbg
     dev = torch.device("cuda")
