@@ -229,8 +229,10 @@ inline int op_backward_blocks(int C, int U, int cmp) {
 }
 
 // ---- sort, segments, updates ----------------------------------------------------
-// sorted positions per wave of the segment update (a power of two <= 32)
-#define SEG_BLOCK 32
+// sorted positions per wave of the segment update: 8 up to SEG_SHORT_MAX
+// positions, else 32
+#define SEG_SHORT_MAX 65536
+inline int64_t segment_blocks(int64_t n) { return n / 8 + 2; }
 
 struct SortWork {
   uint32_t* keys_alt;   // [max_n] ping-pong buffers of the sort
@@ -238,7 +240,7 @@ struct SortWork {
   uint32_t* hist;       // [256][max blocks]
   uint32_t* scan_tmp;   // block sums of the multi-launch scan
   float* partial;       // [max_n][width] per-block partial sums of segments
-  uint32_t* segflag;    // [max_n / SEG_BLOCK + 2] piece flags per block of sorted positions
+  uint32_t* segflag;    // [segment_blocks(max_n)] piece flags per block of sorted positions
   int max_n;
 };
 

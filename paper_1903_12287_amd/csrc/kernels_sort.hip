@@ -5,7 +5,7 @@
 // accumulator per embedding row, summed over the row) is applied once per
 // touched row.
 //
-// The sorted positions are cut into fixed blocks of SEG_BLOCK.  A wave per block sums
+// The sorted positions are cut into fixed blocks of 8 or 32.  A wave per block sums
 // every piece of the block (a piece = the positions of one segment inside the
 // block) in position order; a segment that lies inside one block is updated
 // there and then.  A segment that crosses block boundaries (a hub row of a
@@ -387,7 +387,7 @@ struct RelRider {
   float* relG;
 };
 
-// Block of SEG_BLOCK sorted positions, one wave.  RQ floats of a row per lane
+// Block of LEN sorted positions, one wave.  RQ floats of a row per lane
 // (lane L holds elements RQ L .. RQ L + RQ - 1; width <= 64 RQ).  The rows are
 // loaded SB positions at a time, together with the embedding rows of the
 // whole segments ending among them, all loads in flight together, and a
@@ -395,7 +395,7 @@ struct RelRider {
 // total at its last position.  Whole segments are updated in place; the (at
 // most two) pieces that continue into a neighbouring block are written to
 // `partial` at their first position.
-template <int MODE, int RQ>
+template <int MODE, int RQ, int LEN>
 __global__ __launch_bounds__(256) void seg_update_local(StepGeom g, StepBufs b, const uint32_t* keys,
                                                         const uint32_t* vals, int n, const float* rows,
                                                         int64_t ld, int width, float* partial, uint32_t* segflag,
@@ -408,11 +408,11 @@ __global__ __launch_bounds__(256) void seg_update_local(StepGeom g, StepBufs b, 
   constexpr int SB = 16 / RQ;                      // positions per batch of loads
   const int lane = threadIdx.x & 63;
   const int blk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
-  const int p0 = blk * SEG_BLOCK;
+  const int p0 = blk * LEN;
   if (p0 >= n) return;
-  const int np = min(SEG_BLOCK, n - p0);
-  const int pos = p0 + (lane & (SEG_BLOCK - 1));
-  const bool valid = lane < SEG_BLOCK && pos < p0 + np;
+  const int np = min(LEN, n - p0);
+  const int pos = p0 + (lane & (LEN - 1));
+  const bool valid = lane < LEN && pos < p0 + np;
   const uint32_t k = valid ? keys[pos] : 0u;
   const uint32_t vidx = valid ? vals[pos] : 0u;
   const bool diff_prev = valid && (pos == 0 || keys[pos - 1] != k);
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(256) void seg_update_local(StepGeom g, StepBufs b, 
 // where they start: its last piece plus the leading piece of every following
 // block the segment covers, added in block order, 16 loads in flight; the
 // extent comes from the piece flags the local pass left per block
-template <int MODE, int RQ>
+template <int MODE, int RQ, int LEN>
 __global__ __launch_bounds__(256) void seg_update_span(StepGeom g, StepBufs b, const uint32_t* keys, int n,
                                                        int width, const float* partial, const uint32_t* segflag,
                                                        float lr, RelRider rr, int own_blocks) {
@@ -545,12 +545,13 @@ __global__ __launch_bounds__(256) void seg_update_span(StepGeom g, StepBufs b, c
   }
   const int lane = threadIdx.x & 63;
   const int blk = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
-  const int p0 = blk * SEG_BLOCK;
-  const int p1 = p0 + SEG_BLOCK;
-  const int nblk = (n + SEG_BLOCK - 1) / SEG_BLOCK;
+  const int p0 = blk * LEN;
+  const int p1 = p0 + LEN;
+  const int nblk = (n + LEN - 1) / LEN;
   if (MODE == SEG_ENTITY && blk == 0 && b.nuniq) {
     // the step's touched rows: the blocks' segment counts (integer sum)
     uint32_t cnt = 0;
+#pragma unroll 8
     for (int j = lane; j < nblk; j += 64) cnt += (segflag[j] >> 16) & 63u;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cnt += (uint32_t)__shfl_xor((int)cnt, o, 64);
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(256) void seg_update_span(StepGeom g, StepBufs b, c
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const int i = i0 + u;
-      const int at = i == 0 ? s : p1 + (i - 1) * SEG_BLOCK;
+      const int at = i == 0 ? s : p1 + (i - 1) * LEN;
       const float* part = partial + (int64_t)at * width;
 #pragma unroll
       for (int q = 0; q < RQ; ++q) {
@@ -745,7 +746,6 @@ static void seg_update(const StepGeom& g, const StepBufs& b, const uint32_t* key
                        const RelRider* rider = nullptr) {
   if (n < 0) n = 0;
   if (n == 0 && !rider) return;
-  const int blocks = (n + 4 * SEG_BLOCK - 1) / (4 * SEG_BLOCK);
   RelRider rr{};
   int extra1 = 0, extra2 = 0;
   if (rider) {
@@ -753,21 +753,27 @@ static void seg_update(const StepGeom& g, const StepBufs& b, const uint32_t* key
     extra1 = rr.nchunks * RELSUM_PIECES;
     extra2 = (rr.dr + 63) / 64;
   }
+  auto launch = [&](auto local, auto span, int len) {
+    const int blocks = (n + 4 * len - 1) / (4 * len);
+    local<<<blocks + extra1, 256, 0, s>>>(g, b, keys, vals, n, rows, ld, width, w.partial, w.segflag, lr, rr, blocks);
+    span<<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr, blocks);
+  };
+  // A wave's block is a serial chain, so few positions go in short blocks:
+  // 16,000 of d = 32 took 18 + 4.5 us (this pass and the crossing segments) in
+  // blocks of 32, 500 waves on 1,024 SIMDs, and take 8.5 + 6.8 us in blocks of
+  // 8; 45,000 of d = 200 took 23 + 7.6 us and take 13.7 + 11.3 us.  More
+  // pieces cross a block's end, though: with the few, long segments of the
+  // relations (40,000 positions, 5,000 relations) 13 + 61 us for 24 + 19 us.
+  const bool few = MODE == SEG_ENTITY && n <= SEG_SHORT_MAX;
   if (width <= 128) {
-    seg_update_local<MODE, 2><<<blocks + extra1, 256, 0, s>>>(g, b, keys, vals, n, rows, ld, width, w.partial,
-                                                               w.segflag, lr, rr, blocks);
-    seg_update_span<MODE, 2><<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr,
-                                                              blocks);
+    few ? launch(seg_update_local<MODE, 2, 8>, seg_update_span<MODE, 2, 8>, 8)
+        : launch(seg_update_local<MODE, 2, 32>, seg_update_span<MODE, 2, 32>, 32);
   } else if (width <= 256) {
-    seg_update_local<MODE, 4><<<blocks + extra1, 256, 0, s>>>(g, b, keys, vals, n, rows, ld, width, w.partial,
-                                                               w.segflag, lr, rr, blocks);
-    seg_update_span<MODE, 4><<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr,
-                                                              blocks);
+    few ? launch(seg_update_local<MODE, 4, 8>, seg_update_span<MODE, 4, 8>, 8)
+        : launch(seg_update_local<MODE, 4, 32>, seg_update_span<MODE, 4, 32>, 32);
   } else {
-    seg_update_local<MODE, 8><<<blocks + extra1, 256, 0, s>>>(g, b, keys, vals, n, rows, ld, width, w.partial,
-                                                               w.segflag, lr, rr, blocks);
-    seg_update_span<MODE, 8><<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr,
-                                                              blocks);
+    few ? launch(seg_update_local<MODE, 8, 8>, seg_update_span<MODE, 8, 8>, 8)
+        : launch(seg_update_local<MODE, 8, 32>, seg_update_span<MODE, 8, 32>, 32);
   }
 }
 
