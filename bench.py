@@ -38,9 +38,9 @@ N_NODES, N_EDGES, DIM = 4_847_571, 68_993_773, 128
 C, U, S = 1000, 1000, 40
 LR, MARGIN, SEED = 0.1, 0.1, 20190002
 PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense fp32 matrix
-PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense bf16 matrix
+PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense bf16 and fp16 matrix
 PEAK_HBM = 8000.0        # GB/s
-SPLIT_PIECES = 6         # bf16 piece products per float32 product in the score contraction
+SPLIT_PIECES = 3         # fp16 plane products per float32 product in the score contraction
 
 
 def parse():
@@ -201,9 +201,9 @@ def roofline(st, kernel, traffic=None, pieces=None, issued=1.0):
     """Dominant kernel: the score contraction with its fused loss epilogue.
     Algorithmic flops per launch: 2 sides x 2 C N d per chunk (a third of the
     12 C N d of the three contractions), one launch per step.  The kernel
-    issues v_mfma_f32_16x16x32_bf16 in both precisions; a float32 contraction
-    issues `pieces` exact bf16 piece products per product, so its ceiling is
-    the bf16 matrix peak over `pieces` (frac), and its rate against the fp32
+    issues v_mfma_f32_16x16x32_f16 or _bf16 (the same rate); a float32
+    contraction issues `pieces` fp16 plane products per product, so its ceiling
+    is that matrix peak over `pieces` (frac), and its rate against the fp32
     matrix peak is given beside it (fp32_peak_frac).  `issued`: the share of
     the algorithmic products the kernel computes (with cos, side 1's in-chunk
     block comes transposed from side 0's tiles)."""
@@ -217,7 +217,7 @@ def roofline(st, kernel, traffic=None, pieces=None, issued=1.0):
            "unit": "TFLOP/s", "frac": achieved / peak if achieved else None, "traffic": traffic,
            "avg_launch_ms": avg_ms, "flops_per_launch": flops, "timed_launches": timed}
     if pieces and achieved:
-        out["peak_note"] = (f"bf16 matrix peak {PEAK_BF16_MFMA} / {pieces} exact bf16 piece products "
+        out["peak_note"] = (f"fp16 matrix peak {PEAK_BF16_MFMA} / {pieces} fp16 plane products "
                             "per float32 product (the instruction the kernel issues)")
         out["fp32_peak"] = PEAK_FP32_MFMA
         out["fp32_peak_frac"] = achieved / PEAK_FP32_MFMA
@@ -288,9 +288,9 @@ def main():
                    "operator": "translation", "comparator": "cos", "loss": "ranking",
                    "chunk": C, "uniform_negatives": U, "chunks_per_step": S,
                    "edges_per_step": S * C, "partitions": 1},
-        "roofline": roofline(st, "score_split_kernel3<EPI_LOSS_BITS, 6> (float32 score + ranking epilogue)",
+        "roofline": roofline(st, "score_kernel<EPI_LOSS_BITS, false, 4> (float32 score + ranking epilogue)",
                              measured_traffic("score"), pieces=SPLIT_PIECES,
-                             issued=1.0 - (128 * (C // 128)) ** 2 / (2.0 * C * (C + U))),
+                             issued=1.0 - C / (2.0 * (C + U))),
         # from the phase-timing run of phase_steps steps
         "phases_ms_per_step": phases(stp),
         "phase_steps": phase_steps,
@@ -308,7 +308,7 @@ def main():
         print(f"# bf16: {st16['edges'] / dt16:.4g} edges/s", file=sys.stderr)
         out["bf16"] = {"value": st16["edges"] / dt16, "unit": "edges/s",
                        "ms_per_step": dt16 * 1e3 / args.steps, "dtype": "bf16 inputs, f32 accumulate",
-                       "roofline": roofline(st16, "gemm_bf16_kernel<128,GA_KC,EPI_LOSS_BITS,1> "
+                       "roofline": roofline(st16, "gemm_bf16_kernel<128,GA_KC,EPI_LOSS_BITS> "
                                                   "(score + ranking epilogue)"),
                        "phases_ms_per_step": phases(st16p)}
     if not args.no_cpu_baseline:
@@ -429,7 +429,7 @@ def row_knowledge_graph(reciprocal=False):
         st = pbg.pbg_get_stats(ctx)
         out["value"] = w.E / dt
         out["ms_per_pass"] = dt * 1e3
-        out["roofline"] = roofline(st, "score_split_kernel<EPI_SOFTMAX_EXP, 6> (score)", pieces=SPLIT_PIECES)
+        out["roofline"] = roofline(st, "score_kernel<EPI_SOFTMAX_EXP, true, 4> (score)", pieces=SPLIT_PIECES)
         out["phases_ms_per_step"] = phases(st)
         # filtered ranks of the held-out triples, known = train + held-out
         hs, hr, hd = t(w.held_src), t(w.held_rel), t(w.held_dst)

@@ -1,6 +1,5 @@
 // Loss values and per-edge gradients of a step (Sec. 3.1 losses): the
-// finalisation's workgroup body, shared by its own kernel and by the kernel
-// that runs it beside the transposed piece split.
+// finalisation's workgroup body.
 #pragma once
 
 #include "kernels.h"

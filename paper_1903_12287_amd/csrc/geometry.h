@@ -11,7 +11,8 @@
 //                       unit vector), and nn holds the raw (or unit) entities
 //   nn  [S][2][N][dp]   side 0: destination candidates, side 1: source candidates
 //   ds  [S][2][C][Np]   score gradient dL/dS (raw scores between softmax passes);
-//                       for the ranking loss dL/dS is 0 or 1 and is kept as bits,
+//                       for the ranking loss dL/dS is 0 or 1 and is kept as bits:
+//                       float32 in the blocks of BitsView, bfloat16 inputs in
 //                       dsb [S][2][ceil(Np/16)][C] 16-bit words (16 columns of a
 //                       row per word, stored word-column major)
 //   dq  [S][2][C][dp]   dS . N per side

@@ -7,8 +7,9 @@
 #include "geometry.h"
 
 // ---- matrix-core contractions -------------------------------------------------
-// EPI_LOSS_BITS: ranking loss with dS (0 or 1) written as bits, 16 columns per
-// uint16 word, word (w, row) at dsb[w * ldcb + row] (nwcb words per row; batch
+// EPI_LOSS_BITS: ranking loss with dS (0 or 1) written as bits: row pieces in
+// the blocks of BitsView, bfloat16 inputs 16 columns per uint16 word, word
+// (w, row) at dsb[w * ldcb + row] (nwcb words per row; batch
 // strides cb_cs / cb_ss in words)
 enum { EPI_STORE = 0, EPI_LOSS = 1, EPI_SOFTMAX_STATS = 2, EPI_LOSS_BITS = 3, EPI_SOFTMAX_EXP = 4,
        EPI_RANK = 5 };

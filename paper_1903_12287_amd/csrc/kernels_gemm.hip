@@ -2,7 +2,9 @@
 // for the small products of the linear operator (Sec. 3.1: g(x) = A x with one
 // relation, formed for a whole step: Q = X A^T, K = Y A, and in the backward
 // X and Y gradients and dA).  The chunk x candidates contractions of the score
-// and its backward run on the bf16 instructions (kernels_gemm_bf16.hip).
+// and its backward run on fp16 row pieces (kernels_score.hip,
+// kernels_bits_backward.hip, kernels_value_backward.hip) or, with bfloat16
+// inputs, in kernels_gemm_bf16.hip.
 //
 // A 256-thread workgroup (4 waves in a 2 x 2 arrangement) computes a 128 x BN
 // tile (BN = 128, or 64 for narrow outputs); each wave owns 64 x BN/2 outputs,
