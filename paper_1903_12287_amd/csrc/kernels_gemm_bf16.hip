@@ -93,7 +93,11 @@ struct TileH {
   static constexpr int LOADS = TX * BK / 8 / 256;
   static constexpr int SIZE = TX * BK;
 
-  __device__ __forceinline__ static void load(u32x4* r, rsrc_t rs, int ld, int x0, int xdim, int k0, int kdim, int tid) {
+  // offsets of rows count from the tile's (GA_KC) or the slice's (GA_MC) first
+  // row: dS may hold more than 4 GiB
+  __device__ __forceinline__ static void load(u32x4* r, const uint16_t* p, int ld, int x0, int xdim, int k0, int kdim,
+                                              int tid) {
+    const rsrc_t rs = make_rsrc(p + (MODE == GA_KC ? (int64_t)x0 * ld : (MODE == GA_MC ? (int64_t)k0 * ld : 0)));
 #pragma unroll
     for (int q = 0; q < LOADS; ++q) {
       const int f = tid + 256 * q;
@@ -101,13 +105,13 @@ struct TileH {
       if (MODE == GA_MC) {
         const int k = f / (TX / 8), xq = f % (TX / 8);
         const int gk = k0 + k, gx = x0 + 8 * xq;
-        if (gk < kdim && gx < ((xdim + 7) & ~7)) off = (uint32_t)(((int64_t)gk * ld + gx) * 2);
+        if (gk < kdim && gx < ((xdim + 7) & ~7)) off = (uint32_t)((k * ld + gx) * 2);
         r[q] = bload16(rs, off);
       } else {
         const int x = f >> 2, kq = f & 3;
         const int gx = x0 + x, gk = k0 + 8 * kq;
         if (MODE == GA_KC) {
-          if (gx < xdim && gk < ((kdim + 7) & ~7)) off = (uint32_t)(((int64_t)gx * ld + gk) * 2);
+          if (gx < xdim && gk < ((kdim + 7) & ~7)) off = (uint32_t)((x * ld + gk) * 2);
           r[q] = bload16(rs, off);
         } else if (MODE == GA_BITS_ROW) {
           if (gx < xdim && gk < ((kdim + 7) & ~7)) off = (uint32_t)(((int64_t)(gk >> 4) * ld + gx) * 2);
@@ -466,8 +470,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmArgsH& a, int tiles_n, 
   const int wm = w >> 1, wn = w & 1;
   const int l16 = lane & 15, g = lane >> 4;
 
-  const rsrc_t ra_s = make_rsrc(a.A + c * a.a_cs + side * a.a_ss);
-  const rsrc_t rb = make_rsrc(a.B + c * a.b_cs + side * a.b_ss);
+  const uint16_t* ra_s = a.A + c * a.a_cs + side * a.a_ss;
+  const uint16_t* rb = a.B + c * a.b_cs + side * a.b_ss;
 
   v4f acc[4][JN];
 #pragma unroll

@@ -45,7 +45,7 @@ __device__ __forceinline__ void value_run(const ValueArgs& a, const float* ds, c
   const int tid = threadIdx.x, l16 = lane & 15, g = lane >> 4;
   const int nk = (K + BK - 1) / BK;
   if (nk <= 0) return;
-  const rsrc_t rb = make_rsrc(brows), rd = make_rsrc(ds);
+  const rsrc_t rb = make_rsrc(brows);
   uint32_t ob[BL];
   int brow[BL];
 #pragma unroll
@@ -61,7 +61,8 @@ __device__ __forceinline__ void value_run(const ValueArgs& a, const float* ds, c
       dma16(rb, sm.B[buf] + (w + 4 * i) * 512, (tail && kt * BK + brow[i] >= K) ? kOob : ob[i], kt * BK * a.ld * 2);
   };
   // dS of a slice: COL four k rows (tid / 32 + 8 q) of four columns, else two
-  // rows (tid / 4 + 64 q) of eight k
+  // rows (tid / 4 + 64 q) of eight k.  Offsets count from the slice's (COL) or
+  // the tile's first row: dS may hold more than 4 GiB
   v4f pa[4];
   float f[4];      // COL: factor of each row; else: factors of the two rows
   v4f fk[2];       // SCALED, not COL: factors of the eight k
@@ -69,13 +70,14 @@ __device__ __forceinline__ void value_run(const ValueArgs& a, const float* ds, c
   const int k4 = (K + 3) & ~3;
   auto load_a = [&](int kt) {
     const int k0 = kt * BK;
+    const rsrc_t rd = make_rsrc(ds + (int64_t)(COL ? k0 : m0) * a.lds);
     if (COL) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int k = k0 + (tid >> 5) + 8 * q;
         const bool in = k < K;
         pa[q] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                                            rd, in && m0 + xcol < a.lds ? (uint32_t)(((int64_t)k * a.lds + m0 + xcol) * 4) : kOob, 0, 0));
+                                            rd, in && m0 + xcol < a.lds ? (uint32_t)(((k - k0) * a.lds + m0 + xcol) * 4) : kOob, 0, 0));
         const int kk = in ? k : 0;
         f[q] = afac;
         if (SOFTMAX) f[q] *= rs[(int64_t)min((m0 + xcol) >> 6, a.nct - 1) * a.C + kk];
@@ -88,7 +90,7 @@ __device__ __forceinline__ void value_run(const ValueArgs& a, const float* ds, c
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           pa[2 * q + h] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
-                                                      rd, m < M && k0 + kq + 4 * h < k4 ? (uint32_t)(((int64_t)m * a.lds + k0 + kq + 4 * h) * 4) : kOob, 0, 0));
+                                                      rd, m < M && k0 + kq + 4 * h < k4 ? (uint32_t)(((m - m0) * a.lds + k0 + kq + 4 * h) * 4) : kOob, 0, 0));
         f[q] = afac;
         if (SOFTMAX) f[q] *= rs[(int64_t)(k0 >> 6) * a.C + (m < M ? m : 0)];
       }
