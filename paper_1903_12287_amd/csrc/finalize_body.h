@@ -5,7 +5,7 @@
 #include "kernels.h"
 #include "device_common.h"
 
-// ---- row scales of the backward --------------------------------------
+// ---- row scales of the ranking backward --------------------------------------
 // Every row's fp16 scale relative to the largest row of its (chunk, side) of
 // nn and of qk, 2^(e - e_max + 15), 0 for rows more than 29 binades below it.
 // Each of the chunk's nblk workgroups finds the four largest exponents again
@@ -31,14 +31,6 @@ __device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b,
     for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) top = max(top, tops[w]);
     if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_max : b.pq_max)[z] = top;
     const int64_t ko = (int64_t)z * (nn ? g.ks_n : g.ks_q);
-    if (g.loss != LOSS_RANKING) {
-      // the other losses take 2^(e - e_max + 15) as float32, zero up to the
-      // end of the last slice (dS is zero there)
-      float* kf = (nn ? b.nkf : b.qkf) + ko;
-      for (int t = blk * FIN_THREADS + threadIdx.x; t < ((rows + 31) & ~31); t += nblk * FIN_THREADS)
-        kf[t] = t < rows ? ldexpf(1.0f, 15 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top) : 0.0f;
-      continue;
-    }
     uint16_t* ks = (nn ? b.nks : b.qks) + ko;
     for (int t = blk * FIN_THREADS + threadIdx.x; t < rows; t += nblk * FIN_THREADS) {
       const int ex = 30 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top;
@@ -55,7 +47,7 @@ __device__ __forceinline__ void finalize_block(const StepGeom& g, const StepBufs
   const int Cc = chunk_edges(g, c);
   double acc = 0.0;
   const int e = blk * FIN_THREADS + threadIdx.x;
-  if (g.pieces == PIECES_SCALED) row_scales(g, b, c, Cc, blk, nblk);
+  if (g.pieces == PIECES_SCALED && g.loss == LOSS_RANKING) row_scales(g, b, c, Cc, blk, nblk);
   if (e < Cc) {
     const int64_t ce = (int64_t)c * g.C + e;
     const float p = b.pos[pos_index(g, c, 0, e)];

@@ -44,7 +44,7 @@ enum { PIECES_NONE = 0, PIECES_UNIT = 1, PIECES_SCALED = 2 };
 
 struct StepGeom {
   int C, U, N;      // chunk capacity, uniform draws per side, N = C + U
-  int d, dp, Np;    // dim, padded row stride, padded score-row stride
+  int d, dp, Np;    // dim, padded row stride, score-row stride (N rounded up to 32)
   int dr;           // floats per relation parameter row
   int nct;          // column tiles of the score contraction per chunk-side
   int nchunks;      // chunks in this step
@@ -135,8 +135,6 @@ struct StepBufs {
   int* pq_max;          // [S][2]
   uint16_t* nks;        // [S][2][ks_n]
   uint16_t* qks;        // [S][2][ks_q]
-  float* nkf;           // the same for the logistic and softmax losses, as float32
-  float* qkf;
   float* pos;           // [S][C] positive scores ([S][2][C] with reciprocal predicates)
   float* bias;          // [S][C] <theta_r, x_d> (translation + dot)
   int32_t* neg;         // [S][2][U] uniform draws (side 0 from partition j, side 1 from i)

@@ -165,9 +165,7 @@ struct ValueArgs {
   int dh, ld, dp;
   int C, U, m_step;
   const int32_t* cstart;
-  const float *nkf, *qkf;       // [c][2][ks_n / ks_q] 2^15 times each row's scale relative to the largest
-  int ks_n, ks_q;               // (NULL: unit rows)
-  const int *nmax, *qmax;
+  const float *ni, *qi;         // [c][2][C + U] and [c][2][C] inverse row scales (NULL: unit rows)
   const float* cscale;
   float *dq, *dn;
   int64_t dq_cs, dq_ss, dn_cs, dn_ss;

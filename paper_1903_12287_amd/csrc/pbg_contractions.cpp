@@ -207,13 +207,9 @@ static void run_value_backward(const StepGeom& g, const StepBufs& b, hipStream_t
   a.U = g.U;
   a.m_step = g.m_step;
   a.cstart = g.cstart;
-  a.ks_n = g.ks_n;
-  a.ks_q = g.ks_q;
   if (g.pieces == PIECES_SCALED) {
-    a.nkf = b.nkf;
-    a.qkf = b.qkf;
-    a.nmax = b.pn_max;
-    a.qmax = b.pq_max;
+    a.ni = b.pn_is;
+    a.qi = b.pq_is;
   }
   a.cscale = g.cweight;
   a.dq = b.dq;

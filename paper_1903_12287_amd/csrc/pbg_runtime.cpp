@@ -84,7 +84,8 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
   ctx->ws_ready = false;
   Arena& a = ctx->ws;
   const int N = C + U;
-  const int d = ctx->d, dp = round_up(d, 4), Np = round_up(N, 4);
+  // rows of dS start on a 128-byte line: the backward's waves read 32 columns
+  const int d = ctx->d, dp = round_up(d, 4), Np = round_up(N, 32);
   const int nct = score_tiles(ctx, C, U);
   const int64_t s = S;
   StepBufs& b = ctx->bufs;
@@ -115,9 +116,6 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
       if (ranking) {
         b.nks = (uint16_t*)a.get(s * 2 * round_up(N, 32) * 2);
         b.qks = (uint16_t*)a.get(s * 2 * round_up(C, 32) * 2);
-      } else {
-        b.nkf = (float*)a.get(s * 2 * round_up(N, 32) * 4);
-        b.qkf = (float*)a.get(s * 2 * round_up(C, 32) * 4);
       }
     }
   }
@@ -195,6 +193,9 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
   // bf16 transposes copy them: start from zeros so they always hold finite values
   hipError_t ez = hipMemsetAsync(b.qk, 0, (size_t)s * 2 * C * dp * 4, ctx->cs);
   if (ez == hipSuccess) ez = hipMemsetAsync(b.nn, 0, (size_t)s * 2 * N * dp * 4, ctx->cs);
+  // the backward multiplies the zeros past a chunk's rows by whatever scales lie there
+  if (ez == hipSuccess && b.pn_is) ez = hipMemsetAsync(b.pn_is, 0, (size_t)(s * 2 * N + 256) * 4, ctx->cs);
+  if (ez == hipSuccess && b.pq_is) ez = hipMemsetAsync(b.pq_is, 0, (size_t)(s * 2 * C + 256) * 4, ctx->cs);
   if (ez == hipSuccess) ez = hipStreamSynchronize(ctx->cs);
   if (ez != hipSuccess) {
     ctx->ws.release();
@@ -491,7 +492,7 @@ BucketTables partition_tables(pbg_ctx* ctx, int32_t i, int32_t j) {
 void bucket_geom(const pbg_ctx* ctx, int32_t i, int32_t j, const BucketTables& tb, int C, int U, uint64_t seed,
                  StepGeom& g) {
   const int N = C + U;
-  const int d = ctx->d, dp = round_up(d, 4), Np = round_up(N, 4);
+  const int d = ctx->d, dp = round_up(d, 4), Np = round_up(N, 32);
   const int64_t rows_i = tb.rows_i, rows_j = tb.rows_j;
   memset(&g, 0, sizeof(g));
   g.C = C;

@@ -1,0 +1,58 @@
+"""Gradients whose factors span many binades: candidates that only small
+probabilities reach, and rows of very unlike size in one chunk.  A row's first
+Adagrad step is lr g / |g|, so every row's gradient counts relative to its own
+size."""
+import numpy as np
+import pytest
+
+from paper_1903_12287_amd import synth
+from tests.pbg_cases import GpuModel, make_problem, teacher_forced_step
+
+pytestmark = pytest.mark.gpu
+
+HOT, COLD, GIANT = 100, 300, 6
+
+
+def _problem(loss, C, U, m, d, giant, gap, seed=3, op="identity"):
+    """Edges join hot rows (about 2 along axis 0).  Cold rows, reached by the
+    uniform draws only, lie opposite to them: their scores are below the hot
+    ones by `gap`'s range.  Giant rows (2^giant, or none) lie opposite to them
+    too: no probability is left for them, and no hinge selects them."""
+    pb = make_problem(op, "dot", loss, R=1, n=HOT + COLD + GIANT, m=m, d=d, C=C, U=U, S=4, seed=seed)
+    rng = synth.rng_for(seed)
+    x = 0.3 * rng.standard_normal((pb.n, d))
+    x[:HOT, 0] = 2.0
+    x[HOT:, 0] = -np.linspace(*gap, COLD + GIANT) / 2.0 + 2.0
+    if giant is not None:
+        x[HOT + COLD:] = 0.0
+        x[HOT + COLD:, 0] = -(2.0**giant)
+    pb.parts[0][...] = x.astype(np.float32)
+    if pb.rel is not None:
+        pb.rel[...] = 1.0
+    pb.src, pb.dst = (rng.integers(0, HOT, m) for _ in range(2))
+    return pb
+
+
+def _check(pb, eps):
+    gm = GpuModel(pb)
+    try:
+        _, gl, ol, worst = teacher_forced_step(gm, 0, len(pb.src), 0, eps)
+    finally:
+        gm.close()
+    assert abs(gl - ol) <= 1e-5 * max(1.0, abs(ol))
+    assert worst <= 1.0
+
+
+# (C, U, edges, d): both column widths and a remainder of every tile
+SHAPES = [(100, 150, 230, 33), (300, 260, 560, 100), (70, 130, 70, 250), (64, 64, 64, 16)]
+
+
+@pytest.mark.parametrize("C,U,m,d", SHAPES)
+@pytest.mark.parametrize("giant", [None, 20, 45])
+@pytest.mark.parametrize("loss", ["logistic", "softmax"])
+def test_small_probabilities(loss, giant, C, U, m, d):
+    """Scores down to -40 (probabilities of 2^-60; |g| down to Adagrad's
+    epsilon of 1e-10).  A score's error is about d 2^-24 of its absolute sum of
+    up to 100, which is the relative error of its probability: 1e-4 bounds it
+    with the gradient's own 1e-5."""
+    _check(_problem(loss, C, U, m, d, giant, (10.0, 44.0)), 1e-4)
