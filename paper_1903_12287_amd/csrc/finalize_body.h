@@ -6,35 +6,57 @@
 #include "device_common.h"
 
 // ---- row scales of the ranking backward --------------------------------------
-// Every row's fp16 scale relative to the largest row of its (chunk, side) of
-// nn and of qk, 2^(e - e_max + 15), 0 for rows more than 29 binades below it.
-// Each of the chunk's nblk workgroups finds the four largest exponents again
-// (a few thousand floats that the L2 holds; one atomic maximum a row in the
-// gather cost it twenty times its own time) and writes its share of the scales.
+// The rows of nn and of qk differ by powers of two, and an fp16 scale holds 30
+// of them, so rows far below a (chunk, side)'s largest go to further levels:
+// level l takes rows 30 l to 30 l + 29 binades below it with scale
+// 2^(e - e_max + 30 l + 15), the others with 0.  The backward sums a level at a
+// time, so a large row that an edge does not select costs it nothing.  (Rows of
+// zeros belong to no level; one level is the rule.)  Each of the chunk's nblk
+// workgroups finds the four largest and smallest exponents again (a few
+// thousand floats that the L2 holds; one atomic maximum a row in the gather
+// cost it twenty times its own time) and writes its share of the scales.
 __device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b, int c, int Cc, int blk, int nblk) {
-  __shared__ int tops[FIN_THREADS / PBG_WAVE];
+  __shared__ float ends[2][FIN_THREADS / PBG_WAVE];
   const int Nc = Cc + g.U;
   for (int k = 0; k < 4; ++k) {
     const bool nn = k < 2;
     const int z = c * 2 + (k & 1), rows = nn ? Nc : Cc;
     const float* is = nn ? b.pn_is + (int64_t)z * g.N : b.pq_is + (int64_t)z * g.C;
-    float m = 0.0f;
+    float hi = 0.0f, lo = -INFINITY;   // of the scales and of the negated ones, rows of zeros apart
 #pragma unroll 4
-    for (int t = threadIdx.x; t < rows; t += FIN_THREADS) m = fmaxf(m, is[t]);
-    m = group16_max(m);
-    m = fmaxf(m, __shfl_xor(m, 16, PBG_WAVE));
-    m = fmaxf(m, __shfl_xor(m, 32, PBG_WAVE));
+    for (int t = threadIdx.x; t < rows; t += FIN_THREADS) {
+      const float x = is[t];
+      hi = fmaxf(hi, x);
+      lo = fmaxf(lo, x == PIECES_ZERO_ROW ? -INFINITY : -x);
+    }
+    hi = group16_max(hi);
+    lo = group16_max(lo);
+    hi = fmaxf(hi, __shfl_xor(hi, 16, PBG_WAVE));
+    lo = fmaxf(lo, __shfl_xor(lo, 16, PBG_WAVE));
+    hi = fmaxf(hi, __shfl_xor(hi, 32, PBG_WAVE));
+    lo = fmaxf(lo, __shfl_xor(lo, 32, PBG_WAVE));
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) tops[threadIdx.x >> 6] = (int)(__float_as_uint(m) >> 23) + 14;
+    if ((threadIdx.x & 63) == 0) {
+      ends[0][threadIdx.x >> 6] = hi;
+      ends[1][threadIdx.x >> 6] = lo;
+    }
     __syncthreads();
-    int top = tops[0];
-    for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) top = max(top, tops[w]);
-    if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_max : b.pq_max)[z] = top;
-    const int64_t ko = (int64_t)z * (nn ? g.ks_n : g.ks_q);
-    uint16_t* ks = (nn ? b.nks : b.qks) + ko;
+    hi = ends[0][0];
+    lo = ends[1][0];
+    for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) {
+      hi = fmaxf(hi, ends[0][w]);
+      lo = fmaxf(lo, ends[1][w]);
+    }
+    const int top = (int)(__float_as_uint(hi) >> 23) + 14;
+    // no row but rows of zeros: one level of zeros
+    const int levels = lo == -INFINITY ? 1 : (top - ((int)(__float_as_uint(-lo) >> 23) + 14)) / 30 + 1;
+    if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_top : b.pq_top)[z] = make_int2(top, levels);
+    const int ld = nn ? g.ks_n : g.ks_q;
+    uint16_t* ks = (nn ? b.nks : b.qks) + (int64_t)z * KS_LEVELS * ld;
     for (int t = blk * FIN_THREADS + threadIdx.x; t < rows; t += nblk * FIN_THREADS) {
-      const int ex = 30 + (int)(__float_as_uint(is[t]) >> 23) + 14 - top;
-      ks[t] = (uint16_t)(ex > 0 ? ex << 10 : 0);
+      const float x = is[t];
+      int ex = x == PIECES_ZERO_ROW ? 0 : 30 + (int)(__float_as_uint(x) >> 23) + 14 - top;
+      for (int l = 0; l < levels; ++l, ex += 30) ks[(int64_t)l * ld + t] = (uint16_t)(ex > 0 && ex <= 30 ? ex << 10 : 0);
     }
   }
 }

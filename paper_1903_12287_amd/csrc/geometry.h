@@ -21,6 +21,7 @@
 // Row index of candidate t of side s in chunk c: (c*2 + s)*N + t.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 enum { OP_IDENTITY = 0, OP_TRANSLATION = 1, OP_DIAGONAL = 2, OP_LINEAR = 3, OP_COMPLEX = 4 };
@@ -41,6 +42,10 @@ enum { LOSS_RANKING = 0, LOSS_LOGISTIC = 1, LOSS_SOFTMAX = 2 };
 
 // Row pieces of the packed rows (pieces.h) that the gather writes beside them
 enum { PIECES_NONE = 0, PIECES_UNIT = 1, PIECES_SCALED = 2 };
+// inverse scale that marks a row of zeros (1.5 * 2^-126; the others are powers of two)
+#define PIECES_ZERO_ROW 0x1.8p-126f
+// levels of 30 binades that the exponents of the row scales can span
+#define KS_LEVELS 9
 
 struct StepGeom {
   int C, U, N;      // chunk capacity, uniform draws per side, N = C + U
@@ -125,16 +130,17 @@ struct StepBufs {
   float* qk;
   float* nn;
   float* nrm;           // [S][2][N] norms of the raw vectors behind nn (cos)
-  // pieces of nn and qk ([S][2][N or C][pld]); PIECES_SCALED: their rows' inverse scales, the scale exponent of
-  // each (chunk, side)'s largest row, and every row's fp16 scale relative to it
+  // pieces of nn and qk ([S][2][N or C][pld]); PIECES_SCALED: their rows' inverse scales, and for the ranking loss
+  // the scale exponent of each (chunk, side)'s largest row with the number of levels below it, and every row's
+  // fp16 scale in each level
   uint16_t* pn;
   uint16_t* pq;
   float* pn_is;         // [S][2][N]
   float* pq_is;         // [S][2][C]
-  int* pn_max;          // [S][2]
-  int* pq_max;          // [S][2]
-  uint16_t* nks;        // [S][2][ks_n]
-  uint16_t* qks;        // [S][2][ks_q]
+  int2* pn_top;         // [S][2]
+  int2* pq_top;         // [S][2]
+  uint16_t* nks;        // [S][2][KS_LEVELS][ks_n]
+  uint16_t* qks;        // [S][2][KS_LEVELS][ks_q]
   float* pos;           // [S][C] positive scores ([S][2][C] with reciprocal predicates)
   float* bias;          // [S][C] <theta_r, x_d> (translation + dot)
   int32_t* neg;         // [S][2][U] uniform draws (side 0 from partition j, side 1 from i)

@@ -144,9 +144,9 @@ struct BitsArgs {
   int C, U, m_step;
   const int32_t* cstart;
   int merged;                   // dQ of side s, edge e also takes dN of side 1 - s; dN: uniform rows only
-  const uint16_t *nks, *qks;    // fp16 scale of each row relative to the largest (NULL: unit rows)
-  int64_t nks_cs, nks_ss, qks_cs, qks_ss;
-  const int *nmax, *qmax;       // [c][2] scale exponent of the largest row
+  const uint16_t *nks, *qks;    // [c][2][KS_LEVELS][ks_n / ks_q] fp16 scale of each row in each level (NULL: unit rows)
+  int ks_n, ks_q;
+  const int2 *ntop, *qtop;      // [c][2] scale exponent of the largest row, levels
   float unscale;                // factor of the sums (unit rows)
   const float* cscale;          // relation weight of each chunk
   float *dq, *dn;

@@ -14,7 +14,11 @@
 // integer add of the patterns.  (The denormals 2^-24 and 2^-23 would need no
 // shift, but the matrix instruction aligns their products by their unnormalised
 // exponent and loses ten bits of the sums.)  With per-row scales (dot) each
-// k's bit is multiplied by its row's scale relative to the tile's largest row.
+// k's bit is multiplied by its row's scale relative to the chunk's largest row.
+// Where rows differ by more than an fp16 number holds, the scales come in
+// levels of 30 binades (finalize_body.h) and the run over k is made once a
+// level, the smallest rows' first, the accumulators carried from one to the
+// next: a row counts unless it is some 140 binades below the largest.
 //
 // Merged in-chunk block (cos without reciprocal predicates: the queries of a
 // side are the other side's candidates): with B0 the bits of side 0 and B1
@@ -61,7 +65,8 @@ struct BitsPhase {
   int blk;              // first row block (ROW) or column block (COL) of the tile
   const uint16_t* B;    // the B rows
   int K, kmerge;
-  const uint16_t* ks;   // A_SCALED: fp16 scale of each k
+  const uint16_t* ks;   // A_SCALED: fp16 scale of each k, [levels][ld_ks]
+  int ld_ks, levels;
 };
 
 template <int NB, int IM>
@@ -150,9 +155,16 @@ __device__ __forceinline__ void bits_phase(const BitsPhase& p, int ld, int n0, i
   constexpr uint32_t kBit = one_bits(MODE);
   const uint32_t crot = (uint32_t)(l16 + (MODE == A_UNIT ? 22 : 0)) & 31u;
   u32x4 ks = {0u, 0u, 0u, 0u};
-  if (MODE == A_SCALED) ks = *(const u32x4*)(p.ks + 8 * g);
-  for (int kt = 0; kt < nk; ++kt) {
-    const int buf = kt & 1;
+  const int nit = MODE == A_SCALED ? nk * p.levels : nk;   // slices of all levels
+  const uint16_t* lks = p.ks;                              // the level's scales
+  if (MODE == A_SCALED) {
+    lks += (int64_t)(p.levels - 1) * p.ld_ks;
+    ks = *(const u32x4*)(lks + 8 * g);
+  }
+  int lkt = 0;   // slice of the level
+  for (int it = 0; it < nit; ++it) {
+    const int kt = MODE == A_SCALED ? lkt : it;
+    const int buf = it & 1;
     wait_loads();
     __syncthreads();
     const bool merged = MERGE && kt * BK < p.kmerge;
@@ -190,9 +202,14 @@ __device__ __forceinline__ void bits_phase(const BitsPhase& p, int ld, int n0, i
       }
       af[i] = __builtin_bit_cast(v8h, v);
     }
-    if (kt + 1 < nk) {
-      ld_.template slice<MERGE>(sm, buf ^ 1, kt + 1);
-      if (MODE == A_SCALED) ks = *(const u32x4*)(p.ks + (kt + 1) * BK + 8 * g);
+    const bool level_ends = MODE == A_SCALED && kt + 1 == nk;
+    if (MODE == A_SCALED) {
+      lkt = level_ends ? 0 : kt + 1;
+      if (level_ends) lks -= p.ld_ks;
+    }
+    if (it + 1 < nit) {
+      ld_.template slice<MERGE>(sm, buf ^ 1, MODE == A_SCALED ? lkt : it + 1);
+      if (MODE == A_SCALED) ks = *(const u32x4*)(lks + lkt * BK + 8 * g);
     }
     const uint32_t bb = buf * sizeof(sm.B[0]);
 #pragma unroll
@@ -208,6 +225,12 @@ __device__ __forceinline__ void bits_phase(const BitsPhase& p, int ld, int n0, i
 #pragma unroll
         for (int i = 0; i < IM; ++i)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(af[i], bf[q], acc[i][j], 0, 0, 0);
+    }
+    if (level_ends && it + 1 < nit) {
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] *= 0x1p-30f;
     }
   }
 }
@@ -275,27 +298,35 @@ __global__ __launch_bounds__(256, 2) void bits_backward_kernel(BitsArgs a, int t
   const uint16_t* qrows = a.Q + c * a.q_cs + side * a.q_ss;   // queries of this side
   const int CB = a.CB;
   float f = a.unscale;
+  // the scales of the rows of B
+  const uint16_t* ks = nullptr;
+  const int ld_ks = dq ? a.ks_n : a.ks_q;
+  int levels = 1;
+  if (MODE == A_SCALED) {
+    const int z = 2 * c + side;
+    ks = (dq ? a.nks : a.qks) + (int64_t)z * KS_LEVELS * ld_ks;
+    const int2 t = (dq ? a.ntop : a.qtop)[z];
+    f = ldexpf(1.0f, wave_uniform(t.x) - 156);
+    levels = wave_uniform(t.y);
+  }
   if (dq) {
     if (MERGED && side == 1) {
       // in-chunk block by columns, then the uniform candidates by rows
       const BitsPhase p{a.bits0 + c * a.bits_cs, a.bits1 + c * a.bits1_cs, a.RB, a.CB1, m0 >> 4, nrows, Cc,
-                        Cc, nullptr};
+                        Cc, nullptr, 0, 1};
       bits_phase<NB, IM, MODE, true, true>(p, a.ld, n0, a.dh, sm, acc, w, lane);
       __syncthreads();   // the stages are free again
-      const BitsPhase u{bs, nullptr, a.RB, CB, m0 >> 4, nrows + (int64_t)Cc * a.ld, a.U, 0, nullptr};
+      const BitsPhase u{bs, nullptr, a.RB, CB, m0 >> 4, nrows + (int64_t)Cc * a.ld, a.U, 0, nullptr, 0, 1};
       bits_phase<NB, IM, MODE, false, false>(u, a.ld, n0, a.dh, sm, acc, w, lane);
     } else {
       const BitsPhase p{bs, MERGED ? a.bits1 + c * a.bits1_cs : nullptr, a.RB, CB, m0 >> 4, nrows, Nc,
-                        MERGED ? Cc : 0, MODE == A_SCALED ? a.nks + c * a.nks_cs + side * a.nks_ss : nullptr};
+                        MERGED ? Cc : 0, ks, ld_ks, levels};
       bits_phase<NB, IM, MODE, false, MERGED>(p, a.ld, n0, a.dh, sm, acc, w, lane);
     }
-    if (MODE == A_SCALED) f = ldexpf(1.0f, a.nmax[2 * c + side] - 156);
   } else {
     const bool uni = MERGED && side == 1;   // side 1's bits hold the uniform columns only
-    const BitsPhase p{bs, nullptr, a.RB, CB, (uni ? m0 - first : m0) >> 4, qrows, Cc, 0,
-                      MODE == A_SCALED ? a.qks + c * a.qks_cs + side * a.qks_ss : nullptr};
+    const BitsPhase p{bs, nullptr, a.RB, CB, (uni ? m0 - first : m0) >> 4, qrows, Cc, 0, ks, ld_ks, levels};
     bits_phase<NB, IM, MODE, true, false>(p, a.ld, n0, a.dh, sm, acc, w, lane);
-    if (MODE == A_SCALED) f = ldexpf(1.0f, a.qmax[2 * c + side] - 156);
   }
   // the chunk's relation weight scales its gradients (powers of two aside, an
   // ordinary float32 product)

@@ -161,13 +161,11 @@ static void run_bits_backward(const StepGeom& g, const StepBufs& b, hipStream_t 
   a.unscale = 0x1p-1f;   // bits 2^-14, unit rows times 2^15
   if (g.pieces == PIECES_SCALED) {
     a.nks = b.nks;
-    a.nks_cs = 2ll * g.ks_n;
-    a.nks_ss = g.ks_n;
+    a.ks_n = g.ks_n;
     a.qks = b.qks;
-    a.qks_cs = 2ll * g.ks_q;
-    a.qks_ss = g.ks_q;
-    a.nmax = b.pn_max;
-    a.qmax = b.pq_max;
+    a.ks_q = g.ks_q;
+    a.ntop = b.pn_top;
+    a.qtop = b.pq_top;
   }
   a.cscale = g.cweight;
   a.dq = b.dq;

@@ -111,11 +111,11 @@ pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S) {
     if (pieces_of(ctx) == PIECES_SCALED) {
       b.pn_is = (float*)a.get((s * 2 * N + 256) * 4);
       b.pq_is = (float*)a.get((s * 2 * C + 256) * 4);
-      b.pn_max = (int*)a.get(s * 4 * 4);
-      b.pq_max = b.pn_max ? b.pn_max + s * 2 : nullptr;
       if (ranking) {
-        b.nks = (uint16_t*)a.get(s * 2 * round_up(N, 32) * 2);
-        b.qks = (uint16_t*)a.get(s * 2 * round_up(C, 32) * 2);
+        b.pn_top = (int2*)a.get(s * 4 * 8);
+        b.pq_top = b.pn_top ? b.pn_top + s * 2 : nullptr;
+        b.nks = (uint16_t*)a.get(s * 2 * KS_LEVELS * round_up(N, 32) * 2);
+        b.qks = (uint16_t*)a.get(s * 2 * KS_LEVELS * round_up(C, 32) * 2);
       }
     }
   }

@@ -10,9 +10,10 @@ __device__ __forceinline__ void row_pieces(const StepGeom& g, uint16_t* p, float
     pieces::store_row(r, 32768.0f, p, g.d, g.dh, cplx, lane);
     return;
   }
-  const int e = pieces::scale_exponent(pieces::row_absmax(r));
+  const float top = pieces::row_absmax(r);
+  const int e = pieces::scale_exponent(top);
   pieces::store_row(r, pieces::scale_of(e), p, g.d, g.dh, cplx, lane);
-  if (lane == 0) *inv = pieces::inverse_scale_of(e);
+  if (lane == 0) *inv = top == 0.0f ? PIECES_ZERO_ROW : pieces::inverse_scale_of(e);
 }
 
 // row t of side `side` of nn

@@ -56,3 +56,17 @@ def test_small_probabilities(loss, giant, C, U, m, d):
     up to 100, which is the relative error of its probability: 1e-4 bounds it
     with the gradient's own 1e-5."""
     _check(_problem(loss, C, U, m, d, giant, (10.0, 44.0)), 1e-4)
+
+
+@pytest.mark.parametrize("C,U,m,d", SHAPES + [(130, 300, 400, 113), (20, 40, 50, 8)])
+@pytest.mark.parametrize("giant", [None, 20, 45, 90])
+@pytest.mark.parametrize("op", ["identity", "diagonal"])
+def test_ranking_rows_of_unlike_size(op, giant, C, U, m, d):
+    """Candidates up to 2^90 that no hinge selects beside ordinary ones, rows of
+    2^-33 that select candidates no other query does, and rows of zeros."""
+    pb = _problem("ranking", C, U, m, d, giant, (-1.0, 30.0), op=op)
+    pb.parts[0][:10] *= np.float32(2.0**-33)
+    pb.parts[0][HOT:HOT + 10] = 0.0
+    pb.src[::7] = np.arange(len(pb.src[::7])) % 10
+    pb.dst[3::11] = np.arange(len(pb.dst[3::11])) % 10
+    _check(pb, 1e-5)
