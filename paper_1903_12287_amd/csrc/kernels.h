@@ -368,15 +368,14 @@ void launch_check_ids(const int32_t* ids, int64_t n, int32_t limit, uint32_t* fl
 void launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 void launch_check_ids64(const int64_t* ids, int64_t n, int64_t limit, uint32_t* flag, uint32_t bit,
                         hipStream_t s);
-// flag: 1 source, 2 destination, 4 relation id out of range; in device memory
-// and (host_flag) in page-locked host memory, both only ever set
+// flag (device memory, only ever set): 1 source, 2 destination, 4 relation id out of range
 void launch_check_edges(const int32_t* src, int32_t rows_i, const int32_t* dst, int32_t rows_j,
-                        const int32_t* rel, int32_t n_rel, int64_t n, uint32_t* flag, uint32_t* host_flag,
-                        hipStream_t s);
-// bad: device word, nothing is written where it is set (NULL: none)
+                        const int32_t* rel, int32_t n_rel, int64_t n, uint32_t* flag, hipStream_t s);
+// bad: device word (NULL: none); where it is set nothing is written but its value to host_bad (page-locked)
 void launch_score_edges(const StepGeom& g, const float* emb_i, const float* emb_j, const float* relp,
                         const float* relT, const int32_t* src, const int32_t* rel,
-                        const int32_t* dst, int64_t n, const uint32_t* bad, float* out, hipStream_t s);
+                        const int32_t* dst, int64_t n, const uint32_t* bad, uint32_t* host_bad, float* out,
+                        hipStream_t s);
 void launch_sample_negatives(uint64_t seed, uint32_t bucket, int64_t chunk0, int64_t n_chunks, int U,
                              uint32_t rows_j, uint32_t rows_i, int32_t* out, hipStream_t s);
 

@@ -27,11 +27,10 @@ __global__ void check_ids64_kernel(const int64_t* ids, int64_t n, int64_t limit,
 }
 
 // the id checks of a call's edges in one pass: bits 1, 2 and 4 (source,
-// destination, relation) into the device word that the kernels behind it read
-// and into the host's
+// destination, relation) into the device word that the kernel behind it reads
 __global__ __launch_bounds__(256) void check_edges_kernel(const int32_t* src, int32_t rows_i, const int32_t* dst,
                                                           int32_t rows_j, const int32_t* rel, int32_t n_rel,
-                                                          int64_t n, uint32_t* flag, uint32_t* host_flag) {
+                                                          int64_t n, uint32_t* flag) {
   uint32_t bad = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -40,24 +39,28 @@ __global__ __launch_bounds__(256) void check_edges_kernel(const int32_t* src, in
     bad |= (d < 0) | (d >= rows_j) ? 2u : 0u;
     bad |= rel && ((r < 0) | (r >= n_rel)) ? 4u : 0u;
   }
-  if (bad) {
-    atomicOr(flag, bad);
-    atomicOr_system(host_flag, bad);
-  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) bad |= (uint32_t)__shfl_xor((int)bad, o, PBG_WAVE);
+  if (bad && (threadIdx.x & 63) == 0) atomicOr(flag, bad);
 }
 
-// f(s, r, d) = sim(g(x_s, theta_r), x_d), one wave per edge; nothing is written
-// where *bad is set
+// f(s, r, d) = sim(g(x_s, theta_r), x_d), one wave per edge; where *bad is set
+// the first wave hands its value to the host and nothing else is written
 __global__ __launch_bounds__(256) void score_edges_kernel(StepGeom g, const float* emb_i,
                                                           const float* emb_j, const float* relp,
                                                           const float* relT, const int32_t* src,
                                                           const int32_t* rel, const int32_t* dst,
-                                                          int64_t n, const uint32_t* bad, float* out) {
+                                                          int64_t n, const uint32_t* bad, uint32_t* host_bad,
+                                                          float* out) {
   __shared__ float stage[4][512];
   const int lane = threadIdx.x & 63;
   const int w = threadIdx.x >> 6;
   const int64_t e = (int64_t)blockIdx.x * 4 + w;
-  if (e >= n || (bad && *bad)) return;
+  if (e >= n) return;
+  if (bad && *bad) {
+    if (e == 0 && lane == 0) *(volatile uint32_t*)host_bad = *bad;
+    return;
+  }
   const bool cplx = g.op == OP_COMPLEX;
   const int d = g.d;
   const int r = rel ? rel[e] : 0;
@@ -121,19 +124,19 @@ void launch_check_ids64(const int64_t* ids, int64_t n, int64_t limit, uint32_t* 
 }
 
 void launch_check_edges(const int32_t* src, int32_t rows_i, const int32_t* dst, int32_t rows_j,
-                        const int32_t* rel, int32_t n_rel, int64_t n, uint32_t* flag, uint32_t* host_flag,
-                        hipStream_t s) {
+                        const int32_t* rel, int32_t n_rel, int64_t n, uint32_t* flag, hipStream_t s) {
   if (n <= 0) return;
-  check_edges_kernel<<<blocks_for(n), 256, 0, s>>>(src, rows_i, dst, rows_j, rel, n_rel, n, flag, host_flag);
+  check_edges_kernel<<<blocks_for(n), 256, 0, s>>>(src, rows_i, dst, rows_j, rel, n_rel, n, flag);
 }
 
 void launch_score_edges(const StepGeom& g, const float* emb_i, const float* emb_j, const float* relp,
                         const float* relT, const int32_t* src, const int32_t* rel,
-                        const int32_t* dst, int64_t n, const uint32_t* bad, float* out, hipStream_t s) {
+                        const int32_t* dst, int64_t n, const uint32_t* bad, uint32_t* host_bad, float* out,
+                        hipStream_t s) {
   if (n <= 0) return;
   const int64_t blocks = (n + 3) / 4;
   score_edges_kernel<<<(unsigned)blocks, 256, 0, s>>>(g, emb_i, emb_j, relp, relT, src, rel, dst, n,
-                                                      bad, out);
+                                                      bad, host_bad, out);
 }
 
 void launch_sample_negatives(uint64_t seed, uint32_t bucket, int64_t chunk0, int64_t n_chunks, int U,

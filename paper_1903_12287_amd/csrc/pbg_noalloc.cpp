@@ -100,7 +100,7 @@ extern "C" pbg_status pbg_score_edges_noalloc(pbg_ctx* ctx, int32_t i, int32_t j
   g.op = ctx->op;
   g.cmp = ctx->cmp;
   if (relT) launch_transpose_rel(ctx->relp, relT, ctx->R, ctx->d, cs);
-  launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, nullptr, scores, cs);
+  launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, nullptr, nullptr, scores, cs);
   e = hipGetLastError();
   if (e == hipSuccess) e = hipStreamSynchronize(cs);
   if (e != hipSuccess) return hip_fail(ctx, e, "score_edges_noalloc");

@@ -942,6 +942,16 @@ pbg_status ensure_edge_flags(pbg_ctx* ctx) {
     }
     ctx->edge_flag = p;
   }
+  if (ctx->edge_dirty) {
+    // nothing of an earlier call may still write them
+    hipError_t e = hipStreamSynchronize(ctx->cs);
+    if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
+    *ctx->edge_hflag = 0;
+    launch_fill_u32(ctx->edge_flag, 1, 0u, ctx->cs);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(ctx, e, "id range check");
+    ctx->edge_dirty = false;
+  }
   return PBG_OK;
 }
 
@@ -964,8 +974,8 @@ extern "C" pbg_status pbg_score_edges(pbg_ctx* ctx, int32_t i, int32_t j, const 
   if (ctx->R > 1 && !rel) return set_err(ctx, PBG_ERR_INVALID_ARG, "rel may be NULL only with one relation");
   if (!src_local || !dst_local || !scores) return set_err(ctx, PBG_ERR_INVALID_ARG, "NULL array");
   hipStream_t cs = ctx->cs;
-  // The check's flags live as long as the context, are 0 between calls, and
-  // the score kernel reads them itself: two launches and one wait a call.
+  // The check's flags live as long as the context, and the score kernel reads
+  // the verdict itself: two launches and one wait a call.
   // (Allocating, clearing and copying a flag and waiting for it before the
   // scores: 46 us a call for 4,000 edges of d = 128, now 21.)
   pbg_status st = ensure_edge_flags(ctx);
@@ -976,8 +986,9 @@ extern "C" pbg_status pbg_score_edges(pbg_ctx* ctx, int32_t i, int32_t j, const 
     e = hipMalloc(&relT, (size_t)ctx->R * ctx->d * ctx->d * 4);
     if (e != hipSuccess) return hip_fail(ctx, e, "hipMalloc");
   }
+  ctx->edge_dirty = true;
   launch_check_edges(src_local, (int32_t)pbg_partition_rows(ctx, i), dst_local, (int32_t)pbg_partition_rows(ctx, j),
-                     rel, ctx->R, n, ctx->edge_flag, ctx->edge_hflag, cs);
+                     rel, ctx->R, n, ctx->edge_flag, cs);
   StepGeom g;
   memset(&g, 0, sizeof(g));
   g.d = ctx->d;
@@ -985,20 +996,19 @@ extern "C" pbg_status pbg_score_edges(pbg_ctx* ctx, int32_t i, int32_t j, const 
   g.dr = ctx->dr;
   g.op = ctx->op;
   g.cmp = ctx->cmp;
-  if (relT) launch_transpose_rel(ctx->relp, relT, ctx->R, ctx->d, cs);
-  launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, ctx->edge_flag, scores, cs);
   e = hipGetLastError();
-  if (e == hipSuccess) e = hipStreamSynchronize(cs);
-  const uint32_t flag = *(volatile uint32_t*)ctx->edge_hflag;
-  if (e != hipSuccess) {
-    st = hip_fail(ctx, e, "score_edges");
-  } else if (flag) {
-    *ctx->edge_hflag = 0;
-    launch_fill_u32(ctx->edge_flag, 1, 0u, cs);
-    e = hipStreamSynchronize(cs);
-    st = e != hipSuccess ? hip_fail(ctx, e, "id range check")
-                         : set_err(ctx, PBG_ERR_INVALID_ARG, "an id is out of range (flags %u)", flag);
+  if (e == hipSuccess) {   // no scores behind a check that did not start
+    if (relT) launch_transpose_rel(ctx->relp, relT, ctx->R, ctx->d, cs);
+    launch_score_edges(g, pi.emb, pj.emb, ctx->relp, relT, src_local, rel, dst_local, n, ctx->edge_flag,
+                       ctx->edge_hflag, scores, cs);
+    e = hipGetLastError();
   }
+  const hipError_t es = hipStreamSynchronize(cs);   // also after an error: what was launched reads the caller's arrays
+  if (e == hipSuccess) e = es;
+  const uint32_t flag = *(volatile uint32_t*)ctx->edge_hflag;
+  if (e != hipSuccess) st = hip_fail(ctx, e, "score_edges");
+  else if (flag) st = set_err(ctx, PBG_ERR_INVALID_ARG, "an id is out of range (flags %u)", flag);
+  else ctx->edge_dirty = false;   // else the next call clears them
   if (relT) (void)hipFree(relT);
   return st;
 }

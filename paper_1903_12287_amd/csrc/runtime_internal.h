@@ -94,8 +94,9 @@ struct pbg_ctx {
   uint32_t* flag_dev = nullptr;
   uint32_t* hflag = nullptr;          // page-locked copy of the id check's flags
   hipEvent_t check_ev = nullptr;      // the copy has landed
-  uint32_t* edge_flag = nullptr;      // pbg_score_edges' id check: a device word and its page-locked twin,
-  uint32_t* edge_hflag = nullptr;     // 0 between calls
+  uint32_t* edge_flag = nullptr;      // pbg_score_edges' id check: its verdict in device memory and, where an id is
+  uint32_t* edge_hflag = nullptr;     // out of range, in page-locked memory; both 0 ...
+  bool edge_dirty = false;            // ... unless a call ended without knowing so
   bool check_pending = false;
   double* steploss_dev = nullptr;
   int64_t steploss_cap = 0;
@@ -157,9 +158,9 @@ pbg_status check_bucket_call(pbg_ctx* ctx, int32_t i, int32_t j, const int32_t* 
 // the id range check's verdict (waits for it); with defer the check above only
 // launches it, and the caller finishes it once it has queued work that needs
 // no valid ids (check_pending)
-// the flags of pbg_score_edges' id check, allocated once a context
-pbg_status ensure_edge_flags(pbg_ctx* ctx);
 pbg_status finish_id_check(pbg_ctx* ctx, int32_t i, int32_t j);
+// the flags of pbg_score_edges' id check: allocated once a context, and cleared
+pbg_status ensure_edge_flags(pbg_ctx* ctx);
 pbg_status ensure_workspace(pbg_ctx* ctx, int C, int U, int S);
 // chunk bounds of a call's edges for PBG_CHUNK_BY_RELATION (rel: device, n
 // edges sorted by relation): ctx->cstart_host / cstart_dev; INVALID_ARG when
