@@ -230,7 +230,7 @@ inline int op_backward_blocks(int C, int U, int cmp) {
 // ---- sort, segments, updates ----------------------------------------------------
 // sorted positions per wave of the segment update: 8 up to SEG_SHORT_MAX
 // positions, else 32
-#define SEG_SHORT_MAX 65536
+#define SEG_SHORT_MAX 16384
 inline int64_t segment_blocks(int64_t n) { return n / 8 + 2; }
 
 struct SortWork {

@@ -578,19 +578,25 @@ __global__ __launch_bounds__(256) void seg_update_span(StepGeom g, StepBufs b, c
   const int nparts = 1 + nfull + 1;   // block of s, the covered blocks, the block where it ends
   RowT<RQ> acc;
   row_zero(acc);
+  // Lanes past the row and pieces past the last load what is there and count
+  // as 0: a branch around each load took longer than the loads.
+  int fl[RQ];
+#pragma unroll
+  for (int q = 0; q < RQ; ++q) fl[q] = min(lane + 64 * q, width - 1);
   for (int i0 = 0; i0 < nparts; i0 += 16) {
     float t[16][RQ];
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      const int i = i0 + u;
+      const int i = min(i0 + u, nparts - 1);
       const int at = i == 0 ? s : p1 + (i - 1) * LEN;
       const float* part = partial + (int64_t)at * width;
 #pragma unroll
-      for (int q = 0; q < RQ; ++q) {
-        const int f = lane + 64 * q;
-        t[u][q] = (i < nparts && f < width) ? part[f] : 0.0f;
-      }
+      for (int q = 0; q < RQ; ++q) t[u][q] = part[fl[q]];
     }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+#pragma unroll
+      for (int q = 0; q < RQ; ++q) t[u][q] = i0 + u < nparts && lane + 64 * q < width ? t[u][q] : 0.0f;
 #pragma unroll
     for (int u = 0; u < 16; ++u)
 #pragma unroll
@@ -758,12 +764,17 @@ static void seg_update(const StepGeom& g, const StepBufs& b, const uint32_t* key
     local<<<blocks + extra1, 256, 0, s>>>(g, b, keys, vals, n, rows, ld, width, w.partial, w.segflag, lr, rr, blocks);
     span<<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr, blocks);
   };
-  // A wave's block is a serial chain, so few positions go in short blocks:
-  // 16,000 of d = 32 took 18 + 4.5 us (this pass and the crossing segments) in
-  // blocks of 32, 500 waves on 1,024 SIMDs, and take 8.5 + 6.8 us in blocks of
-  // 8; 45,000 of d = 200 took 23 + 7.6 us and take 13.7 + 11.3 us.  More
-  // pieces cross a block's end, though: with the few, long segments of the
-  // relations (40,000 positions, 5,000 relations) 13 + 61 us for 24 + 19 us.
+  // A wave's block is a serial chain, so few positions go in short blocks (512
+  // waves of 32 for 1,024 SIMDs at the line).  Four times as many pieces cross a
+  // block's end, though, and one wave adds a long segment's.  The line is where
+  // that costs what the blocks save even where a few rows hold most positions.
+  // Both passes together, blocks of 32 and of 8, d = 128, at the line (16,368
+  // positions) a million rows alike 24.5 and 14.1 us, 10,000 rows by Zipf's law
+  // with exponent 1.1 20.6 and 14.7, with 1.5 21.7 and 20.2, 20 rows 13.7 and
+  // 14.2; at 24,552 24.5 and 16.0, 19.7 and 17.1, 21.7 and 25.0, 14.7 and 17.0;
+  // at 65,472 32.2 and 27.4, 20.2 and 29.5, 26.7 and 51.2, 20.3 and 36.6.
+  // Relations, few and long, keep 32 (40,000 positions, 5,000 relations: 24 +
+  // 19 us, in blocks of 8 13 + 61).
   const bool few = MODE == SEG_ENTITY && n <= SEG_SHORT_MAX;
   if (width <= 128) {
     few ? launch(seg_update_local<MODE, 2, 8>, seg_update_span<MODE, 2, 8>, 8)

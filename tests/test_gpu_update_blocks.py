@@ -1,5 +1,6 @@
 """The sorted update on both sides of the number of positions at which its
-blocks grow from 8 to 32 (65,536): one step against the oracle."""
+blocks grow from 8 to 32 (16,384), and well past it: one step against the
+oracle."""
 import numpy as np
 import pytest
 
@@ -9,13 +10,14 @@ from tests.pbg_cases import GpuModel, make_problem, oracle_model
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("S", [8, 32])
 @pytest.mark.parametrize("n,U,d", [(1500, 511, 16), (1500, 512, 16), (1500, 513, 16), (40, 512, 130), (40, 513, 130),
                                    (300, 512, 260), (300, 513, 260)])
-def test_update_around_the_block_line(n, U, d):
-    """32 chunks of 512 edges: 65,472, 65,536 and 65,600 positions.  A row sums
-    up to 20,000 float32 terms (the Zipf head among 40 rows): 20,000 x 2^-24 =
+def test_update_around_the_block_line(n, U, d, S):
+    """Chunks of 512 edges: 16,368, 16,384 and 16,400 positions, and four times
+    as many.  A row sums up to 20,000 float32 terms (the Zipf head among 40 rows): 20,000 x 2^-24 =
     1.2e-3 of its absolute sum at worst."""
-    pb = make_problem("translation", "dot", "logistic", n=n, m=32 * 512, d=d, C=512, U=U, S=32, seed=3)
+    pb = make_problem("translation", "dot", "logistic", n=n, m=S * 512, d=d, C=512, U=U, S=S, seed=3)
     gm = GpuModel(pb)
     try:
         gl = gm.train()
