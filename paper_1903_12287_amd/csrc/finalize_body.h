@@ -16,36 +16,57 @@
 // thousand floats that the L2 holds; one atomic maximum a row in the gather
 // cost it twenty times its own time) and writes its share of the scales.
 __device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b, int c, int Cc, int blk, int nblk) {
-  __shared__ float ends[2][FIN_THREADS / PBG_WAVE];
+  constexpr int WAVES = FIN_THREADS / PBG_WAVE;
+  __shared__ float ends[4][WAVES][2];   // of the scales and of the negated ones, rows of zeros apart
   const int Nc = Cc + g.U;
+  auto scales = [&](int k) {
+    const int z = c * 2 + (k & 1);
+    return k < 2 ? b.pn_is + (int64_t)z * g.N : b.pq_is + (int64_t)z * g.C;
+  };
+  // each thread's first rows of all four, on their way together (a small step
+  // has no others)
+  const int own = blk * FIN_THREADS + threadIdx.x;
+  float first[4], mine[4];
+#pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const bool nn = k < 2;
-    const int z = c * 2 + (k & 1), rows = nn ? Nc : Cc;
-    const float* is = nn ? b.pn_is + (int64_t)z * g.N : b.pq_is + (int64_t)z * g.C;
-    float hi = 0.0f, lo = -INFINITY;   // of the scales and of the negated ones, rows of zeros apart
-#pragma unroll 4
-    for (int t = threadIdx.x; t < rows; t += FIN_THREADS) {
-      const float x = is[t];
+    const int rows = k < 2 ? Nc : Cc;
+    first[k] = (int)threadIdx.x < rows ? scales(k)[threadIdx.x] : PIECES_ZERO_ROW;
+    mine[k] = own < rows ? scales(k)[own] : 0.0f;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float* is = scales(k);
+    const int rows = k < 2 ? Nc : Cc;
+    float hi = 0.0f, lo = -INFINITY;
+    auto add = [&](float x) {
       hi = fmaxf(hi, x);
       lo = fmaxf(lo, x == PIECES_ZERO_ROW ? -INFINITY : -x);
-    }
+    };
+    add(first[k]);
+#pragma unroll 4
+    for (int t = threadIdx.x + FIN_THREADS; t < rows; t += FIN_THREADS) add(is[t]);
     hi = group16_max(hi);
     lo = group16_max(lo);
     hi = fmaxf(hi, __shfl_xor(hi, 16, PBG_WAVE));
     lo = fmaxf(lo, __shfl_xor(lo, 16, PBG_WAVE));
     hi = fmaxf(hi, __shfl_xor(hi, 32, PBG_WAVE));
     lo = fmaxf(lo, __shfl_xor(lo, 32, PBG_WAVE));
-    __syncthreads();
     if ((threadIdx.x & 63) == 0) {
-      ends[0][threadIdx.x >> 6] = hi;
-      ends[1][threadIdx.x >> 6] = lo;
+      ends[k][threadIdx.x >> 6][0] = hi;
+      ends[k][threadIdx.x >> 6][1] = lo;
     }
-    __syncthreads();
-    hi = ends[0][0];
-    lo = ends[1][0];
-    for (int w = 1; w < FIN_THREADS / PBG_WAVE; ++w) {
-      hi = fmaxf(hi, ends[0][w]);
-      lo = fmaxf(lo, ends[1][w]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const bool nn = k < 2;
+    const int z = c * 2 + (k & 1), rows = nn ? Nc : Cc;
+    const float* is = scales(k);
+    float hi = ends[k][0][0], lo = ends[k][0][1];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      hi = fmaxf(hi, ends[k][w][0]);
+      lo = fmaxf(lo, ends[k][w][1]);
     }
     const int top = (int)(__float_as_uint(hi) >> 23) + 14;
     // no row but rows of zeros: one level of zeros
@@ -53,8 +74,8 @@ __device__ __forceinline__ void row_scales(const StepGeom& g, const StepBufs& b,
     if (blk == 0 && threadIdx.x == 0) (nn ? b.pn_top : b.pq_top)[z] = make_int2(top, levels);
     const int ld = nn ? g.ks_n : g.ks_q;
     uint16_t* ks = (nn ? b.nks : b.qks) + (int64_t)z * KS_LEVELS * ld;
-    for (int t = blk * FIN_THREADS + threadIdx.x; t < rows; t += nblk * FIN_THREADS) {
-      const float x = is[t];
+    for (int t = own; t < rows; t += nblk * FIN_THREADS) {
+      const float x = t == own ? mine[k] : is[t];
       int ex = x == PIECES_ZERO_ROW ? 0 : 30 + (int)(__float_as_uint(x) >> 23) + 14 - top;
       for (int l = 0; l < levels; ++l, ex += 30) ks[(int64_t)l * ld + t] = (uint16_t)(ex > 0 && ex <= 30 ? ex << 10 : 0);
     }
