@@ -29,6 +29,12 @@ using namespace pieces;
 
 constexpr int BN = 128, BK = 32, STAGES = 3;
 
+// What the candidates' scales give to the queries' (SCALED; the ranks take
+// theirs through the exponent): an accumulator times a candidate's scale must
+// not overflow where the score does not.  2^-23 is the most that the smallest
+// scale, 2^-126, can give.
+constexpr float kColShare = 0x1p-23f;
+
 struct ScoreTile {
   int c, side, tm, tn, m0, n0, M, N, Cc;
   int64_t nrow0;   // candidate row of column 0
@@ -461,7 +467,7 @@ __device__ __forceinline__ void store_epilogue(const ScoreArgs& a, const ScoreTi
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int n = t.n0 + 64 * wn + 16 * j + l16;
-        const float s = (acc[i][j][r] * scl[r]) * sm.cscl[64 * wn + 16 * j + l16];
+        const float s = (acc[i][j][r] * sm.cscl[64 * wn + 16 * j + l16]) * scl[r];
         if (n < t.N) Cm[(int64_t)m * a.ldc + t.nrow0 + n] = s;
         if (SHARED && n < t.M) (a.Cm + t.c * a.c_cs + a.c_ss)[(int64_t)n * a.ldc + m] = s;
       }
@@ -565,7 +571,7 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
     // last
     auto spread = [&]() {
       if (!col) {
-        sm.scl[own] = SCALED ? scl : a.unscale;
+        sm.scl[own] = !SCALED ? a.unscale : (EPI == EPI_RANK ? scl : scl * (1.0f / kColShare));
         if (EPI == EPI_LOSS || EPI == EPI_SOFTMAX_EXP) sm.thr[own] = bias;
         if (EPI == EPI_RANK) {
           sm.thr[own] = p;
@@ -573,10 +579,11 @@ __global__ __launch_bounds__(128 * WR, WR / 2) void score_kernel(ScoreArgs a, Ti
         }
         if (EPI == EPI_LOSS_BITS) {   // the scale's inverse is exact: a power of two
           sm.thr[own] = thr;
-          sm.nthr[own] = cur.m0 + own < cur.M ? -thr * (SCALED ? __builtin_amdgcn_rcpf(scl) : a.iunscale) : INFINITY;
+          sm.nthr[own] = cur.m0 + own < cur.M ? -thr * (SCALED ? __builtin_amdgcn_rcpf(scl) * kColShare : a.iunscale) : INFINITY;
         }
       } else if (own < BN) {
-        sm.cscl[own] = cur.n0 + own < cur.N ? scl : 1.0f;   // the masked -inf stay so
+        sm.cscl[own] = cur.n0 + own >= cur.N ? 1.0f   // the masked -inf stay so
+                       : (SCALED && EPI != EPI_RANK ? scl * kColShare : scl);
         if (EPI == EPI_LOSS_BITS) {
           sm.thr1[own] = thr;
           sm.nthr1[own] = cur.n0 + own < cur.M ? -thr * a.iunscale : INFINITY;

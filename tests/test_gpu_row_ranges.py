@@ -5,8 +5,9 @@ size."""
 import numpy as np
 import pytest
 
+from oracle import pbg_oracle as O
 from paper_1903_12287_amd import synth
-from tests.pbg_cases import GpuModel, make_problem, teacher_forced_step
+from tests.pbg_cases import GpuModel, make_problem, oracle_model, teacher_forced_step
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +71,22 @@ def test_ranking_rows_of_unlike_size(op, giant, C, U, m, d):
     pb.src[::7] = np.arange(len(pb.src[::7])) % 10
     pb.dst[3::11] = np.arange(len(pb.dst[3::11])) % 10
     _check(pb, 1e-5)
+
+
+@pytest.mark.parametrize("loss", ["ranking", "logistic", "softmax"])
+def test_scores_near_the_largest_float(loss):
+    """A candidate of 2^118 that every hinge selects: its scores, 2^119, are
+    finite, and so are the loss and the embeddings (its accumulators are not)."""
+    pb = _problem(loss, 100, 150, 230, 33, None, (10.0, 20.0))
+    pb.parts[0][HOT + COLD:] = 0.0
+    pb.parts[0][HOT + COLD:, 0] = 2.0**118
+    gm = GpuModel(pb)
+    try:
+        gl = gm.train()
+        emb = gm.state()["emb"][0]
+    finally:
+        gm.close()
+    with np.errstate(all="ignore"):
+        ol = O.train_bucket(oracle_model(pb), 0, 0, pb.src, None, pb.dst, pb.C, pb.U, pb.S, pb.lr, pb.seed)
+    assert abs(gl - ol) <= 1e-5 * abs(ol)
+    assert np.isfinite(emb).all()
