@@ -54,8 +54,13 @@ __device__ __forceinline__ uint32_t split2(float x) {
 __device__ __forceinline__ void split2_pair(float a, float b, uint32_t& h, uint32_t& l) {
   __asm__("" : "+v"(a), "+v"(b));
   const h2_t hh = {(_Float16)a, (_Float16)b};
-  const h2_t ll = {(_Float16)(a - (float)hh.x), (_Float16)(b - (float)hh.y)};
   h = __builtin_bit_cast(uint32_t, hh);
+  // the exact remainders, h's halves read where they are (the compiler converts
+  // each back to float32: eight instructions a pair for four)
+  float ra, rb;
+  __asm__("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(h), "v"(a));
+  __asm__("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(h), "v"(b));
+  const h2_t ll = {(_Float16)ra, (_Float16)rb};
   l = __builtin_bit_cast(uint32_t, ll);
 }
 
