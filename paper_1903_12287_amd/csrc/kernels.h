@@ -92,14 +92,13 @@ void launch_to_bf16_t(const float* q, int64_t q_bs, int q_rows, uint16_t* qh, in
 // StepGeom::dq_has_dn (merged): side 0 holds all its candidates; the second
 // plane holds, at (edge e, edge i), side 1's bit of edge i and in-chunk
 // candidate e; side 1's own bits start at the first uniform candidate.
+// First plane [S][2][CB][RB][8] (StepBufs::bits0), second [S][CB1][RB][8]
+// (StepBufs::bits1).
 struct BitsView {
-  uint32_t* b0;           // [S][2][CB][RB][8]
-  uint32_t* b1;           // [S][CB1][RB][8], merged only
   int RB, CB, CB1;
 };
 inline BitsView bits_view(int C, int U) {
-  BitsView v{nullptr, nullptr, (C + 255) / 256 * 16, (C + U + 127) / 128 * 8, (C + 127) / 128 * 8};
-  return v;
+  return BitsView{(C + 255) / 256 * 16, (C + U + 127) / 128 * 8, (C + 127) / 128 * 8};
 }
 
 struct ScoreArgs {
@@ -119,7 +118,6 @@ struct ScoreArgs {
   int pos_sides;
   const float* bias;
   float margin;
-  int loss;
   float* rowpart;               // [c][2][C][nct][2], column blocks of 64 (share: side 1's in-chunk
   int nct;                      // blocks first, then its uniform ones)
   uint32_t *bits0, *bits1;

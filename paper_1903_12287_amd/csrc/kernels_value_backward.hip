@@ -20,6 +20,14 @@
 // rows, so only B needs a barrier and A a single stage.  Wide tiles (NB = 13)
 // read dS half as often where the rows are long: at d = 400 two column tiles
 // instead of four.
+//
+// Measured a step in traces: softmax, d = 400, 40 chunks of 1,000 edges and
+// 1,000 uniform negatives 1,065 us; logistic, d = 100, as many chunks 346 us.
+// (With one fixed power for all rows, A staged by the whole workgroup between
+// two barriers and the B fragments read just before their products 1,020 and
+// 404 us.)  A slice costs a wave 1,250 cycles of products at NB = 13 and about
+// 140 vector instructions; the rest is the wait for dS, which comes from memory
+// once a column tile.
 #include <algorithm>
 
 #include "kernels.h"

@@ -114,7 +114,6 @@ static ScoreArgs score_args_pieces(const StepGeom& g, const StepBufs& b) {
   a.bias = (g.op == OP_TRANSLATION && g.cmp == CMP_DOT && !g.recip) ? b.bias : nullptr;
   a.rowpart = b.rowpart;
   a.nct = g.nct;
-  a.loss = g.loss;
   a.margin = g.margin;
   a.bits0 = b.bits0;
   a.bits1 = b.bits1;

@@ -2,12 +2,13 @@
 //
 // A float32 row x is kept as two float16 planes h and l of the row times a
 // power of two, x 2^r = h + l: h = fp16(x 2^r) rounds to nearest, l = fp16 of
-// the exact remainder.  The remainder has at most 13 significant bits, of
-// which l keeps 11, so h + l holds x to within 2^-23 of its own power of two,
-// and half of all remainders are held exactly.  r puts the row's largest
-// element in [2^14, 2^15): elements down to 2^-18 of it keep the full
-// precision (h and l normal), smaller ones an absolute error of 2^-40 of the
-// largest.  Rows of unit length take the fixed r = 15.
+// the exact remainder.  Above x's power of two 2^E the remainder is a multiple
+// of 2^(E-23) up to 2^(E-11), l a multiple of 2^(E-22) (2^(E-23) in the lower
+// half) or of fp16's smallest step 2^-24 if that is more: h + l holds x to
+// within max(2^(E-23), 2^-25), and exactly for three of four elements.  r puts
+// the row's largest element in [2^14, 2^15), so elements down to 2^-16 of it
+// are within 2^-23 of their own power of two, smaller ones within 2^-39 of the
+// largest element's.  Rows of unit length take the fixed r = 15.
 //
 // A row is ceil(dim / 32) blocks of 128 bytes, 32 elements of h and the same
 // 32 of l: a 32-deep slice of both planes is one cache line.  (With a plane
@@ -212,11 +213,6 @@ __device__ __forceinline__ v8h kr_fragment(uint32_t a0, uint32_t a1) {
   const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s*)(uintptr_t)a1);
   typedef short v8s __attribute__((ext_vector_type(8)));
   return __builtin_bit_cast(v8h, (v8s)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-__device__ __forceinline__ v4f mfma(bool bf16, v8h a, v8h b, v4f c) {
-  return bf16 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0)
-              : __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
 // vmcnt(0): this wave's loads (to LDS included) have landed
