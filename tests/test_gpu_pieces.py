@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from oracle import pbg_oracle as O
-from tests.pbg_cases import GpuModel, make_problem, oracle_model
+from tests.pbg_cases import GpuModel, gpu_inspect, make_problem, oracle_model
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,29 @@ def test_value_loss_step_at_tile_edges(op, cmp, loss, C, U, m, d):
     assert abs(gl - ol) <= 1e-5 * max(1.0, abs(ol))
     for got, want, rel in ((st["G"][0], om.G[0], 1e-5), (st["emb"][0], om.emb[0], 1e-4), (st["rel"], om.rel, 1e-4)):
         assert np.max(np.abs(got - want)) <= rel * max(1.0, float(np.max(np.abs(want)))) + 1e-6
+
+
+@pytest.mark.parametrize("d,bound", [(8, 2.0**-25), (16, 2.07e-8), (32, 2.09e-8), (64, 1.85e-8), (128, 1.72e-8),
+                                     (400, 1.70e-8)])
+def test_score_error_against_float64(d, bound):
+    """Root mean square error of the scores relative to |a| |b|.  From d = 16 on
+    the bound is what float32 operands as three exact bfloat16 pieces and six
+    products reach on the same rows, where the rounding of the sums counts; at
+    d = 8 the two planes' own 2^-24 an operand does (half of 2^-24 in all)."""
+    C, U, m = 500, 500, 1000
+    pb = make_problem("identity", "dot", "ranking", n=3000, m=m, d=d, C=C, U=U, S=2, sigma=1.0, zipf=0.2, seed=1)
+    gm = GpuModel(pb)
+    try:
+        got, _ = gpu_inspect(gm, 0, m, 0)
+    finally:
+        gm.close()
+    om = oracle_model(pb)
+    want = O.inspect_step(om, 0, 0, pb.src, None, pb.dst, C, U, pb.seed, 0)
+    negs = O.step_negatives(om, 0, 0, O.make_chunks(m, C, None, "consecutive"), pb.seed, U)
+    norm = np.linalg.norm(om.emb[0], axis=1)
+    sq = []
+    for c, (a, b) in enumerate(zip(got, want)):
+        q, t = norm[pb.src[C * c:C * (c + 1)]], norm[np.r_[pb.dst[C * c:C * (c + 1)], negs[c][0]]]
+        e = (a["S0"] - b["S0"]) / (q[:, None] * t)
+        sq.append(e[~np.eye(C, C + U, dtype=bool)] ** 2)   # a chunk's own destination is no candidate
+    assert np.sqrt(np.mean(np.concatenate(sq))) <= bound
