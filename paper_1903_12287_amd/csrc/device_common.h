@@ -130,11 +130,19 @@ __device__ __forceinline__ float sigmoidf(float x) {
   return e / (1.0f + e);
 }
 
-// 1 / x for normal x within one unit in the last place: the hardware estimate
-// and one Newton step (three instructions; an IEEE division takes ten)
+// 1 / x and a / x for normal x: the hardware estimate, a Newton step and, for
+// the quotient, its residual added (three and six instructions; an IEEE
+// division takes ten).  Where the logistic divides both round as the IEEE
+// division does: compared for every float32 u of [1, 2] (1 / u) and every
+// e of [2^-25, 1] (e / ((1 + e) - 1); without the residual one in four differs
+// by a unit).
 __device__ __forceinline__ float rcp_newton(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(fmaf(-x, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float div_newton(float a, float x) {
+  const float r = rcp_newton(x), q = a * r;
+  return fmaf(fmaf(-x, q, a), r, q);
 }
 
 // sigmoid(s) and softplus(s) = log(1 + e^s) from one exponential
@@ -147,7 +155,7 @@ __device__ __forceinline__ void logistic_pair(float s, float& sig, float& sp) {
   const float r = rcp_newton(u);
   sig = s >= 0.0f ? r : e * r;
   const float um1 = u - 1.0f;
-  const float l1p = um1 == 0.0f ? e : __logf(u) * (e * rcp_newton(um1));
+  const float l1p = um1 == 0.0f ? e : __logf(u) * div_newton(e, um1);
   sp = fmaxf(s, 0.0f) + l1p;
 }
 
