@@ -90,3 +90,35 @@ def test_scores_near_the_largest_float(loss):
         ol = O.train_bucket(oracle_model(pb), 0, 0, pb.src, None, pb.dst, pb.C, pb.U, pb.S, pb.lr, pb.seed)
     assert abs(gl - ol) <= 1e-5 * abs(ol)
     assert np.isfinite(emb).all()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf, 3e38])
+@pytest.mark.parametrize("op,cmp", [("identity", "dot"), ("translation", "cos")])
+@pytest.mark.parametrize("loss", ["ranking", "logistic", "softmax"])
+def test_a_row_that_is_no_number_stays_in_its_chunk(loss, op, cmp, value):
+    """Whatever such a row does to its own chunk's products, rows that only the
+    step's other chunks touch get the bits that they get without it."""
+    C, U, m = 100, 28, 300
+    pb = make_problem(op, cmp, loss, R=1, n=900, m=m, d=33, C=C, U=U, S=3, seed=5, zipf=0.5)
+    bad = 0
+    pb.src[pb.src == bad] = 1
+    pb.dst[pb.dst == bad] = 1
+    pb.src[3] = pb.dst[20] = bad   # chunk 0
+    negs = O.step_negatives(oracle_model(pb), 0, 0, O.make_chunks(m, C, None, "consecutive"), pb.seed, U)
+    assert not any((n == bad).any() for pair in negs[1:] for n in pair)
+    first = np.r_[pb.src[:C], pb.dst[:C], negs[0][0], negs[0][1]]
+    others = np.setdiff1d(np.r_[pb.src[C:], pb.dst[C:], negs[1][0], negs[1][1], negs[2][0], negs[2][1]], first)
+    assert len(others) > 100
+    got = []
+    for row in (pb.parts[0][bad].copy(), np.float32(value)):
+        pb.parts[0][bad] = row
+        gm = GpuModel(pb)
+        try:
+            gm.train()
+            got.append(gm.state())
+        finally:
+            gm.close()
+    for key in ("emb", "G"):
+        a, b = (g[key][0][others] for g in got)
+        assert np.isfinite(a).all()
+        np.testing.assert_array_equal(a, b)
