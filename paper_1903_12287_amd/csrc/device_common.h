@@ -130,33 +130,25 @@ __device__ __forceinline__ float sigmoidf(float x) {
   return e / (1.0f + e);
 }
 
-// 1 / x and a / x for normal x: the hardware estimate, a Newton step and, for
-// the quotient, its residual added (three and six instructions; an IEEE
-// division takes ten).  Where the logistic divides both round as the IEEE
-// division does: compared for every float32 u of [1, 2] (1 / u) and every
-// e of [2^-25, 1] (e / ((1 + e) - 1); without the residual one in four differs
-// by a unit).
+// 1 / x for normal x: the hardware estimate and a Newton step (three
+// instructions; an IEEE division takes ten).  For every float32 of [1, 2] it
+// rounds as the IEEE division does.
 __device__ __forceinline__ float rcp_newton(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(fmaf(-x, r, 1.0f), r, r);
 }
-__device__ __forceinline__ float div_newton(float a, float x) {
-  const float r = rcp_newton(x), q = a * r;
-  return fmaf(fmaf(-x, q, a), r, q);
-}
 
 // sigmoid(s) and softplus(s) = log(1 + e^s) from one exponential
 // e = exp(-|s|) in (0, 1]: sigmoid = 1/(1+e) or e/(1+e), softplus =
-// max(s, 0) + log1p(e), with log1p(e) = log(u) * e / (u - 1), u = 1 + e,
-// which stays accurate when e is tiny (u - 1 is then exact)
+// max(s, 0) + log1p(e), with log1p(e) = log(u) + (e - (u - 1)) / u, u = 1 + e:
+// what u's rounding left out (exact) comes back to first order, and all of e
+// where it is tiny
 __device__ __forceinline__ void logistic_pair(float s, float& sig, float& sp) {
   const float e = __expf(-fabsf(s));
   const float u = 1.0f + e;
   const float r = rcp_newton(u);
   sig = s >= 0.0f ? r : e * r;
-  const float um1 = u - 1.0f;
-  const float l1p = um1 == 0.0f ? e : __logf(u) * div_newton(e, um1);
-  sp = fmaxf(s, 0.0f) + l1p;
+  sp = fmaxf(s, 0.0f) + fmaf(e - (u - 1.0f), r, __logf(u));
 }
 
 // round-to-nearest-even fp32 -> bf16 (finite inputs)
