@@ -226,9 +226,12 @@ inline int op_backward_blocks(int C, int U, int cmp) {
 }
 
 // ---- sort, segments, updates ----------------------------------------------------
-// sorted positions per wave of the segment update: 8 up to SEG_SHORT_MAX
-// positions, else 32
-#define SEG_SHORT_MAX 16384
+// sorted positions per wave of the segment update: 8 up to SEG_SHORT_ANY
+// positions, and with at least SEG_SHORT_ROWS rows a table up to SEG_SHORT_MAX,
+// uniform draws counted half; else 32
+#define SEG_SHORT_ANY 16384
+#define SEG_SHORT_MAX 32768
+#define SEG_SHORT_ROWS 1024
 inline int64_t segment_blocks(int64_t n) { return n / 8 + 2; }
 
 struct SortWork {

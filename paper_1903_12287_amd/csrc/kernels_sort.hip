@@ -13,6 +13,8 @@
 // wave of the block where it starts adds them in block order and updates it.
 // No scan or compaction is needed, and the summation order is fixed, so the
 // result does not depend on scheduling.
+#include <algorithm>
+
 #include "kernels.h"
 #include "row_ops.h"
 
@@ -765,17 +767,29 @@ static void seg_update(const StepGeom& g, const StepBufs& b, const uint32_t* key
     span<<<blocks + extra2, 256, 0, s>>>(g, b, keys, n, width, w.partial, w.segflag, lr, rr, blocks);
   };
   // A wave's block is a serial chain, so few positions go in short blocks (512
-  // waves of 32 for 1,024 SIMDs at the line).  Four times as many pieces cross a
-  // block's end, though, and one wave adds a long segment's.  The line is where
-  // that costs what the blocks save even where a few rows hold most positions.
-  // Both passes together, blocks of 32 and of 8, d = 128, at the line (16,368
-  // positions) a million rows alike 24.5 and 14.1 us, 10,000 rows by Zipf's law
-  // with exponent 1.1 20.6 and 14.7, with 1.5 21.7 and 20.2, 20 rows 13.7 and
-  // 14.2; at 24,552 24.5 and 16.0, 19.7 and 17.1, 21.7 and 25.0, 14.7 and 17.0;
-  // at 65,472 32.2 and 27.4, 20.2 and 29.5, 26.7 and 51.2, 20.3 and 36.6.
+  // waves of 32 for 1,024 SIMDs at SEG_SHORT_ANY).  Four times as many pieces
+  // cross a block's end, though, and one wave adds a long segment's.
+  //
+  // Up to SEG_SHORT_ANY that costs no more than the blocks save even where a
+  // few rows hold most positions.  Both passes together, blocks of 32 and of 8,
+  // d = 128, at 16,368 positions a million rows alike 24.5 and 14.1 us, 10,000
+  // rows by Zipf's law with exponent 1.1 20.6 and 14.7, with 1.5 21.7 and 20.2,
+  // 20 rows 13.7 and 14.2; at 65,472 32.2 and 27.4, 20.2 and 29.5, 26.7 and
+  // 51.2, 20.3 and 36.6.
+  //
+  // Between, it depends on the edges' positions, whose rows follow the graph's
+  // degrees; the uniform draws spread over the table, if it is not small, and
+  // count half.  What blocks of 8 save of a whole step of d = 200, exponent 0.9
+  // to 1.2, 1,000 to 3 million rows: 20,800 positions 2 to 15 us, 32,000 of
+  // which a quarter uniform -2 to 12, three quarters 6 to 13, 48,000 of which
+  // three quarters 1 to 14 (here the line lies), half -3 to 14, a sixth -10 to
+  // 11.  30 rows lose 0 to 6, 4 to 11 and 11 to 23.
+  //
   // Relations, few and long, keep 32 (40,000 positions, 5,000 relations: 24 +
   // 19 us, in blocks of 8 13 + 61).
-  const bool few = MODE == SEG_ENTITY && n <= SEG_SHORT_MAX;
+  const bool small = std::min(g.rows_i, g.rows_j) < SEG_SHORT_ROWS;
+  const bool few = MODE == SEG_ENTITY && (n <= SEG_SHORT_ANY ||
+                                          (!small && n - (int64_t)g.nchunks * g.U <= SEG_SHORT_MAX));
   if (width <= 128) {
     few ? launch(seg_update_local<MODE, 2, 8>, seg_update_span<MODE, 2, 8>, 8)
         : launch(seg_update_local<MODE, 2, 32>, seg_update_span<MODE, 2, 32>, 32);
